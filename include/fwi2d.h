@@ -151,6 +151,12 @@ typedef struct {
                              (1|2, 2)                                        */
     int32_t adj_two_step_band_rows;   /* its band rows (4..4096), 0: default */
     int32_t adj_two_step_lane_cols;   /* its columns per lane, 0: default    */
+    /* With every field from band_rows on left 0, batched plans of up to about
+     * two million padded nodes over all shots run on tile kernels instead
+     * (several steps per launch with a tile's state in registers; the same
+     * traces bit for bit, gradients within FP32 rounding), where the plan
+     * estimates them faster.  fwi_plan_info always describes the strip
+     * kernels.                                                              */
 } fwi_exec;
 
 typedef struct {
@@ -408,8 +414,8 @@ fwi_status fwi_born_hessian(int32_t F, const float *omega, const float *spec, in
 
 /* Kernel classes of the per-launch timing below. */
 typedef enum {
-    FWI_KC_FWD_STEP = 0,   /* batched forward step (all shots)                 */
-    FWI_KC_ADJ_STEP = 1,   /* batched adjoint step with imaging                */
+    FWI_KC_FWD_STEP = 0,   /* batched forward step, or a tile launch's steps   */
+    FWI_KC_ADJ_STEP = 1,   /* batched adjoint step(s) with imaging, likewise   */
     FWI_KC_PLAIN_VEL = 2,  /* plain velocity update (one shot)                 */
     FWI_KC_PLAIN_PRES = 3, /* plain pressure update (one shot)                 */
     FWI_KC_PLAIN_ADJ_A = 4,/* plain adjoint velocity half + imaging            */

@@ -65,6 +65,14 @@ struct fwi_plan {
                              // kept at the receiver nodes alone
     bool adj2 = false;       // adjoint sweeps use the two-step kernel
     Sweep sweep_a2;          // its decomposition (shots per group of `sweep`)
+    // tile kernels (several steps per launch, state in registers): shapes,
+    // steps per launch and axes of the forward and adjoint tiles, shots per
+    // partial gradient, levels of the forward call's sampling buffer
+    struct Tiles {
+        bool on = false;
+        int fT = 0, aT = 0, levels = 0;
+        TileAxis fx{}, fz{}, ax{}, az{};
+    } tile;
     int device;
     Geo geo;
     long long SS, ST;  // per-shot floats of a state record / a store record
@@ -75,7 +83,7 @@ struct fwi_plan {
     struct TabOff {
         size_t pml, zpad, st;                            // built on the device
         size_t sij, sw, ri, rw, in, is, ip, ir, iw, win, col; // copied from blob
-        size_t swin, rnode;                              // copied from blob
+        size_t swin, rnode, rptr, irc;                   // copied from blob
         size_t blob;                                     // offset of blob's image
         size_t bytes;                                    // size of the region
     } to{};
@@ -170,11 +178,17 @@ struct Layout {
     size_t mid;   // p^{n+1} of a two-step launch outside the stored history
     size_t injacc;   // R^T r^{n-1} per injection node (two-step adjoint)
     size_t nodes;    // p^{n+1} at the receiver nodes (two-step forward, level only sampled)
+    size_t hist;     // levels to sample (tile forward without a kept history)
     size_t total;
 };
 
 int batch_of(const fwi_plan *p) { return p->mode == FWI_EXEC_PLAIN ? 1 : p->Spad; }
 int groups_of(const fwi_plan *p) { return p->mode == FWI_EXEC_PLAIN ? 1 : p->sweep.ngroups; }
+// partial gradients of a backward sweep
+int partials_of(const fwi_plan *p) { return p->tile.on ? p->S : groups_of(p); }
+
+// steps of R^T r staged at a time for the tile adjoint
+constexpr int kStageSteps = 64;
 
 Layout layout(const fwi_plan *p, int op)
 {
@@ -213,6 +227,8 @@ Layout layout(const fwi_plan *p, int op)
     L.Q = take((size_t)p->S * p->grid.nt);
     L.work[0] = take((size_t)B * p->SS);
     L.work[1] = take((size_t)B * p->SS);
+    if (p->tile.on && op == FWI_OP_FORWARD)
+        L.hist = take((size_t)p->tile.levels * p->S * align64(g.N));
     if (p->two_step)
         L.mid = take((size_t)B * p->ST);
     if (p->samp_nodes)
@@ -222,15 +238,19 @@ Layout layout(const fwi_plan *p, int op)
         L.lam[1] = take((size_t)B * p->SS);
         L.ckpt = take((size_t)(p->nseg - 1) * B * p->SS);
         L.store = take((size_t)(p->k + 1) * B * p->ST);
-        L.gpart = take((size_t)groups_of(p) * 3 * g.N);
+        L.gpart = take((size_t)partials_of(p) * 3 * g.N);
         L.fold = take(2 * (size_t)g.N);
         L.traces = take(ntr);
         L.resid = take(ntr);
         L.partials = take(misfit_blocks(ntr));
-        if (p->adj2)
+        if (p->tile.on)
+            L.injacc = take((size_t)std::max(p->inj_nodes, 1) * std::min(kStageSteps, p->grid.nt));
+        else if (p->adj2)
             L.injacc = take((size_t)std::max(p->inj_nodes, 1));
     }
     L.total = off;
+    if (op == FWI_OP_GRADIENT)   // a gradient workspace also serves a forward call
+        L.total = std::max(L.total, layout(p, FWI_OP_FORWARD).total);
     return L;
 }
 
@@ -265,6 +285,8 @@ struct DevTabs {
     int *inj_col = nullptr;        // grid column of each injection node
     unsigned *samp_win = nullptr;  // two-step forward: [S][Nz][strips]
     int4 *rec_node = nullptr;      // [S][nrec]: node index of each bilinear corner
+    int *inj_rowptr = nullptr;     // tile adjoint: [S][Nz + 1] first node of each row
+    unsigned *inj_rc = nullptr;    // row << 16 | column of each node
 };
 
 struct Ctx {
@@ -668,6 +690,130 @@ void sweep_backward(const Ctx &c, int s0, int nb, const float *resid, float *gpa
     }
 }
 
+// ------------------------------------------------------------ tile sweeps
+
+Recd tile_rec(const fwi_plan *p, float *base)
+{
+    return Recd{base, (unsigned)(p->SS * sizeof(float)),
+                (unsigned)((3 * p->geo.N + p->geo.Npml) * sizeof(float))};
+}
+
+// Forward steps n0 .. n1-1 of every shot from the state record batch `cur`;
+// p^{n0+1} .. p^{n1} go to hist (unless null).  The last state is written to
+// `last`, or to a work buffer if that is null; returns where it is.
+float *tile_steps_fwd(const Ctx &c, float *cur, int n0, int n1, float *hist, long long lvl,
+                      long long ss, float *last)
+{
+    const fwi_plan *p = c.pl;
+    float *w0 = c.f(c.L.work[0]), *w1 = c.f(c.L.work[1]);
+    for (int n = n0; n < n1;) {
+        const int t = std::min(p->tile.fT, n1 - n);
+        float *out = n + t == n1 && last ? last : (cur == w0 ? w1 : w0);
+        FwdTile a;
+        a.in = tile_rec(p, cur);
+        a.out = tile_rec(p, out);
+        a.hist = hist ? hist + (size_t)(n - n0) * lvl : nullptr;
+        a.lvl = lvl;
+        a.ss = ss;
+        a.Q = c.f(c.L.Q);
+        a.src_ij = (const int *)c.tb.src_ij;
+        a.src_w = (const float *)c.tb.src_w;
+        a.n = n;
+        a.nt = p->grid.nt;
+        a.T = t;
+        a.S = p->S;
+        a.x = p->tile.fx;
+        a.z = p->tile.fz;
+        Timed tm(c.pl, c.st, FWI_KC_FWD_STEP, true);
+        launch_tile_fwd(p->geo, c.tb.pml, c.tb.zpad, c.m.K, a, c.st, tm.b, tm.e);
+        cur = out;
+        n += t;
+    }
+    return cur;
+}
+
+// sweep_forward with the tile kernels: every level is written (to the store,
+// segment after segment, or to the sampling buffer) and sampled in runs.
+void tile_forward(const Ctx &c, bool keep, float *traces)
+{
+    const fwi_plan *p = c.pl;
+    const Geo &g = p->geo;
+    const int nt = p->grid.nt, B = batch_of(p);
+    float *cur = c.f(c.L.work[0]);
+    zero_state(c, cur, B);
+    const int run = keep ? p->k : p->tile.levels;
+    const long long ss = keep ? p->ST : align64(g.N);
+    const long long lvl = keep ? (long long)B * p->ST : (long long)p->S * ss;
+    float *hist = keep ? c.f(c.L.store) + lvl : c.f(c.L.hist);
+    for (int n0 = 0; n0 < nt; n0 += run) {
+        const int n1 = std::min(n0 + run, nt);
+        float *ck = keep && n1 < nt ? c.f(c.L.ckpt) + (size_t)(n0 / run) * B * p->SS : nullptr;
+        cur = tile_steps_fwd(c, cur, n0, n1, traces || n1 == nt ? hist : nullptr, lvl, ss, ck);
+        if (traces) {
+            Timed tm(c.pl, c.st, FWI_KC_SAMPLE);
+            launch_sample_hist(g, hist, lvl, ss, rec_of(c, 0), p->S, traces, nt, n0, n1 - n0,
+                               c.st);
+        }
+    }
+}
+
+// sweep_backward with the tile kernels, after tile_forward(keep = true).
+void tile_backward(const Ctx &c, const float *resid, float *gpart)
+{
+    const fwi_plan *p = c.pl;
+    const Geo &g = p->geo;
+    const int nt = p->grid.nt, k = p->k, B = batch_of(p);
+    const long long lvl = (long long)B * p->ST;
+    float *store = c.f(c.L.store), *injv = c.f(c.L.injacc);
+    float *lam[2] = {c.f(c.L.lam[0]), c.f(c.L.lam[1])};
+    const Inj inj = inj_of(c, 0, p->S);
+    zero_state(c, lam[0], B);
+    int li = 0;
+    for (int sg = p->nseg - 1; sg >= 0; --sg) {
+        const int n0 = sg * k, n1 = std::min(n0 + k, nt);
+        if (sg != p->nseg - 1) {
+            // recompute the segment from its checkpoint, keeping the pressure
+            float *cur = c.f(c.L.work[0]);
+            if (n0 == 0)
+                zero_state(c, cur, B);
+            else
+                cur = c.f(c.L.ckpt) + (size_t)(sg - 1) * B * p->SS;
+            tile_steps_fwd(c, cur, n0, n1, store + lvl, lvl, p->ST, nullptr);
+        }
+        // adjoint steps m = n1 .. n0+1; step m takes p^m and adds R^T r^{m-1}
+        for (int m = n1; m > n0;) {
+            const int cnt = std::min(kStageSteps, m - n0);
+            {
+                Timed tm(c.pl, c.st, FWI_KC_INJECT);
+                launch_inject_stage(inj, resid, p->nrec, nt, m - 1, cnt, injv, c.st);
+            }
+            for (int j = 0; j < cnt;) {
+                const int t = std::min(p->tile.aT, cnt - j);
+                AdjTile a;
+                a.in = tile_rec(p, lam[li]);
+                a.out = tile_rec(p, lam[li ^ 1]);
+                a.hist = store + (size_t)(m - j - n0) * lvl;
+                a.lvl = lvl;
+                a.ss = p->ST;
+                a.injv = injv + (size_t)j * inj.nnodes;
+                a.rowptr = c.tb.inj_rowptr;
+                a.injrc = c.tb.inj_rc;
+                a.nnodes = inj.nnodes;
+                a.gpart = gpart;
+                a.T = t;
+                a.S = p->S;
+                a.x = p->tile.ax;
+                a.z = p->tile.az;
+                Timed tm(c.pl, c.st, FWI_KC_ADJ_STEP, true);
+                launch_tile_adj(g, c.tb.pml, c.tb.zpad, c.m.K, a, c.st, tm.b, tm.e);
+                li ^= 1;
+                j += t;
+            }
+            m -= cnt;
+        }
+    }
+}
+
 fwi_status check_call(const fwi_plan *p, void *ws, size_t ws_bytes, int op)
 {
     if (!p)
@@ -724,6 +870,8 @@ Ctx make_ctx(fwi_plan *p, void *ws, void *stream, int op)
         c.tb.inj_col = (int *)(b + o.col);
         c.tb.samp_win = (unsigned *)(b + o.swin);
         c.tb.rec_node = (int4 *)(b + o.rnode);
+        c.tb.inj_rowptr = (int *)(b + o.rptr);
+        c.tb.inj_rc = (unsigned *)(b + o.irc);
         c.t = pml_tables(p, c.tb.pml);
     }
     c.m.K = c.f(c.L.Kpad);
@@ -784,7 +932,7 @@ fwi_status run_backward(const Ctx &c, int param, const float *m1, const float *m
     fwi_plan *p = c.pl;
     const Geo &g = p->geo;
     float *gpart = c.f(c.L.gpart);
-    int G = groups_of(p);
+    int G = partials_of(p);
     {
         Timed tm(p, c.st, FWI_KC_OTHER);
         launch_fill(gpart, (long long)G * 3 * g.N, 0.0f, c.st);
@@ -794,6 +942,8 @@ fwi_status run_backward(const Ctx &c, int param, const float *m1, const float *m
             sweep_forward(c, s, 1, true, nullptr);
             sweep_backward(c, s, 1, res, gpart);
         }
+    } else if (p->tile.on) {
+        tile_backward(c, res, gpart);
     } else {
         sweep_backward(c, 0, p->Spad, res, gpart);
     }
@@ -850,7 +1000,10 @@ fwi_status run_gradient(fwi_plan *p, int param, const float *m1, const float *m2
         }
         return launched("gradient");
     }
-    sweep_forward(c, 0, p->Spad, true, observed ? tr : nullptr);
+    if (p->tile.on)
+        tile_forward(c, true, observed ? tr : nullptr);
+    else
+        sweep_forward(c, 0, p->Spad, true, observed ? tr : nullptr);
     const float *res = adj_src;
     if (observed) {
         Timed tm(p, c.st, FWI_KC_OTHER);
@@ -858,6 +1011,97 @@ fwi_status run_gradient(fwi_plan *p, int param, const float *m1, const float *m2
         res = resid;
     }
     return run_backward(c, param, m1, m2, res, g1, g2);
+}
+
+}  // namespace
+
+namespace {
+
+// n tiles of `span` nodes over an axis of `len`, overlapping enough that each
+// owned node lies `halo` or more from the inner edges of its tile; n = 0 if
+// the span is too short.
+TileAxis tile_axis(int len, int span, int halo, int unit)
+{
+    const int hu = (halo + unit - 1) / unit * unit;   // owned ranges start at a whole lane
+    if (len <= span)
+        return {1, len, 0, hu, unit};
+    const int last = (len - span + unit - 1) / unit * unit;
+    const int most = span - halo - hu;
+    if (most < unit)
+        return {0, len, 0, hu, unit};
+    for (int n = 2;; ++n) {
+        int gap = 0, prev = 0;
+        for (int k = 1; k < n; ++k) {
+            const int f = k * last / (n - 1) / unit * unit;
+            gap = std::max(gap, f - prev);
+            prev = f;
+        }
+        if (gap <= most)
+            return {n, len, last, hu, unit};
+    }
+}
+
+// Tile kernels or strip kernels, and the steps per tile launch.
+//
+// A tile launch of T steps costs, with one 64 x 64 tile a workgroup on 256
+// compute units (MI355X, us; sides of 101 to 541 padded nodes, 1 to 32 shots,
+// T 2 to 8, within about 10%):
+//   forward  3 + rounds of two workgroups a unit (11 + 1.9 T), a half round
+//            (6.3 + 1.15 T)
+//   adjoint  2.5 + rounds of one workgroup a unit (7.5 + 1.95 T)
+// plus about 3.2 between launches: the load and the store of the tile, then
+// the arithmetic of its T steps.  More steps spread the first over more time
+// but shrink the owned part of a tile (64 - 6 T nodes a side), so T grows until
+// the tiles no longer fit one round.  The strip kernels take 24.5 us a step
+// for both sweeps while the launch is what bounds them and about 20.5 + 9.3
+// per million nodes (all shots) beyond.  The tiles win up to about two million
+// nodes (one shot of 141 x 141: 6.7 against 25.0; 10 of 161 x 161: 7.9 against
+// 26.9; 8 of 241 x 241: 11.9 against 26.8; 16 of 341 x 341: 28.9 against
+// 38.8; 16 of 441 x 441, 3.1 million: 52.8 against 52.2).
+//
+// A plan that sets any part of the decomposition keeps the strip kernels.
+fwi_plan::Tiles choose_tiles(const fwi_plan *p, const fwi_exec &ex)
+{
+    fwi_plan::Tiles t;
+    const Geo &g = p->geo;
+    if (ex.mode != FWI_EXEC_BATCHED || ex.band_rows || ex.shots_per_group || ex.lane_cols ||
+        ex.two_step || ex.two_step_band_rows || ex.two_step_shots_per_group ||
+        ex.two_step_lane_cols || ex.adj_two_step || ex.adj_two_step_band_rows ||
+        ex.adj_two_step_lane_cols || g.Nz > 32767 || g.Nx > 32767)
+        return t;
+    const double nodes = (double)g.N * p->S;
+    const double strips = std::max(24.5, 20.5 + 9.3e-6 * nodes);
+    if (nodes > 4e6)
+        return t;
+    double best[2] = {1e30, 1e30};
+    for (int T = 2; T <= 8; ++T) {
+        const TileAxis x = tile_axis(g.Nx, kTileX, 3 * T, kTileCols);
+        const TileAxis z = tile_axis(g.Nz, kTileZ, 3 * T, 1);
+        if (!x.n || !z.n)
+            continue;
+        const long long h = ((long long)x.n * z.n * p->S + 255) / 256;
+        const double f = 6.2 + (double)(h / 2) * (11 + 1.9 * T) + (double)(h % 2) * (6.3 + 1.15 * T);
+        const double a = 5.7 + (double)h * (7.5 + 1.95 * T);
+        if (f / T < best[0]) {
+            best[0] = f / T;
+            t.fT = T;
+            t.fx = x;
+            t.fz = z;
+        }
+        if (a / T < best[1]) {
+            best[1] = a / T;
+            t.aT = T;
+            t.ax = x;
+            t.az = z;
+        }
+    }
+    t.on = best[0] + best[1] < strips;
+    // levels that a forward call buffers for sampling: about 64 MB, whole
+    // launches
+    const double level = (double)p->S * (double)align64(g.N) * sizeof(float);
+    const int lv = (int)std::min(64.0, std::max(8.0, 64e6 / level));
+    t.levels = std::max(t.fT, lv / std::max(t.fT, 1) * t.fT);
+    return t;
 }
 
 }  // namespace
@@ -1153,6 +1397,7 @@ fwi_status fwi_plan_create(const fwi_grid *grid, const fwi_acq *acq, const fwi_e
                         "(records of a group must stay below 2 GiB)", (long long)g.N, spg);
         }
     }
+    p->tile = choose_tiles(p, ex);
     {
         // checkpoint interval: with ckpt_every = 0 the whole pressure history
         // is kept when it fits (plain: one shot's history <= 64 GiB;
@@ -1362,6 +1607,25 @@ fwi_status fwi_plan_create(const fwi_grid *grid, const fwi_acq *acq, const fwi_e
         p->samp_nodes = fits;
     }
 
+    // tile adjoint: the nodes of a shot lie in row order; where each row's
+    // begin, and every node's row and column
+    std::vector<int> inj_rowptr;
+    std::vector<unsigned> inj_rc;
+    if (p->tile.on) {
+        inj_rowptr.resize((size_t)S * (g.Nz + 1));
+        inj_rc.resize(inj_node.size());
+        for (int s = 0; s < S; ++s) {
+            int k = p->shot_node_ptr[s];
+            for (int i = 0; i <= g.Nz; ++i) {
+                while (k < p->shot_node_ptr[s + 1] && inj_node[k] < (long long)i * g.Nx)
+                    ++k;
+                inj_rowptr[(size_t)s * (g.Nz + 1) + i] = k;
+            }
+        }
+        for (size_t k = 0; k < inj_node.size(); ++k)
+            inj_rc[k] = ((unsigned)(inj_node[k] / g.Nx) << 16) | (unsigned)inj_col[k];
+    }
+
     if (hipGetDevice(&p->device) != hipSuccess) {
         delete p;
         return fail(FWI_EDEVICE, "no HIP device");
@@ -1393,6 +1657,8 @@ fwi_status fwi_plan_create(const fwi_grid *grid, const fwi_acq *acq, const fwi_e
     o.col = take(sizeof(int) * inj_col.size());
     o.swin = take(sizeof(unsigned) * samp_win.size());
     o.rnode = take(sizeof(int4) * rec_node.size());
+    o.rptr = take(sizeof(int) * inj_rowptr.size());
+    o.irc = take(sizeof(unsigned) * inj_rc.size());
     o.bytes = off;
     try {
         p->blob.assign(off - o.blob, 0);
@@ -1418,6 +1684,8 @@ fwi_status fwi_plan_create(const fwi_grid *grid, const fwi_acq *acq, const fwi_e
     put(o.col, inj_col.data(), sizeof(int) * inj_col.size());
     put(o.swin, samp_win.data(), sizeof(unsigned) * samp_win.size());
     put(o.rnode, rec_node.data(), sizeof(int4) * rec_node.size());
+    put(o.rptr, inj_rowptr.data(), sizeof(int) * inj_rowptr.size());
+    put(o.irc, inj_rc.data(), sizeof(unsigned) * inj_rc.size());
     *out = p;
     return FWI_OK;
 }
@@ -1491,6 +1759,8 @@ fwi_status fwi_forward(fwi_plan *p, int32_t param, const float *m1, const float 
     if (p->mode == FWI_EXEC_PLAIN) {
         for (int s = 0; s < p->S; ++s)
             sweep_forward(c, s, 1, false, traces + s * per_shot);
+    } else if (p->tile.on) {
+        tile_forward(c, false, traces);
     } else {
         sweep_forward(c, 0, p->Spad, false, traces);
     }
@@ -1601,6 +1871,8 @@ fwi_status fwi_forward_keep(fwi_plan *p, int32_t param, const float *m1, const f
     if (p->mode == FWI_EXEC_PLAIN) {
         for (int s = 0; s < p->S; ++s)
             sweep_forward(c, s, 1, false, traces + s * per_shot);
+    } else if (p->tile.on) {
+        tile_forward(c, true, traces);
     } else {
         sweep_forward(c, 0, p->Spad, true, traces);
     }

@@ -270,6 +270,56 @@ void launch_fused_fwd2(const Geo &g, const float *tabs, const float *model,
                        hipStream_t st, hipEvent_t e0 = nullptr, hipEvent_t e1 = nullptr);
 
 
+// ------------------------------------------------------------------ tiles
+// One axis of the tile kernels' decomposition: n tiles of a fixed span cover
+// `len` nodes, tile k starting at k last / (n - 1) rounded down to a multiple
+// of `unit` (columns per lane; 1 along z) and owning the nodes `halo` or more
+// from the edges it shares with other tiles.  last: start of the last tile.
+struct TileAxis {
+    int n, len, last, halo, unit;
+};
+// Columns per lane, rows per wave and waves of a workgroup: 64 x 64 nodes.
+constexpr int kTileCols = 1, kTileRows = 4, kTileWaves = 16;
+constexpr int kTileX = 64 * kTileCols, kTileZ = kTileRows * kTileWaves;
+// T forward steps from state n of every shot (record: vx, vz, p, pz N floats
+// apart); p^{n+1+j} of shot s also goes to hist + j lvl + s ss (floats) unless
+// hist is null.
+struct FwdTile {
+    Recd in, out;
+    float *hist;
+    long long lvl, ss;
+    const float *Q;         // [S][nt] time integral of the wavelet at n+1/2
+    const int *src_ij;      // [S][2]: row and column of the source's cell
+    const float *src_w;     // [S][4]: its weights
+    int n, nt, T, S;
+    TileAxis x, z;
+};
+// T adjoint steps m, m-1, ... (see k_tile.hip): p^{m-j} of shot s at
+// hist - j lvl + s ss; injv[j nnodes + k] holds R^T r^{m-1-j} at node k;
+// rowptr[s (Nz + 1) + i] the first node of shot s in row i or below, injrc
+// (row << 16 | column) of each node.  gpart [S][3][N].
+struct AdjTile {
+    Recd in, out;
+    const float *hist;
+    long long lvl, ss;
+    const float *injv;
+    const int *rowptr;
+    const unsigned *injrc;
+    int nnodes;
+    float *gpart;
+    int T, S;
+    TileAxis x, z;
+};
+void launch_tile_fwd(const Geo &g, const float *tabs, const float *zpad, const float *model,
+                     const FwdTile &a, hipStream_t st, hipEvent_t e0 = nullptr,
+                     hipEvent_t e1 = nullptr);
+void launch_tile_adj(const Geo &g, const float *tabs, const float *zpad, const float *model,
+                     const AdjTile &a, hipStream_t st, hipEvent_t e0 = nullptr,
+                     hipEvent_t e1 = nullptr);
+// R^T r^{n1 - j} at every node for j < nsteps: out[j nnodes + k].
+void launch_inject_stage(const Inj &inj, const float *resid, int nrec, int nt, int n1, int nsteps,
+                         float *out, hipStream_t st);
+
 // ------------------------------------------------------------------ born
 // Decomposition of the Born data and gradient launches.
 struct BornSplit {

@@ -294,6 +294,28 @@ __global__ void k_inject_pair(Inj inj, const float *resid, int nrec, int nt, int
     next[k] = inj_sum(inj, resid, nrec, nt, n - 1, k, s);
 }
 
+// R^T r of a run of steps, for the tile adjoint: out[j nnodes + k] = R^T
+// r^{n1 - j} at node k, j < nsteps.  A block covers 64 nodes by 64 steps: the
+// residuals are read along time, the sums written along the nodes through LDS.
+__global__ void __launch_bounds__(256) k_inject_stage(Inj inj, const float *resid, int nrec, int nt,
+                                                     int n1, int nsteps, float *out)
+{
+    __shared__ float tile[64][65];
+    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+    const int k0 = blockIdx.x * 64, j0 = blockIdx.y * 64;
+    for (int q = wv; q < 64; q += 4) {
+        const int k = k0 + q, j = j0 + lane;
+        if (k < inj.nnodes && j < nsteps)
+            tile[q][lane] = inj_sum(inj, resid, nrec, nt, n1 - j, k, inj.shot[k]);
+    }
+    __syncthreads();
+    for (int q = wv; q < 64; q += 4) {
+        const int k = k0 + lane, j = j0 + q;
+        if (k < inj.nnodes && j < nsteps)
+            out[(long long)j * inj.nnodes + k] = tile[lane][q];
+    }
+}
+
 __device__ inline float wave_sum(float v)
 {
     for (int off = 32; off > 0; off >>= 1)
@@ -617,6 +639,15 @@ void launch_inject_pair(const Geo &g, const Inj &inj, const float *resid, int nr
         return;
     hipLaunchKernelGGL(k_inject_pair, dim3(blocks_for(inj.nnodes)), dim3(kBlock), 0, st, inj,
                        resid, nrec, nt, n, lp, shot0, next);
+}
+
+void launch_inject_stage(const Inj &inj, const float *resid, int nrec, int nt, int n1, int nsteps,
+                         float *out, hipStream_t st)
+{
+    if (inj.nnodes <= 0 || nsteps <= 0)
+        return;
+    hipLaunchKernelGGL(k_inject_stage, dim3(blocks_for(inj.nnodes, 64), blocks_for(nsteps, 64)),
+                       dim3(256), 0, st, inj, resid, nrec, nt, n1, nsteps, out);
 }
 
 int misfit_blocks(long long n)
