@@ -119,9 +119,12 @@ typedef struct {
                              lowered to the smallest one giving the same
                              number of bands)                                */
     int32_t shots_per_group; /* batched kernels: shots a wave advances together;
-                             0: default (with the two-step adjoint 2, or 1
-                             when 16-row bands of two-shot waves would not
-                             fill the device once; without it up to 4)      */
+                             0: default (one-step kernels: with the two-step
+                             adjoint 2, or 1 when 16-row bands of two-shot
+                             waves would not fill the device once; without
+                             it up to 4.  The two-step adjoint then takes 1,
+                             2 or 4 by its own estimate, which fwi_plan_info
+                             does not report)                               */
     int32_t lane_cols;    /* batched kernels: adjacent grid columns each lane
                              holds, 1, 2 or 4; 0: default.  Supported
                              (shots_per_group, lane_cols) pairs: lane_cols 1
@@ -146,9 +149,8 @@ typedef struct {
                              launch (the intermediate adjoint state stays on
                              chip; same results bit for bit): 0 default (on
                              where supported), 1 off, 2 on.  The two-step
-                             adjoint uses the shots per group of the one-step
-                             kernels; supported (shots, cols): (1|2|4, 1),
-                             (1|2, 2)                                        */
+                             adjoint uses shots_per_group where that is set;
+                             supported (shots, cols): (1|2|4, 1), (1|2, 2)   */
     int32_t adj_two_step_band_rows;   /* its band rows (4..4096), 0: default */
     int32_t adj_two_step_lane_cols;   /* its columns per lane, 0: default    */
     /* With every field from band_rows on left 0, batched plans of up to about

@@ -9,7 +9,6 @@
 #include <cmath>
 #include <cstdio>
 #include <cstring>
-#include <map>
 #include <mutex>
 #include <string>
 #include <vector>
@@ -64,7 +63,9 @@ struct fwi_plan {
     bool samp_nodes = false; // its intermediate level, when only sampled, is
                              // kept at the receiver nodes alone
     bool adj2 = false;       // adjoint sweeps use the two-step kernel
-    Sweep sweep_a2;          // its decomposition (shots per group of `sweep`)
+    Sweep sweep_a2;          // its decomposition, with shot groups of its own
+    int adj_list = 0;        // listed nodes of the strip adjoints (0: they do not add R^T r)
+    int samp_list = 0;       // listed nodes of the two-step forward kernel
     // tile kernels (several steps per launch, state in registers): shapes,
     // steps per launch and axes of the forward and adjoint tiles, shots per
     // partial gradient, levels of the forward call's sampling buffer
@@ -82,8 +83,8 @@ struct fwi_plan {
     // table region).
     struct TabOff {
         size_t pml, zpad, st;                            // built on the device
-        size_t sij, sw, ri, rw, in, is, ip, ir, iw, win, col; // copied from blob
-        size_t swin, rnode, rptr, irc;                   // copied from blob
+        size_t sij, sw, ri, rw, in, is, ip, ir, iw, win; // copied from blob
+        size_t swin, rnode, rptr, irc, aln, alc, alp, slc, slp;   // copied from blob
         size_t blob;                                     // offset of blob's image
         size_t bytes;                                    // size of the region
     } to{};
@@ -176,18 +177,23 @@ struct Layout {
     size_t work[2], lam[2];
     size_t ckpt, store, gpart, fold, traces, resid, partials;
     size_t mid;   // p^{n+1} of a two-step launch outside the stored history
-    size_t injacc;   // R^T r^{n-1} per injection node (two-step adjoint)
+    size_t injacc;   // R^T r of up to kStageSteps steps per injection node (batched adjoint)
     size_t nodes;    // p^{n+1} at the receiver nodes (two-step forward, level only sampled)
     size_t hist;     // levels to sample (tile forward without a kept history)
     size_t total;
 };
 
 int batch_of(const fwi_plan *p) { return p->mode == FWI_EXEC_PLAIN ? 1 : p->Spad; }
-int groups_of(const fwi_plan *p) { return p->mode == FWI_EXEC_PLAIN ? 1 : p->sweep.ngroups; }
 // partial gradients of a backward sweep
-int partials_of(const fwi_plan *p) { return p->tile.on ? p->S : groups_of(p); }
+int partials_of(const fwi_plan *p)
+{
+    return p->mode == FWI_EXEC_PLAIN ? 1
+           : p->tile.on              ? p->S
+           : p->adj2                 ? p->sweep_a2.ngroups
+                                     : p->sweep.ngroups;
+}
 
-// steps of R^T r staged at a time for the tile adjoint
+// steps of R^T r staged at a time for the batched adjoints (even)
 constexpr int kStageSteps = 64;
 
 Layout layout(const fwi_plan *p, int op)
@@ -232,7 +238,7 @@ Layout layout(const fwi_plan *p, int op)
     if (p->two_step)
         L.mid = take((size_t)B * p->ST);
     if (p->samp_nodes)
-        L.nodes = take((size_t)std::max(p->inj_nodes, 1));
+        L.nodes = take((size_t)std::max(p->samp_list, 1));
     if (op == FWI_OP_GRADIENT) {
         L.lam[0] = take((size_t)B * p->SS);
         L.lam[1] = take((size_t)B * p->SS);
@@ -243,10 +249,9 @@ Layout layout(const fwi_plan *p, int op)
         L.traces = take(ntr);
         L.resid = take(ntr);
         L.partials = take(misfit_blocks(ntr));
-        if (p->tile.on)
-            L.injacc = take((size_t)std::max(p->inj_nodes, 1) * std::min(kStageSteps, p->grid.nt));
-        else if (p->adj2)
-            L.injacc = take((size_t)std::max(p->inj_nodes, 1));
+        if (p->mode != FWI_EXEC_PLAIN)
+            L.injacc = take((size_t)std::max(std::max(p->inj_nodes, p->adj_list), 1) *
+                                std::min(kStageSteps, p->grid.nt) + 64);
     }
     L.total = off;
     if (op == FWI_OP_GRADIENT)   // a gradient workspace also serves a forward call
@@ -281,12 +286,13 @@ struct DevTabs {
     long long *inj_node = nullptr;
     int *inj_shot = nullptr, *inj_cptr = nullptr, *inj_crec = nullptr;
     float *inj_cw = nullptr;
-    unsigned *inj_win = nullptr;   // two-step adjoint: [Spad][Nz + 2 kZPad][strips]
-    int *inj_col = nullptr;        // grid column of each injection node
+    unsigned *inj_win = nullptr;   // strip adjoint: [Spad][Nz + 2 kZPad][strips]
+    int *al_node = nullptr, *al_col = nullptr, *al_ptr = nullptr;   // its node list
     unsigned *samp_win = nullptr;  // two-step forward: [S][Nz][strips]
+    int *sl_col = nullptr, *sl_ptr = nullptr;   // its node list
     int4 *rec_node = nullptr;      // [S][nrec]: node index of each bilinear corner
     int *inj_rowptr = nullptr;     // tile adjoint: [S][Nz + 1] first node of each row
-    unsigned *inj_rc = nullptr;    // row << 16 | column of each node
+    unsigned *inj_rc = nullptr;    // tile adjoint: row << 16 | column of each node
 };
 
 struct Ctx {
@@ -432,86 +438,87 @@ void step_fwd2(const Ctx &c, int s0, int nb, const State &in, Fld mid, const Sta
     a.vout = recd(out.vx, 2 * g.N);
     a.pout = recd(out.p, g.N + g.Npml);
     a.pmid = recd(mid, g.N + g.Npml);
+    a.zpad = c.tb.zpad;
     a.Q = src_of(c, s0).Q;
     a.nodes = midw == 1 ? c.f(c.L.nodes) : nullptr;
     a.nwin = c.tb.samp_win;
-    a.ncol = c.tb.inj_col;
+    a.nptr = c.tb.sl_ptr;
+    a.ncol = c.tb.sl_col;
     a.midw = midw;
     a.n = n;
     Timed tm(c.pl, c.st, FWI_KC_FWD_PAIR, true);
     launch_fused_fwd2(g, c.tb.pml, c.m.K, c.tb.sweep_tabs, p->S, p->sweep2, a, c.st, tm.b, tm.e);
 }
 
-// One adjoint step n for shots [s0, s0+nb): injects R^T r^n into `in`, then
-// writes the adjoint state of step n into `out` and accumulates the
-// sensitivities into gpart.
-void step_adj(const Ctx &c, int s0, int nb, const State &in, const State &out, Fld pn, Fld pzn,
-              Fld pn1, Fld pzn1, const float *resid, float *gpart, int n)
+// One plain adjoint step n of shot s0: injects R^T r^n into `in`, then writes
+// the adjoint state of step n into `out` and accumulates the sensitivities
+// into gpart.  pn, pn1 (and splits): pressure levels n and n+1.
+void step_adj_plain(const Ctx &c, int s0, const State &in, const State &out, Fld pn, Fld pzn,
+                    Fld pn1, Fld pzn1, const float *resid, float *gpart, int n)
 {
     const fwi_plan *p = c.pl;
     const Geo &g = p->geo;
     {
         Timed tm(c.pl, c.st, FWI_KC_INJECT);
-        launch_inject(g, inj_of(c, s0, real_shots(p, s0, nb)), resid, p->nrec, p->grid.nt, n,
-                      in.p, s0, c.st);
+        launch_inject(g, inj_of(c, s0, 1), resid, p->nrec, p->grid.nt, n, in.p, s0, c.st);
     }
-    if (p->mode == FWI_EXEC_PLAIN) {
-        {
-            Timed tm(c.pl, c.st, FWI_KC_PLAIN_ADJ_A);
-            launch_plain_adj_a(g, c.t, c.m, in.vx.p, in.vz.p, out.vx.p, out.vz.p, in.p.p,
-                               in.pz.p, pn.p, pzn.p, pn1.p, pzn1.p, gpart, gpart + g.N,
-                               gpart + 2 * g.N, c.st);
-        }
-        Timed tm(c.pl, c.st, FWI_KC_PLAIN_ADJ_B);
-        launch_plain_adj_b(g, c.t, c.m, out.vx.p, out.vz.p, in.p.p, in.pz.p, out.p.p, out.pz.p,
-                           c.st);
-    } else {
-        // adjoint records: lvx, lvz, lpx, lpz; pressure history: p then split
-        (void)pzn;
-        (void)pzn1;
-        AdjStep a;
-        a.lin = recd(in.vx, 3 * g.N + g.Npml);
-        a.lout = recd(out.vx, 3 * g.N + g.Npml);
-        a.pn = recd(pn, g.N + g.Npml);
-        a.pn1 = recd(pn1, g.N + g.Npml);
-        a.gpart = gpart;
-        a.n = n;
+    {
+        Timed tm(c.pl, c.st, FWI_KC_PLAIN_ADJ_A);
+        launch_plain_adj_a(g, c.t, c.m, in.vx.p, in.vz.p, out.vx.p, out.vz.p, in.p.p, in.pz.p,
+                           pn.p, pzn.p, pn1.p, pzn1.p, gpart, gpart + g.N, gpart + 2 * g.N, c.st);
+    }
+    Timed tm(c.pl, c.st, FWI_KC_PLAIN_ADJ_B);
+    launch_plain_adj_b(g, c.t, c.m, out.vx.p, out.vz.p, in.p.p, in.pz.p, out.p.p, out.pz.p, c.st);
+}
+
+AdjNodes nodes_of(const Ctx &c)
+{
+    return AdjNodes{c.pl->adj_list ? c.tb.inj_win : nullptr, c.tb.al_ptr, c.tb.al_col};
+}
+
+// Batched adjoint step m: pm holds p^m, injv R^T r^{m-1} per node.
+void step_adj(const Ctx &c, const State &in, const State &out, Fld pm, const float *injv,
+              float *gpart)
+{
+    const fwi_plan *p = c.pl;
+    const Geo &g = p->geo;
+    AdjStep a;   // adjoint records: lvx, lvz, lpx, lpz
+    a.lin = recd(in.vx, 3 * g.N + g.Npml);
+    a.lout = recd(out.vx, 3 * g.N + g.Npml);
+    a.pn = recd(pm, g.N);
+    a.nd = nodes_of(c);
+    a.injv = injv;
+    a.gpart = gpart;
+    {
         Timed tm(c.pl, c.st, FWI_KC_ADJ_STEP, true);
-        launch_fused_adj(g, c.tb.pml, c.m.K, c.tb.sweep_tabs, p->S, p->sweep, a, c.st, tm.b,
-                         tm.e);
+        launch_fused_adj(g, c.tb.pml, c.m.K, p->sweep, a, c.st, tm.b, tm.e);
+    }
+    if (!a.nd.win) {
+        Timed tm(c.pl, c.st, FWI_KC_INJECT);
+        launch_inject_post(g, inj_of(c, 0, p->S), injv, p->sweep.spg, out.p, pm, c.m.K, gpart,
+                           c.st);
     }
 }
 
-// Two adjoint steps n, n-1 for shots [s0, s0+nb) (batched only): injects
-// R^T r^n into `in` and keeps R^T r^{n-1} per node for the launch, which
-// adds it between its two steps; writes the adjoint state of step n-1 into
-// `out` and accumulates both steps' sensitivities into gpart.  pm, pn, pn1:
-// pressure records (p, then its split) at levels n-1, n, n+1.
-void step_adj2(const Ctx &c, int s0, int nb, const State &in, const State &out, Fld pm, Fld pn,
-               Fld pn1, const float *resid, float *gpart, int n)
+// Batched adjoint steps m, m-1: pm1 holds p^{m-1}, the next level of the
+// store p^m; injA, injB: R^T r^{m-1}, R^T r^{m-2} per node (injB may be null).
+void step_adj2(const Ctx &c, const State &in, const State &out, Fld pm1, const float *injA,
+               const float *injB, float *gpart)
 {
     const fwi_plan *p = c.pl;
     const Geo &g = p->geo;
-    float *acc = c.f(c.L.injacc);
-    {
-        Timed tm(c.pl, c.st, FWI_KC_INJECT);
-        launch_inject_pair(g, inj_of(c, s0, real_shots(p, s0, nb)), resid, p->nrec, p->grid.nt,
-                           n, in.p, s0, acc, c.st);
-    }
     AdjStep2 a;
     a.lin = recd(in.vx, 3 * g.N + g.Npml);
     a.lout = recd(out.vx, 3 * g.N + g.Npml);
-    a.pm1 = recd(pm, g.N + g.Npml);
-    a.lvl = (unsigned)((const char *)pn.p - (const char *)pm.p);
-    (void)pn1;   // the level after pn, lvl bytes further (checked at plan creation)
+    a.pm1 = recd(pm1, g.N);
+    a.lvl = (unsigned)((size_t)p->Spad * p->ST * sizeof(float));   // (below 2 GiB: plan creation)
     a.gpart = gpart;
     a.zpad = c.tb.zpad;
-    a.injwin = c.tb.inj_win;
-    a.injcol = c.tb.inj_col;
-    a.injacc = acc;
-    a.n = n;
+    a.nd = nodes_of(c);
+    a.injA = injA;
+    a.injB = injB;
     Timed tm(c.pl, c.st, FWI_KC_ADJ_PAIR, true);
-    launch_fused_adj2(g, c.tb.pml, c.m.K, p->S, p->sweep_a2, a, c.st, tm.b, tm.e);
+    launch_fused_adj2(g, c.tb.pml, c.m.K, p->sweep_a2, a, c.st, tm.b, tm.e);
 }
 
 void zero_state(const Ctx &c, float *base, int nb)
@@ -635,6 +642,13 @@ void sweep_backward(const Ctx &c, int s0, int nb, const float *resid, float *gpa
     State lam[2] = {state_at(c.f(c.L.lam[0]), p), state_at(c.f(c.L.lam[1]), p)};
     zero_state(c, c.f(c.L.lam[0]), nb);
     int li = 0;
+    // batched: next adjoint step; R^T r^n of levels n = top .. staged lie in
+    // injv, kStageSteps (an even number) at a time
+    int m = nt, top = -1, staged = nt;
+    float *injv = c.f(c.L.injacc);
+    const Inj inj = inj_of(c, 0, p->S);
+    const int *list = p->adj_list ? c.tb.al_node : nullptr;
+    const int nlist = list ? p->adj_list : inj.nnodes;
     for (int sg = p->nseg - 1; sg >= 0; --sg) {
         int n0 = sg * k, n1 = std::min(n0 + k, nt);
         if (sg != p->nseg - 1) {
@@ -672,18 +686,34 @@ void sweep_backward(const Ctx &c, int s0, int nb, const float *resid, float *gpa
                 cw = nw;
             }
         }
-        // adjoint steps n1-1 .. n0, in pairs where the two-step kernel is on
-        for (int n = n1 - 1; n >= n0;) {
-            if (p->adj2 && n - 1 >= n0) {
-                auto am = slot(n - 1 - n0), a = slot(n - n0), b = slot(n + 1 - n0);
-                step_adj2(c, s0, nb, lam[li], lam[li ^ 1], am.first, a.first, b.first, resid,
-                          gpart, n);
-                n -= 2;
-            } else {
+        if (p->mode == FWI_EXEC_PLAIN) {
+            for (int n = n1 - 1; n >= n0; --n) {
                 auto a = slot(n - n0), b = slot(n + 1 - n0);
-                step_adj(c, s0, nb, lam[li], lam[li ^ 1], a.first, a.second, b.first, b.second,
-                         resid, gpart, n);
-                n -= 1;
+                step_adj_plain(c, s0, lam[li], lam[li ^ 1], a.first, a.second, b.first, b.second,
+                               resid, gpart, n);
+                li ^= 1;
+            }
+            continue;
+        }
+        // adjoint steps m down to n0+1, where the two-step kernel is on in
+        // pairs: a pair may reach into the next segment by one step, whose
+        // level n0 is slot 0 (step 0, of level 0, adds nothing)
+        while (m > n0) {
+            if (m - 1 < staged) {
+                staged = m - std::min(kStageSteps, m);
+                top = m - 1;
+                Timed tm(c.pl, c.st, FWI_KC_INJECT);
+                launch_inject_stage(inj, list, nlist, resid, p->nrec, nt, top, top - staged + 1,
+                                    injv, c.st);
+            }
+            const float *va = injv + (size_t)(top - (m - 1)) * nlist;
+            if (p->adj2) {
+                step_adj2(c, lam[li], lam[li ^ 1], slot(m - 1 - n0).first, va,
+                          m > 1 ? va + nlist : nullptr, gpart);
+                m -= 2;
+            } else {
+                step_adj(c, lam[li], lam[li ^ 1], slot(m - n0).first, va, gpart);
+                m -= 1;
             }
             li ^= 1;
         }
@@ -785,7 +815,8 @@ void tile_backward(const Ctx &c, const float *resid, float *gpart)
             const int cnt = std::min(kStageSteps, m - n0);
             {
                 Timed tm(c.pl, c.st, FWI_KC_INJECT);
-                launch_inject_stage(inj, resid, p->nrec, nt, m - 1, cnt, injv, c.st);
+                launch_inject_stage(inj, nullptr, inj.nnodes, resid, p->nrec, nt, m - 1, cnt, injv,
+                                    c.st);
             }
             for (int j = 0; j < cnt;) {
                 const int t = std::min(p->tile.aT, cnt - j);
@@ -867,7 +898,11 @@ Ctx make_ctx(fwi_plan *p, void *ws, void *stream, int op)
         c.tb.inj_crec = (int *)(b + o.ir);
         c.tb.inj_cw = (float *)(b + o.iw);
         c.tb.inj_win = (unsigned *)(b + o.win);
-        c.tb.inj_col = (int *)(b + o.col);
+        c.tb.al_node = (int *)(b + o.aln);
+        c.tb.al_col = (int *)(b + o.alc);
+        c.tb.al_ptr = (int *)(b + o.alp);
+        c.tb.sl_col = (int *)(b + o.slc);
+        c.tb.sl_ptr = (int *)(b + o.slp);
         c.tb.samp_win = (unsigned *)(b + o.swin);
         c.tb.rec_node = (int4 *)(b + o.rnode);
         c.tb.inj_rowptr = (int *)(b + o.rptr);
@@ -1280,16 +1315,14 @@ fwi_status fwi_plan_create(const fwi_grid *grid, const fwi_acq *acq, const fwi_e
         // Defaults, from the autotuner's measurements on MI355X over padded
         // grids of 281 to 2081 nodes a side with 8 to 64 shots.
         //
-        // Band heights of the two-step kernels: a launch of W equal waves, R
-        // of which the device holds at once, runs about ceil(W / R) rounds,
-        // each as long as one band (H rows plus the 6 rows of the two-step
-        // halo).  Among the heights the autotuner tries, the smallest
-        // ceil(W / R) (H + 6) wins, ties going to the taller band.  Over
-        // those shapes this picks the measured best adjoint height in most
-        // of them and one within 6% of the best in the rest; the forward
-        // choices below come within 10%.
-        auto resident = [](bool adjoint, int sg, int cl) {
-            const int r = resident_waves2(adjoint, sg, cl);
+        // Band heights of the two-step forward kernel: a launch of W equal
+        // waves, R of which the device holds at once, runs about ceil(W / R)
+        // rounds, each as long as one band (H rows plus the 6 rows of the
+        // two-step halo).  Among the heights the autotuner tries, the smallest
+        // ceil(W / R) (H + 6) wins, ties going to the taller band; the choices
+        // come within 10% of the measured best.
+        auto resident = [](int sg, int cl) {
+            const int r = resident_waves2(sg, cl);
             return r > 0 ? r : 2048;   // two waves per SIMD of 256 compute units
         };
         auto pick_rows = [&](int Sp, int sg, int cl, int R, const int *cand, int nc) {
@@ -1306,7 +1339,44 @@ fwi_status fwi_plan_create(const fwi_grid *grid, const fwi_acq *acq, const fwi_e
             }
             return best;
         };
+        // Shots per wave and band height of the two-step adjoint: a row of a
+        // workgroup takes kRowUs[n - 1] us where a compute unit runs n
+        // workgroups at once (measured on MI355X at one column per lane;
+        // wider lanes are taken in proportion), a band H + 10 rows (its halo
+        // and the start of its windows), and taller bands lose some of the
+        // cache lines that the groups of a band share.  With more shots a wave
+        // moves fewer bytes (the model and the partial gradient once for all)
+        // but fewer waves run.  Against the best of all heights measured, the
+        // choice takes 1.02 times as long at 64 shots of 1081 x 1081 padded
+        // nodes (4 shots, 91 rows: 898 us against 1004 with 2 shots), 1.00 at
+        // 32 of 2081 x 2081 (4, 49: 1537 against 1749), 1.00 at 40 of 481 x
+        // 481 (2, 49: 155; 171 with 1, 177 with 4) and 1.00 at 13 of 413 x 531
+        // (1, 20: 57; 67 with 2).  Shots that only fill up a group cost the
+        // forward sweeps too.
+        auto adj_cost = [&](int sg, int cl, int H) {
+            static const double kRowUs[3][4] = {{1.2, 1.55, 1.9, 2.6}, {2.1, 2.55, 3.4, 0}, {3.6, 4.4, 0, 0}};
+            const int i = sg == 1 ? 0 : sg == 2 ? 1 : 2, most = sg == 1 ? 4 : sg == 2 ? 3 : 2;
+            const long long b = (sweep_of(g, p->S, H, sg, cl, 2).nwaves + 1023) / 1024;
+            const double us = (double)(b / most) * kRowUs[i][most - 1] +
+                              (b % most ? kRowUs[i][b % most - 1] : 0.0);
+            const double pad = (double)((p->S + sg - 1) / sg * sg) / p->S;
+            return us * cl * (H + 10) * (1.0 + H / 800.0) * (1.0 + 1.2 * (pad - 1.0));
+        };
         static const int kRowsAdj2[] = {12, 16, 20, 24, 32, 48, 64, 96, 128, 160, 192};
+        auto adj_rows = [&](int sg, int cl, double &cost) {
+            int best = 0;
+            for (int cand : kRowsAdj2) {
+                const int H = ex.adj_two_step_band_rows
+                                  ? ex.adj_two_step_band_rows
+                                  : balanced_rows(Nz, (int)std::min<long long>(cand, Nz));
+                const double c = adj_cost(sg, cl, H);
+                if (best == 0 || c < cost) {
+                    best = H;
+                    cost = c;
+                }
+            }
+            return best;
+        };
         static const int kRowsFwd2[] = {12, 14, 16, 18, 20, 24, 28, 32, 48, 64, 96};
         // the batched kernels address a shot group's records, the model and
         // a partial gradient with 32-bit byte offsets below 2^31
@@ -1321,20 +1391,14 @@ fwi_status fwi_plan_create(const fwi_grid *grid, const fwi_acq *acq, const fwi_e
         const bool adj2_wanted =
             p->mode != FWI_EXEC_PLAIN && ex.adj_two_step != 1 && adj2_fits(2);
         const int ca = ex.adj_two_step_lane_cols ? ex.adj_two_step_lane_cols : 1;
-        // Shot groups (shared by the one-step kernels and the two-step
-        // adjoint, whose partial gradients they share): with the two-step
-        // adjoint two shots a wave, or one when even 16-row bands of
-        // two-shot waves leave the device short of one round of waves
-        // (with four shots a wave that kernel needs all 256 VGPRs and ran
-        // about 1.5 times slower); without it up to four shots a wave.  One
-        // column per lane.
+        // Shot groups of the one-step kernels: with the two-step adjoint (they
+        // then only run what a forward segment leaves over) two shots a wave,
+        // or one when even 16-row bands of two-shot waves number fewer than
+        // two per SIMD; without it up to four.  One column per lane.
         int spg = ex.shots_per_group, cols = ex.lane_cols;
         if (spg == 0) {
             if (adj2_wanted) {
-                spg = p->S >= 2 ? 2 : 1;
-                if (spg == 2 && adj2_supported(2, ca) &&
-                    sweep_of(g, p->S, 16, 2, ca, 2).nwaves < resident(true, 2, ca))
-                    spg = 1;
+                spg = p->S >= 2 && sweep_of(g, p->S, 16, 2, ca, 2).nwaves >= 2048 ? 2 : 1;
             } else {
                 spg = p->S >= 4 ? 4 : (p->S >= 2 ? 2 : 1);
             }
@@ -1351,8 +1415,26 @@ fwi_status fwi_plan_create(const fwi_grid *grid, const fwi_acq *acq, const fwi_e
             H = balanced_rows(Nz, (int)std::min<long long>(64, std::max<long long>(
                                       8, (Nz + bands - 1) / bands)));
         }
-        p->sweep = sweep_of(g, p->S, H, spg, cols);
-        p->Spad = p->mode == FWI_EXEC_PLAIN ? p->S : p->sweep.ngroups * spg;
+        // shot groups of the two-step adjoint: those of the one-step kernels
+        // where the caller set them, else by its cost
+        int spg_a = spg;
+        if (ex.shots_per_group == 0 && adj2_wanted && adj2_supported(spg, ca)) {
+            double best = 0.0;
+            for (int sg = 1; sg <= 4; sg *= 2) {
+                double c = 0.0;
+                if (sg > p->S || !adj2_supported(sg, ca) || !adj2_fits(sg) ||
+                    (long long)sg * p->SS * 4 >= lim)
+                    continue;
+                (void)adj_rows(sg, ca, c);
+                if (best == 0.0 || c < best) {
+                    spg_a = sg;
+                    best = c;
+                }
+            }
+        }
+        const int fill = std::max(spg, spg_a);   // (powers of two)
+        p->Spad = p->mode == FWI_EXEC_PLAIN ? p->S : (p->S + fill - 1) / fill * fill;
+        p->sweep = sweep_of(g, p->Spad, H, spg, cols);
         // two-step forward kernel over the same padded shots: two columns
         // per lane; two shots a wave from 800 padded columns up, else one
         // (and one if the padded count is odd)
@@ -1365,13 +1447,11 @@ fwi_status fwi_plan_create(const fwi_grid *grid, const fwi_acq *acq, const fwi_e
         }
         int H2 = ex.two_step_band_rows;
         if (H2 == 0)
-            H2 = pick_rows(p->Spad, spg2, cols2, resident(false, spg2, cols2), kRowsFwd2,
+            H2 = pick_rows(p->Spad, spg2, cols2, resident(spg2, cols2), kRowsFwd2,
                            (int)(sizeof kRowsFwd2 / sizeof kRowsFwd2[0]));
         p->sweep2 = sweep_of(g, p->Spad, H2, spg2, cols2, 2);
         p->two_step = p->mode != FWI_EXEC_PLAIN && ex.two_step != 1 && p->Spad % spg2 == 0 &&
                       (long long)spg2 * p->SS * 4 < lim;
-        // two-step adjoint over the same shot groups (it shares their
-        // partial gradients with the one-step kernel)
         const bool a2ok = p->mode != FWI_EXEC_PLAIN && adj2_supported(spg, ca);
         if (ex.adj_two_step == 2 && !a2ok) {
             delete p;
@@ -1386,10 +1466,11 @@ fwi_status fwi_plan_create(const fwi_grid *grid, const fwi_acq *acq, const fwi_e
         }
         p->adj2 = ex.adj_two_step != 1 && a2ok && a2fits;
         int Ha = ex.adj_two_step_band_rows;
-        if (Ha == 0)
-            Ha = pick_rows(p->Spad, spg, ca, resident(true, spg, ca), kRowsAdj2,
-                           (int)(sizeof kRowsAdj2 / sizeof kRowsAdj2[0]));
-        p->sweep_a2 = sweep_of(g, p->Spad, Ha, spg, ca, 2);
+        if (Ha == 0) {
+            double c = 0.0;
+            Ha = adj_rows(spg_a, ca, c);
+        }
+        p->sweep_a2 = sweep_of(g, p->Spad, Ha, spg_a, ca, 2);
         if (p->mode != FWI_EXEC_PLAIN &&
             ((long long)spg * p->SS * 4 >= lim || 3 * g.N * 4 >= lim)) {
             delete p;
@@ -1473,8 +1554,14 @@ fwi_status fwi_plan_create(const fwi_grid *grid, const fwi_acq *acq, const fwi_e
     std::vector<int> inj_shot, inj_cptr, inj_crec;
     std::vector<float> inj_cw;
     p->shot_node_ptr.assign(S + 1, 0);
+    struct Touch {   // (a receiver touches a node once)
+        long long node;
+        int rec;
+        float w;
+    };
+    std::vector<Touch> touch;
     for (int s = 0; s < S; ++s) {
-        std::map<long long, std::vector<std::pair<int, float>>> nodes;
+        touch.clear();
         for (int r = 0; r < nr; ++r) {
             long long c = rec_idx[(size_t)s * nr + r];
             float4 w = rec_w[(size_t)s * nr + r];
@@ -1482,105 +1569,122 @@ fwi_status fwi_plan_create(const fwi_grid *grid, const fwi_acq *acq, const fwi_e
             float ws[4] = {w.x, w.y, w.z, w.w};
             for (int q = 0; q < 4; ++q)
                 if (ws[q] != 0.0f)
-                    nodes[cs[q]].push_back({r, ws[q]});
+                    touch.push_back({cs[q], r, ws[q]});
         }
-        for (auto &kv : nodes) {
-            inj_node.push_back(kv.first);
-            inj_shot.push_back(s);
-            inj_cptr.push_back((int)inj_crec.size());
-            for (auto &rw : kv.second) {
-                inj_crec.push_back(rw.first);
-                inj_cw.push_back(rw.second);
+        std::sort(touch.begin(), touch.end(), [](const Touch &a, const Touch &b) {
+            return a.node != b.node ? a.node < b.node : a.rec < b.rec;
+        });
+        for (const Touch &t : touch) {
+            if ((int)inj_node.size() == p->shot_node_ptr[s] || inj_node.back() != t.node) {
+                inj_node.push_back(t.node);
+                inj_shot.push_back(s);
+                inj_cptr.push_back((int)inj_crec.size());
             }
+            inj_crec.push_back(t.rec);
+            inj_cw.push_back(t.w);
         }
         p->shot_node_ptr[s + 1] = (int)inj_node.size();
     }
     inj_cptr.push_back((int)inj_crec.size());
     p->inj_nodes = (int)inj_node.size();
-    // two-step adjoint: for every shot, row and strip, the range of that
-    // shot's injection nodes in the row whose columns fall in the strip's
-    // window (its output columns and halo), packed (first << 9 | count)
-    std::vector<unsigned> inj_win;
-    std::vector<int> inj_col(inj_node.size());
+    // where each row's nodes begin (they lie in row order), and every node's
+    // column
+    std::vector<int> inj_rowptr((size_t)S * (g.Nz + 1)), inj_col(inj_node.size());
     for (size_t k = 0; k < inj_node.size(); ++k)
         inj_col[k] = (int)(inj_node[k] % g.Nx);
-    if (p->adj2) {
-        const Sweep &sa = p->sweep_a2;
-        const int W = strip_cols(sa.cols, 2);
-        const int halo = (6 + sa.cols - 1) / sa.cols * sa.cols;
-        inj_win.assign((size_t)p->Spad * (g.Nz + 2 * kZPad) * sa.nstrips, 0u);
-        bool fits = inj_node.size() < (1u << 23);
-        for (int s = 0; s < S && fits; ++s) {
-            int k = p->shot_node_ptr[s];
-            const int kend = p->shot_node_ptr[s + 1];
-            while (k < kend) {
-                const long long row = inj_node[k] / g.Nx;
-                int ke = k;
-                while (ke < kend && inj_node[ke] / g.Nx == row)
-                    ++ke;
-                for (int st = 0; st < sa.nstrips; ++st) {
-                    const int lo = st * W - halo, hi = lo + 64 * sa.cols;
-                    int a0 = k;
-                    while (a0 < ke && inj_col[a0] < lo)
-                        ++a0;
-                    int a1 = a0;
-                    while (a1 < ke && inj_col[a1] < hi)
-                        ++a1;
-                    if (a1 > a0) {
-                        if (a1 - a0 > 511) {
-                            fits = false;
-                            break;
-                        }
-                        inj_win[((size_t)s * (g.Nz + 2 * kZPad) + kZPad + row) * sa.nstrips + st] =
-                            ((unsigned)a0 << 9) | (unsigned)(a1 - a0);
-                    }
-                }
-                k = ke;
-            }
-        }
-        if (!fits) {   // more nodes than the packing holds: one-step adjoint
-            p->adj2 = false;
-            inj_win.clear();
+    for (int s = 0; s < S; ++s) {
+        int k = p->shot_node_ptr[s];
+        for (int i = 0; i <= g.Nz; ++i) {
+            while (k < p->shot_node_ptr[s + 1] && inj_node[k] < (long long)i * g.Nx)
+                ++k;
+            inj_rowptr[(size_t)s * (g.Nz + 1) + i] = k;
         }
     }
-    // two-step forward: when its intermediate level is only sampled, the
-    // kernel writes just the receiver nodes of each row.  For every shot,
-    // row and strip, the range of that shot's nodes in the row whose columns
-    // the strip owns (packed as above), and for every receiver the nodes of
-    // its four bilinear corners (-1 where the weight is zero, which has no
-    // node)
-    std::vector<unsigned> samp_win;
-    std::vector<int4> rec_node;
-    if (p->two_step) {
-        const Sweep &s2 = p->sweep2;
-        const int W = strip_cols(s2.cols, 2);
-        samp_win.assign((size_t)S * g.Nz * s2.nstrips, 0u);
-        bool fits = inj_node.size() < (1u << 23);
-        for (int s = 0; s < S && fits; ++s) {
-            int k = p->shot_node_ptr[s];
-            const int kend = p->shot_node_ptr[s + 1];
-            while (k < kend && fits) {
-                const long long row = inj_node[k] / g.Nx;
-                int ke = k;
-                while (ke < kend && inj_node[ke] / g.Nx == row)
-                    ++ke;
-                for (int a0 = k; a0 < ke;) {
-                    const int st = inj_col[a0] / W;
-                    int a1 = a0;
-                    while (a1 < ke && inj_col[a1] / W == st)
-                        ++a1;
-                    if (a1 - a0 > 511) {
-                        fits = false;
-                        break;
+    std::vector<unsigned> inj_rc;
+    if (p->tile.on) {
+        inj_rc.resize(inj_node.size());
+        for (size_t k = 0; k < inj_node.size(); ++k)
+            inj_rc[k] = ((unsigned)(inj_node[k] / g.Nx) << 16) | (unsigned)inj_col[k];
+    }
+    // Nodes listed by shot, strip and row, those of a strip being the ones
+    // whose columns lie in [strip W - reach, strip W - reach + width): for
+    // every row and strip the packed range (first << 9 | count; width <= 256)
+    // counted from the strip's first node, rows offset by `pad` in a table of
+    // `rows` rows a shot.  False if a strip holds more nodes than that packs.
+    auto list_nodes = [&](int nstrips, int W, int reach, int width, int shots, int rows, int pad,
+                          std::vector<unsigned> &win, std::vector<int> &ptr,
+                          std::vector<int> &node, std::vector<int> &col) {
+        win.assign((size_t)shots * rows * nstrips, 0u);
+        ptr.assign((size_t)shots * nstrips, 0);
+        std::vector<int> full;   // rows that hold nodes
+        for (int s = 0; s < S; ++s) {
+            const int *rp = &inj_rowptr[(size_t)s * (g.Nz + 1)];
+            full.clear();
+            for (int i = 0; i < g.Nz; ++i)
+                if (rp[i] != rp[i + 1])
+                    full.push_back(i);
+            for (int st = 0; st < nstrips; ++st) {
+                const int base = (int)node.size();
+                ptr[(size_t)s * nstrips + st] = base;
+                const int lo = st * W - reach;
+                for (int i : full) {
+                    const auto r0 = inj_col.begin() + rp[i], r1 = inj_col.begin() + rp[i + 1];
+                    if (*(r1 - 1) < lo || *r0 >= lo + width)
+                        continue;
+                    const auto c0 = std::lower_bound(r0, r1, lo);
+                    const auto c1 = std::lower_bound(c0, r1, lo + width);
+                    if (c0 == c1)
+                        continue;
+                    const size_t first = node.size() - (size_t)base;
+                    if (first >= (1u << 23) || node.size() > (1u << 30))
+                        return false;
+                    win[((size_t)s * rows + pad + i) * nstrips + st] =
+                        ((unsigned)first << 9) | (unsigned)(c1 - c0);
+                    for (auto c = c0; c != c1; ++c) {
+                        node.push_back((int)(c - inj_col.begin()));
+                        col.push_back(*c);
                     }
-                    samp_win[((size_t)s * g.Nz + row) * s2.nstrips + st] =
-                        ((unsigned)a0 << 9) | (unsigned)(a1 - a0);
-                    a0 = a1;
                 }
-                k = ke;
             }
         }
-        if (fits) {
+        return true;
+    };
+    // strip adjoint: the strip's window (its output columns and halo)
+    std::vector<unsigned> inj_win;
+    std::vector<int> al_node, al_col, al_ptr;
+    if (p->mode != FWI_EXEC_PLAIN && !p->tile.on) {
+        const Sweep &sa = p->adj2 ? p->sweep_a2 : p->sweep;
+        const int reach = p->adj2 ? 6 : 3;
+        const int halo = (reach + sa.cols - 1) / sa.cols * sa.cols;
+        if (list_nodes(sa.nstrips, strip_cols(sa.cols, p->adj2 ? 2 : 1), halo, 64 * sa.cols,
+                       p->Spad, g.Nz + 2 * kZPad, kZPad, inj_win, al_ptr, al_node, al_col)) {
+            p->adj_list = (int)al_node.size();
+        } else {   // one-step adjoint, R^T r added by launches of its own
+            p->adj2 = false;
+            inj_win.clear();
+            al_ptr.clear();
+            al_node.clear();
+            al_col.clear();
+        }
+        al_col.resize(al_col.size() + 64, -1);   // (runs of 64 are read)
+    }
+    // two-step forward, whose intermediate level, when only sampled, is kept at
+    // the receiver nodes: the columns the strip owns; and for every receiver
+    // the listed nodes of its four bilinear corners (-1 where the weight is
+    // zero, which has no node)
+    std::vector<unsigned> samp_win;
+    std::vector<int> sl_node, sl_col, sl_ptr;
+    std::vector<int4> rec_node;
+    if (p->two_step && !p->tile.on) {
+        const Sweep &s2 = p->sweep2;
+        const int W = strip_cols(s2.cols, 2);
+        p->samp_nodes =
+            list_nodes(s2.nstrips, W, 0, W, S, g.Nz, 0, samp_win, sl_ptr, sl_node, sl_col);
+        if (p->samp_nodes) {
+            p->samp_list = (int)sl_node.size();   // every node once
+            std::vector<int> at(inj_node.size());
+            for (size_t l = 0; l < sl_node.size(); ++l)
+                at[sl_node[l]] = (int)l;
             rec_node.resize((size_t)S * nr);
             for (int s = 0; s < S; ++s) {
                 const auto b0 = inj_node.begin() + p->shot_node_ptr[s];
@@ -1593,38 +1697,21 @@ fwi_status fwi_plan_create(const fwi_grid *grid, const fwi_acq *acq, const fwi_e
                     int q4[4];
                     for (int q = 0; q < 4; ++q) {
                         q4[q] = -1;
-                        if (ws[q] != 0.0f) {
-                            const auto it = std::lower_bound(b0, b1, cs[q]);
-                            q4[q] = (int)(it - inj_node.begin());
-                        }
+                        if (ws[q] != 0.0f)
+                            q4[q] = at[std::lower_bound(b0, b1, cs[q]) - inj_node.begin()];
                     }
                     rec_node[(size_t)s * nr + r] = make_int4(q4[0], q4[1], q4[2], q4[3]);
                 }
             }
         } else {
             samp_win.clear();
+            sl_ptr.clear();
+            sl_col.clear();
         }
-        p->samp_nodes = fits;
+        sl_col.resize(sl_col.size() + 64, -1);
     }
-
-    // tile adjoint: the nodes of a shot lie in row order; where each row's
-    // begin, and every node's row and column
-    std::vector<int> inj_rowptr;
-    std::vector<unsigned> inj_rc;
-    if (p->tile.on) {
-        inj_rowptr.resize((size_t)S * (g.Nz + 1));
-        inj_rc.resize(inj_node.size());
-        for (int s = 0; s < S; ++s) {
-            int k = p->shot_node_ptr[s];
-            for (int i = 0; i <= g.Nz; ++i) {
-                while (k < p->shot_node_ptr[s + 1] && inj_node[k] < (long long)i * g.Nx)
-                    ++k;
-                inj_rowptr[(size_t)s * (g.Nz + 1) + i] = k;
-            }
-        }
-        for (size_t k = 0; k < inj_node.size(); ++k)
-            inj_rc[k] = ((unsigned)(inj_node[k] / g.Nx) << 16) | (unsigned)inj_col[k];
-    }
+    if (!p->tile.on)
+        inj_rowptr.clear();
 
     if (hipGetDevice(&p->device) != hipSuccess) {
         delete p;
@@ -1654,7 +1741,11 @@ fwi_status fwi_plan_create(const fwi_grid *grid, const fwi_acq *acq, const fwi_e
     o.ir = take(sizeof(int) * inj_crec.size());
     o.iw = take(sizeof(float) * inj_cw.size());
     o.win = take(sizeof(unsigned) * inj_win.size());
-    o.col = take(sizeof(int) * inj_col.size());
+    o.aln = take(sizeof(int) * al_node.size());
+    o.alc = take(sizeof(int) * al_col.size());
+    o.alp = take(sizeof(int) * al_ptr.size());
+    o.slc = take(sizeof(int) * sl_col.size());
+    o.slp = take(sizeof(int) * sl_ptr.size());
     o.swin = take(sizeof(unsigned) * samp_win.size());
     o.rnode = take(sizeof(int4) * rec_node.size());
     o.rptr = take(sizeof(int) * inj_rowptr.size());
@@ -1681,7 +1772,11 @@ fwi_status fwi_plan_create(const fwi_grid *grid, const fwi_acq *acq, const fwi_e
     put(o.ir, inj_crec.data(), sizeof(int) * inj_crec.size());
     put(o.iw, inj_cw.data(), sizeof(float) * inj_cw.size());
     put(o.win, inj_win.data(), sizeof(unsigned) * inj_win.size());
-    put(o.col, inj_col.data(), sizeof(int) * inj_col.size());
+    put(o.aln, al_node.data(), sizeof(int) * al_node.size());
+    put(o.alc, al_col.data(), sizeof(int) * al_col.size());
+    put(o.alp, al_ptr.data(), sizeof(int) * al_ptr.size());
+    put(o.slc, sl_col.data(), sizeof(int) * sl_col.size());
+    put(o.slp, sl_ptr.data(), sizeof(int) * sl_ptr.size());
     put(o.swin, samp_win.data(), sizeof(unsigned) * samp_win.size());
     put(o.rnode, rec_node.data(), sizeof(int4) * rec_node.size());
     put(o.rptr, inj_rowptr.data(), sizeof(int) * inj_rowptr.size());
@@ -1727,7 +1822,7 @@ fwi_status fwi_plan_get_info(const fwi_plan *p, fwi_plan_info *info)
     info->adj_two_step = p->adj2 ? 1 : 0;
     info->adj_two_step_band_rows = p->sweep_a2.H;
     info->adj_two_step_lane_cols = p->sweep_a2.cols;
-    info->shot_groups = groups_of(p);
+    info->shot_groups = p->mode == FWI_EXEC_PLAIN ? 1 : (p->S + p->sweep.spg - 1) / p->sweep.spg;
     info->mode = p->mode;
     info->device = p->device;
     info->pml_cells = p->geo.Npml;

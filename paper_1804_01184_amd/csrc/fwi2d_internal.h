@@ -117,10 +117,12 @@ void launch_sample_hist(const Geo &g, const float *hist, long long slot_stride, 
 // shot0: shot index of lp.shot(0) (the table holds global shot indices).
 void launch_inject(const Geo &g, const Inj &inj, const float *resid, int nrec, int nt, int n,
                    Fld lp, int shot0, hipStream_t st);
-// Injection before a two-step adjoint launch (steps n, n-1): R^T r^n into
-// lp as launch_inject, and R^T r^{n-1} of node k of the table into next[k].
-void launch_inject_pair(const Geo &g, const Inj &inj, const float *resid, int nrec, int nt,
-                        int n, Fld lp, int shot0, float *next, hipStream_t st);
+// After a one-step adjoint launch without node tables: adds R^T r^{m-1} (injv)
+// to lp and its imaging term to the partial gradients of the shot groups (spg
+// shots each; one launch per shot of a group, so no two threads share a cell).
+// pm: p^m.
+void launch_inject_post(const Geo &g, const Inj &inj, const float *injv, int spg, Fld lp, Fld pm,
+                        const float *K, float *gpart, hipStream_t st);
 // wt (may be null): one weight per trace of nt samples.
 void launch_misfit(const float *d, const float *dobs, float *resid, long long n,
                    float *partials, int nblocks, float *J, hipStream_t st,
@@ -183,9 +185,9 @@ bool adj2_supported(int spg, int cols);
 // (steps = 2) forward kernels; the two-step kernels need twice the halo.
 int strip_cols(int cols, int steps = 1);
 Sweep sweep_of(const Geo &g, int S, int band_rows, int spg, int cols, int steps = 1);
-// Waves of the two-step adjoint (adjoint = true) or forward kernel with
-// (spg, cols) that the current device holds at once, 0 if unknown.
-int resident_waves2(bool adjoint, int spg, int cols);
+// Waves of the two-step forward kernel with (spg, cols) that the current device
+// holds at once, 0 if unknown.
+int resident_waves2(int spg, int cols);
 
 // Source tables of a plan for the batched kernels, kept in device memory
 // so that the kernels take one pointer to them.
@@ -214,40 +216,51 @@ struct FwdStep {
 };
 // Two forward steps n -> n+2: pmid receives p^{n+1} and its split.
 // Two forward steps n, n+1.  p^{n+1} goes to pmid (midw 0), or, when the
-// level is only sampled, just its receiver nodes go to `nodes` (midw 1:
-// nwin[(s Nz + i) nstrips + strip] packs (first << 9 | count) of the nodes
-// of shot s in row i whose columns the strip owns, ncol the grid column of
-// each node), or nothing is kept (midw 2).
+// level is only sampled, just its receiver nodes go to `nodes` (midw 1), or
+// nothing is kept (midw 2).  The nodes are listed by shot, strip (the one
+// owning the column) and row: nwin[(s Nz + i) nstrips + strip] packs
+// (first << 9 | count) of those of shot s in row i, first counted from
+// nptr[s nstrips + strip], ncol the grid column of each (64 readable entries
+// after the last).
 struct FwdStep2 {
     Recd vin, pin, vout, pout, pmid;
+    const float *zpad;     // z damping tables padded by kZPad zero rows (ztab_pad)
     const float *Q;
     float *nodes;
     const unsigned *nwin;
-    const int *ncol;
+    const int *nptr, *ncol;
     int midw;
     int n;
 };
-struct AdjStep {
-    Recd lin, lout, pn, pn1;
-    float *gpart;       // [groups][3][N]: gK, gbx, gbz
-    int n;
+// Receiver nodes for the strip adjoints, listed by shot, strip and row (a node
+// in the windows of several strips is listed for each).
+// win[(s (Nz + 2 kZPad) + kZPad + i) nstrips + strip] packs
+// (first << 9 | count) of those of shot s in row i within the strip's window
+// (halo included; 0: none), first counted from ptr[s nstrips + strip]; col:
+// each listed node's column.  The lists are followed by 64 readable entries.
+struct AdjNodes {
+    const unsigned *win;
+    const int *ptr;
+    const int *col;
 };
-// Two adjoint steps n, n-1 (in order): pm1 holds p^{n-1}, p^n and p^{n+1}
-// follow lvl and 2 lvl bytes after it (consecutive levels of the pressure
-// store).  The adjoint source of step n-1 is added between the steps at the
-// receiver nodes: injwin[(s Nz + i) nstrips + strip] packs
-// (first << 9 | count) of the nodes of shot s in row i within the strip's
-// window (halo included; 0: none), injcol the grid column of each node,
-// injacc R^T r^{n-1} at each node.
+// Adjoint step m: pn holds p^m; injv: R^T r^{m-1} at each listed node (nd.win
+// null: added by the caller, see launch_inject_post).
+struct AdjStep {
+    Recd lin, lout, pn;
+    AdjNodes nd;
+    const float *injv;
+    float *gpart;       // [groups][3][N]: gK, gbx, gbz
+};
+// Two adjoint steps m, m-1 (in order): pm1 holds p^{m-1}, p^m follows lvl
+// bytes after it (consecutive levels of the pressure store).  injA, injB:
+// R^T r^{m-1} and R^T r^{m-2} at each listed node (injB null: none).
 struct AdjStep2 {
     Recd lin, lout, pm1;
     unsigned lvl;
     const float *zpad;     // z damping tables padded by kZPad zero rows (ztab_pad)
     float *gpart;
-    const unsigned *injwin;
-    const int *injcol;
-    const float *injacc;
-    int n;
+    AdjNodes nd;
+    const float *injA, *injB;
 };
 
 // tabs: the 8 damping tables (x: alpha, beta, alpha_h, beta_h; then z) in
@@ -256,14 +269,14 @@ struct AdjStep2 {
 void launch_fused_fwd(const Geo &g, const float *tabs, const float *model,
                       const SweepTables *tab_dev, int S, const Sweep &sw, const FwdStep &a,
                       hipStream_t st, hipEvent_t e0 = nullptr, hipEvent_t e1 = nullptr);
-void launch_fused_adj(const Geo &g, const float *tabs, const float *model,
-                      const SweepTables *tab_dev, int S, const Sweep &sw, const AdjStep &a,
-                      hipStream_t st, hipEvent_t e0 = nullptr, hipEvent_t e1 = nullptr);
+void launch_fused_adj(const Geo &g, const float *tabs, const float *model, const Sweep &sw,
+                      const AdjStep &a, hipStream_t st, hipEvent_t e0 = nullptr,
+                      hipEvent_t e1 = nullptr);
 // sw: a decomposition made with steps = 2 and the shots per group of the
 // one-step adjoint (the two share the partial gradients of each group).
-void launch_fused_adj2(const Geo &g, const float *tabs, const float *model, int S,
-                       const Sweep &sw, const AdjStep2 &a, hipStream_t st,
-                       hipEvent_t e0 = nullptr, hipEvent_t e1 = nullptr);
+void launch_fused_adj2(const Geo &g, const float *tabs, const float *model, const Sweep &sw,
+                       const AdjStep2 &a, hipStream_t st, hipEvent_t e0 = nullptr,
+                       hipEvent_t e1 = nullptr);
 // sw: a decomposition made with steps = 2.
 void launch_fused_fwd2(const Geo &g, const float *tabs, const float *model,
                        const SweepTables *tab_dev, int S, const Sweep &sw, const FwdStep2 &a,
@@ -316,9 +329,10 @@ void launch_tile_fwd(const Geo &g, const float *tabs, const float *zpad, const f
 void launch_tile_adj(const Geo &g, const float *tabs, const float *zpad, const float *model,
                      const AdjTile &a, hipStream_t st, hipEvent_t e0 = nullptr,
                      hipEvent_t e1 = nullptr);
-// R^T r^{n1 - j} at every node for j < nsteps: out[j nnodes + k].
-void launch_inject_stage(const Inj &inj, const float *resid, int nrec, int nt, int n1, int nsteps,
-                         float *out, hipStream_t st);
+// R^T r^{n1 - j} at every listed node for j < nsteps: out[j nlist + l] at node
+// list[l] (list null: every node, nlist = nnodes).
+void launch_inject_stage(const Inj &inj, const int *list, int nlist, const float *resid, int nrec,
+                         int nt, int n1, int nsteps, float *out, hipStream_t st);
 
 // ------------------------------------------------------------------ born
 // Decomposition of the Born data and gradient launches.

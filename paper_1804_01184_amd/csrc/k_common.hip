@@ -280,39 +280,42 @@ __global__ void k_inject(Inj inj, const float *resid, int nrec, int nt, int n, F
     lp.shot(s - shot0)[inj.node[k]] += inj_sum(inj, resid, nrec, nt, n, k, s);
 }
 
-// Before a two-step adjoint launch (steps n and n-1): R^T r^n added to the
-// adjoint pressure as k_inject does, and R^T r^{n-1} per node kept in `next`
-// for the launch to add between its two steps.
-__global__ void k_inject_pair(Inj inj, const float *resid, int nrec, int nt, int n, Fld lp,
-                              int shot0, float *next)
+__global__ void k_inject_post(Inj inj, const float *injv, int spg, int member, Fld lp, Fld pm,
+                              const float *K, float *gpart, long long N)
 {
     int k = blockIdx.x * blockDim.x + threadIdx.x;
-    if (k >= inj.nnodes)
+    if (k >= inj.nnodes || inj.shot[k] % spg != member)
         return;
-    int s = inj.shot[k];
-    lp.shot(s - shot0)[inj.node[k]] += inj_sum(inj, resid, nrec, nt, n, k, s);
-    next[k] = inj_sum(inj, resid, nrec, nt, n - 1, k, s);
+    const int s = inj.shot[k];
+    const long long q = inj.node[k];
+    const float v = injv[k];
+    lp.shot(s)[q] += v;
+    gpart[(long long)(s / spg) * 3 * N + q] += pm.shot(s)[q] * v / K[q];
 }
 
-// R^T r of a run of steps, for the tile adjoint: out[j nnodes + k] = R^T
-// r^{n1 - j} at node k, j < nsteps.  A block covers 64 nodes by 64 steps: the
-// residuals are read along time, the sums written along the nodes through LDS.
-__global__ void __launch_bounds__(256) k_inject_stage(Inj inj, const float *resid, int nrec, int nt,
-                                                     int n1, int nsteps, float *out)
+// R^T r of a run of steps, for the batched adjoints: out[j nlist + l] = R^T
+// r^{n1 - j} at node list[l] (or l), j < nsteps.  A block covers 64 listed
+// nodes by 64 steps: the residuals are read along time, the sums written along
+// the list through LDS.
+__global__ void __launch_bounds__(256) k_inject_stage(Inj inj, const int *list, int nlist,
+                                                     const float *resid, int nrec, int nt, int n1,
+                                                     int nsteps, float *out)
 {
     __shared__ float tile[64][65];
     const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
     const int k0 = blockIdx.x * 64, j0 = blockIdx.y * 64;
     for (int q = wv; q < 64; q += 4) {
-        const int k = k0 + q, j = j0 + lane;
-        if (k < inj.nnodes && j < nsteps)
+        const int l = k0 + q, j = j0 + lane;
+        if (l < nlist && j < nsteps) {
+            const int k = list ? list[l] : l;
             tile[q][lane] = inj_sum(inj, resid, nrec, nt, n1 - j, k, inj.shot[k]);
+        }
     }
     __syncthreads();
     for (int q = wv; q < 64; q += 4) {
-        const int k = k0 + lane, j = j0 + q;
-        if (k < inj.nnodes && j < nsteps)
-            out[(long long)j * inj.nnodes + k] = tile[lane][q];
+        const int l = k0 + lane, j = j0 + q;
+        if (l < nlist && j < nsteps)
+            out[(long long)j * nlist + l] = tile[lane][q];
     }
 }
 
@@ -631,23 +634,23 @@ void launch_inject(const Geo &, const Inj &inj, const float *resid, int nrec, in
                        nrec, nt, n, lp, shot0);
 }
 
-void launch_inject_pair(const Geo &g, const Inj &inj, const float *resid, int nrec, int nt,
-                        int n, Fld lp, int shot0, float *next, hipStream_t st)
+void launch_inject_post(const Geo &g, const Inj &inj, const float *injv, int spg, Fld lp, Fld pm,
+                        const float *K, float *gpart, hipStream_t st)
 {
-    (void)g;
     if (inj.nnodes <= 0)
         return;
-    hipLaunchKernelGGL(k_inject_pair, dim3(blocks_for(inj.nnodes)), dim3(kBlock), 0, st, inj,
-                       resid, nrec, nt, n, lp, shot0, next);
+    for (int member = 0; member < spg; ++member)
+        hipLaunchKernelGGL(k_inject_post, dim3(blocks_for(inj.nnodes)), dim3(kBlock), 0, st, inj,
+                           injv, spg, member, lp, pm, K, gpart, g.N);
 }
 
-void launch_inject_stage(const Inj &inj, const float *resid, int nrec, int nt, int n1, int nsteps,
-                         float *out, hipStream_t st)
+void launch_inject_stage(const Inj &inj, const int *list, int nlist, const float *resid, int nrec,
+                         int nt, int n1, int nsteps, float *out, hipStream_t st)
 {
-    if (inj.nnodes <= 0 || nsteps <= 0)
+    if (nlist <= 0 || nsteps <= 0)
         return;
-    hipLaunchKernelGGL(k_inject_stage, dim3(blocks_for(inj.nnodes, 64), blocks_for(nsteps, 64)),
-                       dim3(256), 0, st, inj, resid, nrec, nt, n1, nsteps, out);
+    hipLaunchKernelGGL(k_inject_stage, dim3(blocks_for(nlist, 64), blocks_for(nsteps, 64)),
+                       dim3(256), 0, st, inj, list, nlist, resid, nrec, nt, n1, nsteps, out);
 }
 
 int misfit_blocks(long long n)

@@ -29,21 +29,18 @@
 // row i into one of two alternating register sets, so their latency overlaps
 // a row of work and no register copies (which would wait for them) are
 // needed.  The adjoint reads the values it needs only at the end of a row
-// (the stored forward pressure of step n+1, the splits, the partial
-// gradient) into a single set, issued at the start of the row before the
-// next row's loads.  Loads are unconditional: rows outside the grid or past
+// (the partial gradient) into a single set, issued at the start of the row
+// before the next row's loads.  Loads are unconditional: rows outside the grid or past
 // the band are read through an out-of-range lane offset, which returns zero
 // without touching memory, so the memory counters see the same sequence on
 // every row.
 //
-// Receiver sampling and the adjoint-source injection are separate small
-// launches, one thread per receiver or node (done inside the sweep, they
-// made the waves holding receivers walk their lists serially, a few memory
-// round trips per node, and those waves set the length of the launch).
-// Inside a two-step launch only per-row table lookups remain: k_adj2 adds
-// its second step's adjoint source, staged per node by the injection launch
-// before it, and k_fwd2 writes the receiver nodes of an intermediate level
-// that is only sampled, for a node sampling launch after it.
+// Receiver sampling is a separate small launch, and the receivers' sums of the
+// adjoint source (R^T r) are staged per node by one, 64 steps at a time.  The
+// kernels only add or write the nodes listed for their strip and row: k_adj
+// and k_adj2 add the staged sums to the new adjoint pressure, and k_fwd2 writes
+// the receiver nodes of an intermediate level that is only sampled, for a node
+// sampling launch after it.
 // Workgroups are numbered so that each XCD receives a contiguous range of
 // waves (neighbouring strips, the shot groups of a band and neighbouring
 // bands share its L2).
@@ -393,6 +390,79 @@ __global__ void __launch_bounds__(NTHR)
     }
 }
 
+// Per-row uniform values of 64 consecutive rows, one row a lane: the z damping
+// tables (zero outside the grid) and the packed receiver-node entries of the
+// wave's shots.  A row's values are read out with v_readlane: scalar loads
+// return out of order, so a wait for a table value would also wait for the
+// node entries prefetched with it, which miss the caches on every row.
+template <int NW>
+struct RowLanes {
+    int base;              // row of lane 0
+    float az, bz, ahz, bhz;
+    unsigned win[NW];
+    __device__ float at(float v, int r) const
+    {
+        return __builtin_bit_cast(
+            float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, v), r - base));
+    }
+    __device__ unsigned node(int k, int r) const
+    {
+        return (unsigned)__builtin_amdgcn_readlane((int)win[k], r - base);
+    }
+    // Rows [r, r + 64) (clamped to the tables' padding).  node_row(k): entry of
+    // row 0 of the wave's k-th shot and strip, row_stride entries a row.
+    template <typename F>
+    __device__ void load(const Geo &g, const float *zpad, int r, int lane, int lo, int hi, F node_row,
+                         int row_stride)
+    {
+        base = r;
+        const int ZP = g.Nz + 2 * kZPad;
+        const int i = imin(imax(r + lane, -kZPad), g.Nz + kZPad - 1);
+        const float *z = zpad + kZPad + i;
+        az = z[0];
+        bz = z[ZP];
+        ahz = z[2 * ZP];
+        bhz = z[3 * ZP];
+        const int n = imin(imax(r + lane, lo), hi);
+#pragma unroll
+        for (int k = 0; k < NW; ++k) {
+            const unsigned *q = node_row(k);
+            win[k] = q ? q[(long long)n * row_stride] : 0u;
+        }
+        // (used here, so that the wait for them stays in this branch of the row
+        // loop: at its end it would wait for the next row's loads on every row)
+        asm volatile("" ::"v"(az), "v"(bz), "v"(ahz), "v"(bhz));
+#pragma unroll
+        for (int k = 0; k < NW; ++k)
+            asm volatile("" ::"v"(win[k]));
+    }
+};
+
+// A run of 64 receiver nodes of one shot and strip, one a lane: their grid
+// columns and, in the adjoint, a value each.  A strip's nodes lie in row order,
+// so a wave marching down its band reads a run every 64 nodes; walking them
+// with scalar loads, one or two memory round trips a node, set the length of
+// the waves that hold receivers.
+struct NodeLanes {
+    int base = 0, end = 0;   // node indices [base, end) held
+    int col;
+    float val;
+    __device__ void load(const int *cols, const float *vals, int first, int lane)
+    {
+        base = first;
+        end = first + WAVE;
+        col = cols[first + lane];
+        val = vals ? vals[first + lane] : 0.f;
+        asm volatile("" ::"v"(col), "v"(val));   // (wait here, as RowLanes::load)
+    }
+    __device__ int col_at(int e) const { return __builtin_amdgcn_readlane(col, e - base); }
+    __device__ float val_at(int e) const
+    {
+        return __builtin_bit_cast(
+            float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, val), e - base));
+    }
+};
+
 // ------------------------------------------------------- forward, two steps
 //
 // Steps n -> n+1 -> n+2 in one pass: the wave computes step n+1 on rows
@@ -400,9 +470,9 @@ __global__ void __launch_bounds__(NTHR)
 // three columns beyond its own rows and columns, so strips carry a 6-column
 // halo and step-one rows run three ahead), keeps step n+1's velocities,
 // split and model in three-row delay lines and its pressure in a window,
-// and computes step n+2 three rows behind.  Only p^{n+1} (and its split) of
-// the intermediate level is written, to the `mid` record (the pressure
-// history the adjoint reads); the intermediate velocities never leave
+// and computes step n+2 three rows behind.  Only p^{n+1} of the intermediate
+// level is written, to the `mid` record (the pressure history the adjoint
+// reads, which needs no split); the intermediate velocities never leave
 // registers, so two steps cost one read and one write of the state.
 
 template <int SPG, int C>
@@ -415,23 +485,25 @@ __global__ void __launch_bounds__(NTHR)
         return;
     XTab<C> xt;
     xtab<C>(g, tabs, w, xt);
-    cfloat *zaz = ctab(tabs + 4 * g.Nx), *zbz = zaz + g.Nz;
-    cfloat *zahz = zbz + g.Nz, *zbhz = zahz + g.Nz;
     const unsigned FB = 4u * (unsigned)g.N;
     const rsrc_t rM = res(model, 3u * FB);
     const rsrc_t rPin = grp_res(a.pin, w.s0, SPG), rVin = grp_res(a.vin, w.s0, SPG);
     const rsrc_t rPmid = grp_res(a.pmid, w.s0, SPG);
     const rsrc_t rPout = grp_res(a.pout, w.s0, SPG), rVout = grp_res(a.vout, w.s0, SPG);
-    cuint *nwin = (cuint *)a.nwin;
-    cint *ncol = (cint *)a.ncol;
-    // z tables with zero outside the grid (step-one rows run past it)
-    auto zt = [&](cfloat *t, int r) -> float { return row_ok(g, r) ? t[r] : 0.f; };
     // row byte offset of row r plus `extra`, or 0 when row r is outside the
     // grid (its lane offset is then kOOB)
     auto rofs = [&](int r, unsigned extra) -> unsigned {
         return row_ok(g, r) ? rowb(g, r) + extra : 0u;
     };
     const int t0 = w.i0 - 3;
+    // z tables and, where the intermediate level is only sampled, its nodes
+    // (rows without nodes and padding shots hold 0)
+    cfloat *zaz = ctab(a.zpad) + kZPad, *zbz = zaz + g.Nz + 2 * kZPad;
+    cfloat *zahz = zbz + g.Nz + 2 * kZPad, *zbhz = zahz + g.Nz + 2 * kZPad;
+    int nbase[SPG];   // first node of the wave's strip
+#pragma unroll
+    for (int k = 0; k < SPG; ++k)
+        nbase[k] = a.midw == 1 && w.s0 + k < S ? ((cint *)a.nptr)[(w.s0 + k) * sw.nstrips + w.strip] : 0;
 
     float P1[SPG][4][C];    // p^n rows t .. t+3
     float VZ1[SPG][3][C];   // vz^{n+1/2} rows t-2 .. t
@@ -482,7 +554,7 @@ __global__ void __launch_bounds__(NTHR)
             float bz[C], vz[C];
             vld<C>(rM, vo, rofs(r, 2u * FB), bz);
             vld<C>(rVin, vo, rofs(r, ovz), vz);
-            const float ahz = zt(zahz, r), bhz = zt(zbhz, r);
+            const float ahz = zahz[r], bhz = zbhz[r];
 #pragma unroll
             for (int c = 0; c < C; ++c)
                 VZ1[k][q][c] = ahz * vz[c] -
@@ -536,18 +608,15 @@ __global__ void __launch_bounds__(NTHR)
     auto row = [&](int t, FRow<SPG, C> &b) {
         const bool okt = row_ok(g, t);
         const bool rp1 = t < g.npml || t >= g.Nz - g.npml;   // row t in the layer
-        const float ahz1 = zt(zahz, t + 1), bhz1 = zt(zbhz, t + 1);
-        const float az1 = zt(zaz, t), btz1 = zt(zbz, t);
-        const ZRow z1 = zrow(g, okt ? t : 0);
-        unsigned zw1[C];
-        zoffs_w<C>(w, z1, zw1);
+        const float ahz1 = zahz[t + 1], bhz1 = zbhz[t + 1];
+        const float az1 = zaz[t], btz1 = zbz[t];
         const bool mid_on = t >= w.i0 && t < w.i1;   // this wave owns p^{n+1} row t
         const int r = t - 3;                          // step-two row
         const bool two = t >= w.i0;                   // step two runs (r >= i0 - 3)
         const bool full = r >= w.i0;                  // step two on an owned row
         const bool rn = row_ok(g, r + 1);
-        const float ahz2 = zt(zahz, r + 1), bhz2 = zt(zbhz, r + 1);
-        const float az2 = zt(zaz, r), btz2 = zt(zbz, r);
+        const float ahz2 = zahz[r + 1], bhz2 = zbhz[r + 1];
+        const float az2 = zaz[r], btz2 = zbz[r];
         const ZRow z2 = zrow(g, full ? r : 0);
         unsigned zw2[C];
         zoffs_w<C>(w, z2, zw2);
@@ -588,23 +657,17 @@ __global__ void __launch_bounds__(NTHR)
             // horizontal differences
             mask_cols<C>(w, pn);
             if (a.midw == 0) {
-                const unsigned km = skoff(a.pmid, k);
-                vst_row<C>(rPmid, w, mid_on, rb1 + km, pn);
-#pragma unroll
-                for (int c = 0; c < C; ++c)
-                    bst(rPmid, mid_on ? zw1[c] : kOOB, z1.base + FB + km, pzn[c]);
-            } else if (a.midw == 1 && mid_on && w.s0 + k < S) {
+                vst_row<C>(rPmid, w, mid_on, rb1 + skoff(a.pmid, k), pn);
+            } else if (a.midw == 1 && mid_on) {
                 // only the receiver nodes of the row that this strip owns
-                const unsigned ie = nwin[((unsigned)(w.s0 + k) * (unsigned)g.Nz + (unsigned)t) *
-                                             (unsigned)sw.nstrips +
-                                         (unsigned)w.strip];
-                const unsigned first = ie >> 9, cnt = ie & 511u;
-                for (unsigned e = 0; e < cnt; ++e) {
-                    const int j = ncol[first + e];
+                const unsigned ie = w.s0 + k < S ? ((cuint *)a.nwin)[((size_t)(w.s0 + k) * (size_t)g.Nz + (size_t)t) * (size_t)sw.nstrips + (size_t)w.strip] : 0u;
+                const int first = nbase[k] + (int)(ie >> 9), last = first + (int)(ie & 511u);
+                for (int e = first; e < last; ++e) {
+                    const int j = ((cint *)a.ncol)[e];
 #pragma unroll
                     for (int c = 0; c < C; ++c)
                         if (w.j0 + c == j)
-                            a.nodes[first + e] = pn[c];
+                            a.nodes[e] = pn[c];
                 }
             }
             // ---- step two at row r = t-3 (p^{n+1} rows r .. r+3 = P2, pn)
@@ -710,28 +773,38 @@ __global__ void __launch_bounds__(NTHR)
 
 // ---------------------------------------------------------------- adjoint
 //
-// State on entry: nu = adjoint after step n+1 with R^T r^n already added to
-// the pressure components (mu).  Main pressure field = mu_px; split field =
-// mu_pz in the absorbing layer (elsewhere mu_pz = mu_px).
-//   gK  += [mu_px (px^{n+1} - ax px^n) + mu_pz (pz^{n+1} - az pz^n)] / K
+// Step m (descending from nt) on entry: mu, lv = adjoint after step m+1 with
+// R^T r^m already added to the pressure components (all zero at m = nt).  Main
+// pressure field = mu_px; split field = mu_pz in the absorbing layer
+// (elsewhere mu_pz = mu_px).
 //   lv_mid = nu_v + D+(beta K mu_p)                       (T2 transposed)
-//   gbx += lvx_mid * (-bhx Dx+ p^n),  gbz likewise
-//   mu_p' = alpha mu_p + D-(beta_h b lv_mid);  lv' = alpha_h lv_mid   (T1^T)
-// (mu_p' receives R^T r^{n-1} from the injection launch before the next,
-// earlier step).  Outside the layer the split forms reduce to the unsplit
-// ones (alpha = 1, pz = 0).
+//   gbx += lvx_mid * (-bhx Dx+ p^m),  gbz likewise
+//   t = D-(beta_h b lv_mid);  mu_p' = alpha mu_p + t + R^T r^{m-1};
+//   lv' = alpha_h lv_mid                                  (T1^T)
+//   gK  += p^m (t + R^T r^{m-1}) / K
+// The bulk-modulus sensitivity of the discrete scheme is the sum over steps of
+// mu_x (px^{m+1} - alpha_x px^m) + mu_z (pz^{m+1} - alpha_z pz^m).  Collecting
+// the terms of each level (summation by parts in time; the field is zero before
+// the first step and the adjoint after the last), px^m meets mu_x' - alpha_x
+// mu_x and pz^m meets mu_z' - alpha_z mu_z, which are the same t + R^T r^{m-1}.
+// So a step needs the pressure of one level and no split.  At smooth-1001 (64
+// shots of 1081 x 1081) that took two of five pressure reads and four of six
+// split reads per shot and row out of the two-step kernel.
+// Outside the layer the split forms reduce to the unsplit ones (alpha = 1,
+// pz = 0).
 
 // One shot's part of an adjoint step at output row i (the update above).
 // Ring slots S0 .. S3 of MU, MZ, PN hold rows i .. i+3 of mu_px, mu_pz and
-// p^n, bK rows i .. i+3 of beta_z K, and WZ rows i-2 .. i+1 of
-// beta_h bz lvz_mid (slot S3 receives row i+1 here).  Adds the shot's
-// bulk-modulus numerator (at row i) and buoyancy sensitivities (gbx at row
-// i, gbz at row i+1) to numK, accX, accZ, and returns the new adjoint state
-// of row i (lvz of row i+1).  Both adjoint kernels call it, so one step
-// rounds the same way in either.
+// p^m, bK rows i .. i+3 of beta_z K, and WZ rows i-2 .. i+1 of
+// beta_h bz lvz_mid (slot S3 receives row i+1 here).  Adds the shot's buoyancy
+// sensitivities (gbx at row i, gbz at row i+1) to accX, accZ, and returns t of
+// row i and the new adjoint state of row i without R^T r^{m-1} (lvz of row
+// i+1).  Both adjoint kernels call it, so one step rounds the same way in
+// either.
 template <int C>
 struct AdjOut {
     float opx[C], opz[C], ovx[C], ovz[C];   // mu_px, mu_pz, lvx at row i; lvz at row i+1
+    float t[C];
 };
 
 template <int C, int S0, int S1, int S2, int S3>
@@ -740,11 +813,10 @@ __device__ inline void adj_shot(const Geo &g, const XTab<C> &xt, const WaveGeo<C
                                 const float (&K0)[C], const float (&MU)[4][C],
                                 const float (&MZ)[4][C], const float (&PN)[4][C],
                                 float (&WZ)[4][C], const float (&lvz1)[C], const float (&lvx)[C],
-                                const float (&bx)[C], const float (&bz1)[C], const float (&p1)[C],
-                                const float (&z0)[C], const float (&z1)[C], float (&numK)[C],
-                                float (&accX)[C], float (&accZ)[C], AdjOut<C> &o)
+                                const float (&bx)[C], const float (&bz1)[C], float (&accX)[C],
+                                float (&accZ)[C], AdjOut<C> &o)
 {
-    float lvzm[C], qx[C], dqx[C], dpx[C], lvxm[C], wx[C], dwx[C], tsum[C];
+    float lvzm[C], qx[C], dqx[C], dpx[C], lvxm[C], wx[C], dwx[C];
 #pragma unroll
     for (int c = 0; c < C; ++c) {
         // lvz_mid at row (i+1): D+z of beta_z K mu_pz
@@ -769,16 +841,36 @@ __device__ inline void adj_shot(const Geo &g, const XTab<C> &xt, const WaveGeo<C
 #pragma unroll
     for (int c = 0; c < C; ++c) {
         const float dwz = kC1 * (WZ[S2][c] - WZ[S1][c]) + kC2 * (WZ[S3][c] - WZ[S0][c]);
-        tsum[c] = dwx[c] * g.rdx + dwz * g.rdz;
+        o.t[c] = dwx[c] * g.rdx + dwz * g.rdz;
     }
 #pragma unroll
     for (int c = 0; c < C; ++c) {
-        const float mux = MU[S0][c], muz = MZ[S0][c], p0 = PN[S0][c];
-        numK[c] += mux * ((p1[c] - z1[c]) - xt.ax[c] * (p0 - z0[c])) + muz * (z1[c] - az * z0[c]);
-        o.opx[c] = xt.ax[c] * mux + tsum[c];
-        o.opz[c] = az * muz + tsum[c];
+        o.opx[c] = xt.ax[c] * MU[S0][c] + o.t[c];
+        o.opz[c] = az * MZ[S0][c] + o.t[c];
         o.ovx[c] = xt.ahx[c] * lvxm[c];
         o.ovz[c] = ahz1 * lvzm[c];
+    }
+}
+
+// R^T r of a step at the receiver nodes of one row that lie in the wave's
+// window (ie: the packed range of AdjNodes, counted from node nbase), added to
+// the row's new adjoint pressure and to t.
+template <int C>
+__device__ inline void add_nodes(const AdjNodes &nd, const float *val, NodeLanes &nl, int nbase,
+                                 unsigned ie, int lane, int j0, float (&mu)[C], float (&t)[C])
+{
+    const int first = nbase + (int)(ie >> 9), last = first + (int)(ie & 511u);
+    for (int e = first; e < last; ++e) {
+        if (e < nl.base || e >= nl.end)
+            nl.load(nd.col, val, e, lane);
+        const int j = nl.col_at(e);
+        const float v = nl.val_at(e);
+#pragma unroll
+        for (int c = 0; c < C; ++c)
+            if (j0 + c == j) {
+                mu[c] += v;
+                t[c] += v;
+            }
     }
 }
 
@@ -787,17 +879,16 @@ struct ARow {   // loads needed early in the row (double buffered)
     float K3[C], bx[C], bz1[C];                 // K at r+3, bx at r, bz at r+1
     float mu3[SPG][C], mz3[SPG][C], pn3[SPG][C];  // mu_px, split mu_pz, p^n at r+3
     float lvz1[SPG][C], lvx[SPG][C];            // lvz at r+1, lvx at r
+    unsigned inj[SPG];                          // receiver nodes of row r (packed)
 };
-template <int SPG, int C>
+template <int C>
 struct ALate {  // loads needed at the end of the row (single set)
     float gK[C], gX[C], gZ1[C];                 // partials at r (gbz at r+1)
-    float pn1[SPG][C], z0[SPG][C], z1[SPG][C];  // p^{n+1}, splits of p^n and p^{n+1} at r
 };
 
 template <int SPG, int C>
 __global__ void __launch_bounds__(NTHR)
-    k_adj(Geo g, const float *__restrict__ tabs, const float *model, const SweepTables *T, int S,
-          Sweep sw, AdjStep a)
+    k_adj(Geo g, const float *__restrict__ tabs, const float *model, Sweep sw, AdjStep a)
 {
     WaveGeo<C> w;
     if (!wave_geo<C>(g, sw, w))
@@ -812,7 +903,14 @@ __global__ void __launch_bounds__(NTHR)
     const rsrc_t rM = res(model, 3u * FB);                                  // K, bx, bz
     const rsrc_t rG = res(a.gpart + (long long)w.grp * 3 * g.N, 3u * FB);  // gK, gbx, gbz
     const rsrc_t rLin = grp_res(a.lin, w.s0, SPG), rLout = grp_res(a.lout, w.s0, SPG);
-    const rsrc_t rPn = grp_res(a.pn, w.s0, SPG), rPn1 = grp_res(a.pn1, w.s0, SPG);
+    const rsrc_t rPn = grp_res(a.pn, w.s0, SPG);
+    cuint *injwin = (cuint *)a.nd.win;
+    const int ZP = g.Nz + 2 * kZPad;
+    NodeLanes nl[SPG];
+    int nbase[SPG];   // first node of the wave's strip
+#pragma unroll
+    for (int k = 0; k < SPG; ++k)
+        nbase[k] = injwin ? ((cint *)a.nd.ptr)[(w.s0 + k) * sw.nstrips + w.strip] : 0;
     auto rowpml = [&](int r) { return r < g.npml || r >= g.Nz - g.npml; };
     auto btz_at = [&](int r) -> float { return row_ok(g, r) ? zbz[r] : 0.f; };
     // mu_pz of shot k at row r (zero outside the grid)
@@ -974,15 +1072,16 @@ __global__ void __launch_bounds__(NTHR)
             vld<C>(rPn, o.o3, rb + 3u * rowN + kn, b.pn3[k]);
             vld<C>(rLin, o.o1, rb + rowN + FB + kl, b.lvz1[k]);
             vld<C>(rLin, o.o0, rb + kl, b.lvx[k]);
+            // (rows and padding shots without nodes hold 0)
+            b.inj[k] = injwin ? injwin[((size_t)(w.s0 + k) * (size_t)ZP + (size_t)(r + kZPad)) *
+                                           (size_t)sw.nstrips + (size_t)w.strip]
+                              : 0u;
         }
     };
     // end-of-row values of row i (issued before the next row's loads)
-    auto load_late = [&](int i, ALate<SPG, C> &t) {
+    auto load_late = [&](int i, ALate<C> &t) {
         const unsigned rb = rowb(g, i);
         const bool more = i + 1 < w.i1;
-        const ZRow z = zrow(g, i);
-        unsigned oz[C];
-        zoffs<C>(w, z, true, oz);
         // partial gradient: this wave's output columns only (the lane
         // holding the last column reads its elements one by one)
         vld<C>(rG, w.vcolw, rb, t.gK);
@@ -997,19 +1096,9 @@ __global__ void __launch_bounds__(NTHR)
             t.gX[c] = tl ? a1 : t.gX[c];
             t.gZ1[c] = tl ? a2 : t.gZ1[c];
         }
-#pragma unroll
-        for (int k = 0; k < SPG; ++k) {
-            const unsigned kn = skoff(a.pn, k), kn1 = skoff(a.pn1, k);
-            vld<C>(rPn1, w.vcol, rb + kn1, t.pn1[k]);
-#pragma unroll
-            for (int c = 0; c < C; ++c) {
-                t.z0[k][c] = bld(rPn, oz[c], z.base + FB + kn);
-                t.z1[k][c] = bld(rPn1, oz[c], z.base + FB + kn1);
-            }
-        }
     };
 
-    auto row = [&](auto phase, int i, ARow<SPG, C> &b, const ALate<SPG, C> &t) {
+    auto row = [&](auto phase, int i, ARow<SPG, C> &b, const ALate<C> &t) {
         constexpr int R = decltype(phase)::value;
         constexpr int S0 = R & 3, S1 = (1 + R) & 3, S2 = (2 + R) & 3, S3 = (3 + R) & 3;
         const unsigned rb = rowb(g, i);
@@ -1043,8 +1132,13 @@ __global__ void __launch_bounds__(NTHR)
             }
             AdjOut<C> o;
             adj_shot<C, S0, S1, S2, S3>(g, xt, w, rn, ahz1, bhz1, az, bK, KW[S0], MU[k], MZ[k],
-                                        PN[k], WZ[k], b.lvz1[k], b.lvx[k], b.bx, b.bz1,
-                                        t.pn1[k], t.z0[k], t.z1[k], numK, accX, accZ, o);
+                                        PN[k], WZ[k], b.lvz1[k], b.lvx[k], b.bx, b.bz1, accX,
+                                        accZ, o);
+            if (b.inj[k] != 0u)
+                add_nodes<C>(a.nd, a.injv, nl[k], nbase[k], b.inj[k], w.lane, w.j0, o.opx, o.t);
+#pragma unroll
+            for (int c = 0; c < C; ++c)
+                numK[c] += PN[k][S0][c] * o.t[c];
             const unsigned ko = skoff(a.lout, k);
             vst_row<C>(rLout, w, true, rb + 2u * FB + ko, o.opx);
 #pragma unroll
@@ -1068,7 +1162,7 @@ __global__ void __launch_bounds__(NTHR)
     };
 
     ARow<SPG, C> A, B;
-    ALate<SPG, C> L;
+    ALate<C> L;
     using P0 = std::integral_constant<int, 0>;
     using P1 = std::integral_constant<int, 1>;
     using P2 = std::integral_constant<int, 2>;
@@ -1100,62 +1194,69 @@ __global__ void __launch_bounds__(NTHR)
 
 // ------------------------------------------------------- adjoint, two steps
 //
-// Adjoint steps n and n-1 in one pass, the reverse counterpart of k_fwd2.
-// Step A (adjoint step n) runs on rows [i0-3, i1+3) of the band with a
-// 6-column halo; step B (adjoint step n-1) follows three rows behind, on
+// Adjoint steps m and m-1 in one pass, the reverse counterpart of k_fwd2.
+// Step A (adjoint step m) runs on rows [i0-3, i1+3) of the band with a
+// 6-column halo; step B (adjoint step m-1) follows three rows behind, on
 // rows [i0-3, i1) (its first three rows only fill its windows, their
 // results are dropped).  Step A's new adjoint state never leaves the chip:
 // its pressure rows feed step B's windows, and its velocities, the model
 // rows and p^n reach step B through four-slot rings read three rows later.
-// Between the two steps the adjoint source of step n-1, summed per receiver
-// node by the injection launch before this one, is added to step A's new
-// pressure at the nodes in the wave's window, the value the separate
-// injection launch adds between two one-step launches.  Step A's
-// sensitivities on the wave's own rows wait three rows and are added to the
-// group's partial gradient before step B's, each with the one-step kernel's
-// expression, so the pair rounds exactly as two one-step launches.
+// Each step adds R^T r of the level below it, staged per receiver node by an
+// earlier launch, to its new pressure at the nodes in the wave's window.
+// Step A's sensitivities on the wave's own rows wait three rows and are added
+// to the group's partial gradient before step B's, each with the one-step
+// kernel's expression, so the pair rounds exactly as two one-step launches.
+//
+// What bounds it is the memory path of each CU (L1 misses in flight against
+// their latency, about 4.3 TB/s moved), so the bytes and requests count: one
+// pressure level a step without its split, the receivers' sums staged 64 steps
+// at a time instead of a launch a pair, and four shots a wave, which read the
+// model and read and write the partial gradient once.  Four shots fit the 256
+// registers of two waves a SIMD (three with two shots) because the values that
+// wait three rows sit in LDS.  us per launch on one and the same buffer, before
+// and after: 958 and 898 (64 shots of 1081 x 1081, 4 shots a wave, 91 rows),
+// 1865 and 1537 (32 of 2081 x 2081; 4, 49), 172 and 155 (40 of 481 x 481; 2,
+// 49); 18 + 10 f + 18 / SPG bytes a cell-step became 16 + 4 f + 18 / SPG, f the
+// layer's share of the cells.
 
 template <int SPG, int C>
 struct A2Row {   // loads of iteration t (double buffered)
     float K3[C], bx[C], bz1[C];                   // K at t+3, bx at t, bz at t+1
-    float mu3[SPG][C], mz3[SPG][C], pn3[SPG][C];  // mu_px, mu_pz, p^n at t+3
+    float mu3[SPG][C], mz3[SPG][C], pn3[SPG][C];  // mu_px, mu_pz, p^m at t+3
     float lvz1[SPG][C], lvx[SPG][C];              // lvz at t+1, lvx at t
-    float pm[SPG][C];                             // p^{n-1} at t
-    unsigned inj[SPG];                            // injection nodes of row t (packed)
-};
-template <int SPG, int C>
-struct A2Late {  // loads needed at the end of iteration t (single set)
-    float gK[C], gX[C], gZ1[C];                   // partials at r = t-3 (gbz at r+1)
-    float pn1[SPG][C], z0[SPG][C], z1[SPG][C];    // p^{n+1} at t; splits of p^n, p^{n+1} at t
-    float zm[SPG][C], zn[SPG][C];                 // splits of p^{n-1}, p^n at r
+    float pm[SPG][C];                             // p^{m-1} at t
 };
 
 template <int SPG, int C>
-__global__ void __launch_bounds__(NTHR)
-    k_adj2(Geo g, const float *__restrict__ tabs, const float *model, int S, Sweep sw, AdjStep2 a)
+__global__ void __launch_bounds__(NTHR) __attribute__((amdgpu_waves_per_eu(C > 1 ? 1 : SPG == 1 ? 4 : SPG == 2 ? 3 : 2)))
+    k_adj2(Geo g, const float *__restrict__ tabs, const float *model, Sweep sw, AdjStep2 a)
 {
     WaveGeo<C> w;
     if (!wave_geo<C, 2 * HALO>(g, sw, w))
         return;
     XTab<C> xt;
     xtab<C>(g, tabs, w, xt);
-    // z tables with kZPad zero rows on each side (rows outside the grid
-    // read zero without a branch)
-    const int ZP = g.Nz + 2 * kZPad;
-    cfloat *zaz = ctab(a.zpad) + kZPad, *zbz = zaz + ZP;
-    cfloat *zahz = zbz + ZP, *zbhz = zahz + ZP;
-    cuint *injwin = (cuint *)a.injwin;
-    cint *injcol = (cint *)a.injcol;
-    cfloat *injacc = ctab(a.injacc);
+    // z tables and receiver nodes of 64 rows (rows and padding shots without
+    // nodes hold 0)
+    RowLanes<SPG> rl;
+    auto node_row = [&](int k) -> const unsigned * {
+        return a.nd.win + ((size_t)(w.s0 + k) * (size_t)(g.Nz + 2 * kZPad) + kZPad) *
+                              (size_t)sw.nstrips + w.strip;
+    };
+    rl.load(g, a.zpad, w.i0 - 6, w.lane, -kZPad, g.Nz + kZPad - 1, node_row, sw.nstrips);
+    NodeLanes nlA[SPG], nlB[SPG];
+    int nbase[SPG];   // first node of the wave's strip
+#pragma unroll
+    for (int k = 0; k < SPG; ++k)
+        nbase[k] = ((cint *)a.nd.ptr)[(w.s0 + k) * sw.nstrips + w.strip];
     const unsigned FB = 4u * (unsigned)g.N;
     const rsrc_t rM = res(model, 3u * FB);                                  // K, bx, bz
     const rsrc_t rG = res(a.gpart + (long long)w.grp * 3 * g.N, 3u * FB);  // gK, gbx, gbz
     const rsrc_t rLin = grp_res(a.lin, w.s0, SPG), rLout = grp_res(a.lout, w.s0, SPG);
-    // the three pressure levels of the group: p^{n-1} at 0, p^n at lvl,
-    // p^{n+1} at 2 lvl bytes
+    // the two pressure levels of the group: p^{m-1} at 0, p^m at lvl bytes
     const rsrc_t rP = res((const float *)((const char *)a.pm1.base + (size_t)w.s0 * a.pm1.sbytes),
-                          2u * a.lvl + (unsigned)(SPG - 1) * a.pm1.sbytes + a.pm1.bytes);
-    const unsigned LN = a.lvl, LN1 = 2u * a.lvl;
+                          a.lvl + (unsigned)(SPG - 1) * a.pm1.sbytes + a.pm1.bytes);
+    const unsigned LN = a.lvl;
     auto rowpml = [&](int r) { return r < g.npml || r >= g.Nz - g.npml; };
     // byte offset of row r plus `extra`, 0 for rows outside the grid (whose
     // lane offsets are then kOOB)
@@ -1182,6 +1283,22 @@ __global__ void __launch_bounds__(NTHR)
 
     const int tA0 = w.i0 - 3, tend = w.i1 + 3;   // step-A rows [tA0, tend)
 
+    // Delay rings, in LDS (each lane its own words): slot R holds the values of
+    // iteration t, slot R + 1 those of iteration t - 3.  Of each shot A's lvx
+    // (row t) and lvz (row t+1); bx (t) and bz (t+1); A's gK numerator, gbx (t)
+    // and gbz (t+1).
+    constexpr int RX = 0, RZ = SPG, RBX = 2 * SPG, RBZ = RBX + 1, RNK = RBX + 2, RAX = RBX + 3,
+                  RAZ = RBX + 4, RN = RBX + 5;
+    __shared__ float ring[NTHR / WAVE][4][RN][C][WAVE];
+    auto &D = ring[threadIdx.x / WAVE];
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+#pragma unroll
+        for (int n = 0; n < RN; ++n)
+#pragma unroll
+            for (int c = 0; c < C; ++c)
+                D[q][n][c][w.lane] = 0.f;
+
     // Windows (rings of 4 slots relabelled by the phase R = (t - tA0) mod 4,
     // as in k_adj): step A's rows t .. t+3 (WZA: t-2 .. t+1), step B's rows
     // r .. r+3 (WZB: r-2 .. r+1) with r = t-3.  Delay rings: slot R holds
@@ -1189,18 +1306,14 @@ __global__ void __launch_bounds__(NTHR)
     float KA[4][C], KB[4][C];
     float MUA[SPG][4][C], MZA[SPG][4][C], PNA[SPG][4][C], WZA[SPG][4][C];
     float MUB[SPG][4][C], MZB[SPG][4][C], PMB[SPG][4][C], WZB[SPG][4][C];
-    float DLX[SPG][4][C], DLZ[SPG][4][C], DPN[SPG][4][C];   // A's lvx (row t), lvz (t+1), p^n (t)
-    float DBX[4][C], DBZ[4][C];                             // bx (row t), bz (t+1)
-    float DNK[4][C], DAX[4][C], DAZ[4][C];                  // A's gK numerator, gbx (t), gbz (t+1)
 #pragma unroll
     for (int q = 0; q < 4; ++q)
 #pragma unroll
         for (int c = 0; c < C; ++c) {
-            KB[q][c] = DBX[q][c] = DBZ[q][c] = DNK[q][c] = DAX[q][c] = DAZ[q][c] = 0.f;
+            KB[q][c] = 0.f;
 #pragma unroll
             for (int k = 0; k < SPG; ++k)
-                MUB[k][q][c] = MZB[k][q][c] = PMB[k][q][c] = WZB[k][q][c] = DLX[k][q][c] =
-                    DLZ[k][q][c] = DPN[k][q][c] = 0.f;
+                MUB[k][q][c] = MZB[k][q][c] = PMB[k][q][c] = WZB[k][q][c] = 0.f;
         }
 
     // step A's windows at its first row tA0 (k_adj's start of a band)
@@ -1210,14 +1323,14 @@ __global__ void __launch_bounds__(NTHR)
         for (int q = 0; q < 6; ++q) {
             const int r = tA0 - 3 + q;
             vld<C>(rM, vo(row_ok(g, r)), rofs(r, 0u), Kr[q]);
-            btzr[q] = zbz[r];
+            btzr[q] = rl.at(rl.bz, r);
         }
 #pragma unroll
         for (int q = 0; q < 3; ++q) {
             const int r = tA0 - 2 + q;
             float bz[C];
             vld<C>(rM, vo(row_ok(g, r)), rofs(r, 2u * FB), bz);
-            const float bhz = zbhz[r];
+            const float bhz = rl.at(rl.bhz, r);
 #pragma unroll
             for (int c = 0; c < C; ++c)
                 wzr[q][c] = bhz * bz[c];
@@ -1304,14 +1417,10 @@ __global__ void __launch_bounds__(NTHR)
             vld<C>(rLin, vo(ok1), rofs(t + 1, FB + kl), b.lvz1[k]);
             vld<C>(rLin, vo(ok0), rofs(t, kl), b.lvx[k]);
             vld<C>(rP, vo(ok0), rofs(t, kp), b.pm[k]);
-            const int s = w.s0 + k;
-            // (rows and padding shots without nodes hold 0)
-            b.inj[k] = injwin[((unsigned)s * (unsigned)ZP + (unsigned)(t + kZPad)) *
-                                  (unsigned)sw.nstrips + (unsigned)w.strip];
         }
     };
     // values needed late in iteration t (issued before the next row's loads)
-    auto load_late = [&](int t, A2Late<SPG, C> &L) {
+    auto load_late = [&](int t, ALate<C> &L) {
         const int r = t - 3;
         const bool own = r >= w.i0 && r < w.i1, ownz = r + 1 >= w.i0 && r + 1 < w.i1;
         // partial gradient of step B's row: this wave's output columns only
@@ -1331,33 +1440,19 @@ __global__ void __launch_bounds__(NTHR)
             L.gX[c] = tl ? a1 : L.gX[c];
             L.gZ1[c] = tl ? a2 : L.gZ1[c];
         }
-        const bool okt = row_ok(g, t), okr = row_ok(g, r);
-        const ZRow zt_ = zrow(g, okt ? t : 0), zr = zrow(g, okr ? r : 0);
-        unsigned oz[C], ozr[C];
-        zoffs<C>(w, zt_, okt, oz);
-        zoffs<C>(w, zr, okr, ozr);
-#pragma unroll
-        for (int k = 0; k < SPG; ++k) {
-            const unsigned kp = skoff(a.pm1, k);
-            vld<C>(rP, vo(okt), rofs(t, LN1 + kp), L.pn1[k]);
-#pragma unroll
-            for (int c = 0; c < C; ++c) {
-                L.z0[k][c] = bld(rP, oz[c], zt_.base + FB + LN + kp);
-                L.z1[k][c] = bld(rP, oz[c], zt_.base + FB + LN1 + kp);
-                L.zm[k][c] = bld(rP, ozr[c], zr.base + FB + kp);
-                L.zn[k][c] = bld(rP, ozr[c], zr.base + FB + LN + kp);
-            }
-        }
     };
 
-    auto row = [&](auto phase, int t, A2Row<SPG, C> &b, const A2Late<SPG, C> &L) {
+    auto row = [&](auto phase, int t, A2Row<SPG, C> &b, const ALate<C> &L) {
         constexpr int R = decltype(phase)::value;
         constexpr int S0 = R & 3, S1 = (1 + R) & 3, S2 = (2 + R) & 3, S3 = (3 + R) & 3;
         // ---- step A (adjoint step n) at row t
         const bool okt = row_ok(g, t), rnA = row_ok(g, t + 1);
-        cfloat *bzt = zbz + t;
-        const float ahz1A = zahz[t + 1], bhz1A = zbhz[t + 1], azA = zaz[t];
-        const float bt0 = bzt[0], bt1 = bzt[1], bt2 = bzt[2], bt3 = bzt[3];
+        if (t + 3 - rl.base >= WAVE)
+            rl.load(g, a.zpad, t - 3, w.lane, -kZPad, g.Nz + kZPad - 1, node_row, sw.nstrips);
+        const float ahz1A = rl.at(rl.ahz, t + 1), bhz1A = rl.at(rl.bhz, t + 1);
+        const float azA = rl.at(rl.az, t);
+        const float bt0 = rl.at(rl.bz, t), bt1 = rl.at(rl.bz, t + 1);
+        const float bt2 = rl.at(rl.bz, t + 2), bt3 = rl.at(rl.bz, t + 3);
         const bool rp3 = rowpml(t + 3), rpt = rowpml(t);
         // ---- step B (adjoint step n-1) at row r
         const int r = t - 3;
@@ -1365,14 +1460,22 @@ __global__ void __launch_bounds__(NTHR)
         const bool own = r >= w.i0;                           // (r < i1 always)
         const bool ownz = r + 1 >= w.i0 && r + 1 < w.i1;      // owns lvz / gbz row r+1
         const bool rnB = row_ok(g, r + 1);
-        const float ahz1B = zahz[r + 1], bhz1B = zbhz[r + 1], azB = zaz[r];
-        const float bu0 = bzt[-3], bu1 = bzt[-2], bu2 = bzt[-1], bu3 = bzt[0];
+        const float ahz1B = rl.at(rl.ahz, r + 1), bhz1B = rl.at(rl.bhz, r + 1);
+        const float azB = rl.at(rl.az, r);
+        const float bu0 = rl.at(rl.bz, r), bu1 = rl.at(rl.bz, r + 1);
+        const float bu2 = rl.at(rl.bz, r + 2), bu3 = bt0;
         const unsigned rbB = own ? rowb(g, r) : 0u, rbZ = ownz ? rowb(g, r + 1) : 0u;
         const ZRow zB = zrow(g, own ? r : 0);
         unsigned zwB[C];
         zoffs_w<C>(w, zB, zwB);
         float numA[C], axA[C], azA_[C], bKA[4][C];
         float numB[C], axB[C], azB_[C], bKB[4][C];
+        float dly[RN][C];   // iteration t - 3
+#pragma unroll
+        for (int n = 0; n < RN; ++n)
+#pragma unroll
+            for (int c = 0; c < C; ++c)
+                dly[n][c] = D[S1][n][c][w.lane];
 #pragma unroll
         for (int c = 0; c < C; ++c) {
             KA[S3][c] = b.K3[c];
@@ -1400,27 +1503,18 @@ __global__ void __launch_bounds__(NTHR)
             AdjOut<C> oA;
             adj_shot<C, S0, S1, S2, S3>(g, xt, w, rnA, ahz1A, bhz1A, azA, bKA, KA[S0], MUA[k],
                                         MZA[k], PNA[k], WZA[k], b.lvz1[k], b.lvx[k], b.bx, b.bz1,
-                                        L.pn1[k], L.z0[k], L.z1[k], numA, axA, azA_, oA);
+                                        axA, azA_, oA);
             // step A's new state as step B's input: zero outside the grid
             float mA[C];
 #pragma unroll
             for (int c = 0; c < C; ++c)
                 mA[c] = okt && w.colok[c] ? oA.opx[c] : 0.f;
-            // the adjoint source of step n-1 at the receiver nodes of row t
-            const unsigned ie = b.inj[k];
-            if (ie != 0u) {
-                const unsigned first = ie >> 9, cnt = ie & 511u;
-                for (unsigned e = 0; e < cnt; ++e) {
-                    const int j = injcol[first + e];
-                    const float v = injacc[first + e];
-#pragma unroll
-                    for (int c = 0; c < C; ++c)
-                        if (w.j0 + c == j)
-                            mA[c] += v;
-                }
-            }
+            const unsigned ieA = rl.node(k, t);
+            if (ieA != 0u)
+                add_nodes<C>(a.nd, a.injA, nlA[k], nbase[k], ieA, w.lane, w.j0, mA, oA.t);
 #pragma unroll
             for (int c = 0; c < C; ++c) {
+                numA[c] += PNA[k][S0][c] * oA.t[c];
                 const bool in = okt && w.colok[c];
                 MUB[k][S3][c] = mA[c];
                 MZB[k][S3][c] = rpt || w.colpml[c] ? (in ? oA.opz[c] : 0.f) : mA[c];
@@ -1429,9 +1523,15 @@ __global__ void __launch_bounds__(NTHR)
             if (runB) {
                 AdjOut<C> oB;
                 adj_shot<C, S0, S1, S2, S3>(g, xt, w, rnB, ahz1B, bhz1B, azB, bKB, KB[S0],
-                                            MUB[k], MZB[k], PMB[k], WZB[k], DLZ[k][S1],
-                                            DLX[k][S1], DBX[S1], DBZ[S1], DPN[k][S1], L.zm[k],
-                                            L.zn[k], numB, axB, azB_, oB);
+                                            MUB[k], MZB[k], PMB[k], WZB[k], dly[RZ + k],
+                                            dly[RX + k], dly[RBX], dly[RBZ], axB, azB_, oB);
+                const unsigned ieB = own && a.injB ? rl.node(k, r) : 0u;
+                if (ieB != 0u)
+                    add_nodes<C>(a.nd, a.injB, nlB[k], nbase[k], ieB, w.lane, w.j0, oB.opx,
+                                 oB.t);
+#pragma unroll
+                for (int c = 0; c < C; ++c)
+                    numB[c] += PMB[k][S0][c] * oB.t[c];
                 const unsigned ko = skoff(a.lout, k);
                 vst_row<C>(rLout, w, own, rbB + 2u * FB + ko, oB.opx);
 #pragma unroll
@@ -1443,9 +1543,8 @@ __global__ void __launch_bounds__(NTHR)
             // step A's values for step B three rows later
 #pragma unroll
             for (int c = 0; c < C; ++c) {
-                DLX[k][S0][c] = okt && w.colok[c] ? oA.ovx[c] : 0.f;
-                DLZ[k][S0][c] = rnA && w.colok[c] ? oA.ovz[c] : 0.f;
-                DPN[k][S0][c] = PNA[k][S0][c];
+                D[S0][RX + k][c][w.lane] = okt && w.colok[c] ? oA.ovx[c] : 0.f;
+                D[S0][RZ + k][c][w.lane] = rnA && w.colok[c] ? oA.ovz[c] : 0.f;
             }
         }
         if (runB) {
@@ -1455,11 +1554,11 @@ __global__ void __launch_bounds__(NTHR)
 #pragma unroll
             for (int c = 0; c < C; ++c) {
                 const float rK = KB[S0][c] != 0.f ? __builtin_amdgcn_rcpf(KB[S0][c]) : 0.f;
-                gk[c] = L.gK[c] + DNK[S1][c] * rK;
+                gk[c] = L.gK[c] + dly[RNK][c] * rK;
                 gk[c] = gk[c] + numB[c] * rK;
-                gx[c] = L.gX[c] + DAX[S1][c];
+                gx[c] = L.gX[c] + dly[RAX][c];
                 gx[c] = gx[c] + axB[c];
-                gz[c] = L.gZ1[c] + DAZ[S1][c];
+                gz[c] = L.gZ1[c] + dly[RAZ][c];
                 gz[c] = gz[c] + azB_[c];
             }
             vst_row<C>(rG, w, own, rbB, gk);
@@ -1468,16 +1567,16 @@ __global__ void __launch_bounds__(NTHR)
         }
 #pragma unroll
         for (int c = 0; c < C; ++c) {
-            DNK[S0][c] = numA[c];
-            DAX[S0][c] = axA[c];
-            DAZ[S0][c] = azA_[c];
-            DBX[S0][c] = b.bx[c];
-            DBZ[S0][c] = b.bz1[c];
+            D[S0][RNK][c][w.lane] = numA[c];
+            D[S0][RAX][c][w.lane] = axA[c];
+            D[S0][RAZ][c][w.lane] = azA_[c];
+            D[S0][RBX][c][w.lane] = b.bx[c];
+            D[S0][RBZ][c][w.lane] = b.bz1[c];
         }
     };
 
     A2Row<SPG, C> A, B;
-    A2Late<SPG, C> L;
+    ALate<C> L;
     using P0 = std::integral_constant<int, 0>;
     using P1 = std::integral_constant<int, 1>;
     using P2 = std::integral_constant<int, 2>;
@@ -1529,19 +1628,19 @@ void launch_f2(const Geo &g, const float *tabs, const float *model, const SweepT
                           tabs, model, T, S, sw, a);
 }
 template <int SPG, int C>
-void launch_a(const Geo &g, const float *tabs, const float *model, const SweepTables *T, int S,
-              const Sweep &sw, const AdjStep &a, hipStream_t st, hipEvent_t e0, hipEvent_t e1)
+void launch_a(const Geo &g, const float *tabs, const float *model, const Sweep &sw,
+              const AdjStep &a, hipStream_t st, hipEvent_t e0, hipEvent_t e1)
 {
     hipExtLaunchKernelGGL((k_adj<SPG, C>), dim3(blocks_of(sw)), dim3(NTHR), 0, st, e0, e1, 0, g,
-                          tabs, model, T, S, sw, a);
+                          tabs, model, sw, a);
 }
 
 template <int SPG, int C>
-void launch_a2(const Geo &g, const float *tabs, const float *model, int S, const Sweep &sw,
+void launch_a2(const Geo &g, const float *tabs, const float *model, const Sweep &sw,
                const AdjStep2 &a, hipStream_t st, hipEvent_t e0, hipEvent_t e1)
 {
     hipExtLaunchKernelGGL((k_adj2<SPG, C>), dim3(blocks_of(sw)), dim3(NTHR), 0, st, e0, e1, 0, g,
-                          tabs, model, S, sw, a);
+                          tabs, model, sw, a);
 }
 
 // Waves of `kern` that the current device holds at once: its workgroups per
@@ -1562,18 +1661,8 @@ int resident_waves(Kern kern)
 
 }  // namespace
 
-int resident_waves2(bool adjoint, int spg, int cols)
+int resident_waves2(int spg, int cols)
 {
-    if (adjoint) {
-        switch (cols * 16 + spg) {
-        case 16 + 1: return resident_waves(k_adj2<1, 1>);
-        case 16 + 2: return resident_waves(k_adj2<2, 1>);
-        case 16 + 4: return resident_waves(k_adj2<4, 1>);
-        case 32 + 1: return resident_waves(k_adj2<1, 2>);
-        case 32 + 2: return resident_waves(k_adj2<2, 2>);
-        }
-        return 0;
-    }
     switch (cols * 16 + spg) {
     case 16 + 1: return resident_waves(k_fwd2<1, 1>);
     case 16 + 2: return resident_waves(k_fwd2<2, 1>);
@@ -1674,25 +1763,23 @@ void launch_fused_fwd2(const Geo &g, const float *tabs, const float *model,
     }
 }
 
-void launch_fused_adj2(const Geo &g, const float *tabs, const float *model, int S,
-                       const Sweep &sw, const AdjStep2 &a, hipStream_t st, hipEvent_t e0,
-                       hipEvent_t e1)
+void launch_fused_adj2(const Geo &g, const float *tabs, const float *model, const Sweep &sw,
+                       const AdjStep2 &a, hipStream_t st, hipEvent_t e0, hipEvent_t e1)
 {
     switch (sw.cols * 16 + sw.spg) {
-    case 16 + 1: launch_a2<1, 1>(g, tabs, model, S, sw, a, st, e0, e1); break;
-    case 16 + 2: launch_a2<2, 1>(g, tabs, model, S, sw, a, st, e0, e1); break;
-    case 16 + 4: launch_a2<4, 1>(g, tabs, model, S, sw, a, st, e0, e1); break;
-    case 32 + 1: launch_a2<1, 2>(g, tabs, model, S, sw, a, st, e0, e1); break;
-    case 32 + 2: launch_a2<2, 2>(g, tabs, model, S, sw, a, st, e0, e1); break;
+    case 16 + 1: launch_a2<1, 1>(g, tabs, model, sw, a, st, e0, e1); break;
+    case 16 + 2: launch_a2<2, 1>(g, tabs, model, sw, a, st, e0, e1); break;
+    case 16 + 4: launch_a2<4, 1>(g, tabs, model, sw, a, st, e0, e1); break;
+    case 32 + 1: launch_a2<1, 2>(g, tabs, model, sw, a, st, e0, e1); break;
+    case 32 + 2: launch_a2<2, 2>(g, tabs, model, sw, a, st, e0, e1); break;
     default: break;
     }
 }
 
-void launch_fused_adj(const Geo &g, const float *tabs, const float *model,
-                      const SweepTables *T, int S, const Sweep &sw, const AdjStep &a,
-                      hipStream_t st, hipEvent_t e0, hipEvent_t e1)
+void launch_fused_adj(const Geo &g, const float *tabs, const float *model, const Sweep &sw,
+                      const AdjStep &a, hipStream_t st, hipEvent_t e0, hipEvent_t e1)
 {
-    FWI_DISPATCH(launch_a, g, tabs, model, T, S, sw, a, st, e0, e1)
+    FWI_DISPATCH(launch_a, g, tabs, model, sw, a, st, e0, e1)
 }
 
 }  // namespace fwi

@@ -350,8 +350,8 @@ __global__ void __launch_bounds__(NW * WAVE) __attribute__((amdgpu_waves_per_eu(
 
 // ---------------------------------------------------------------- adjoint
 //
-// State on entry to step m (descending): mu = adjoint of p^m with R^T r^{m-1}
-// already added (zero before the first step, m = nt).  Step m:
+// State on entry to step m (descending): mu, lv = adjoint after step m+1 with
+// R^T r^m already added (zero before the first step, m = nt).  Step m:
 //   lv_mid = lv + D+(beta K mu),  gb += lv_mid (-beta_h D+ p^m)
 //   t = D-(beta_h b lv_mid),  mu' = alpha mu + t + R^T r^{m-1}
 //   gK += p^m (t + R^T r^{m-1}) / K,  lv' = alpha_h lv_mid
