@@ -333,9 +333,9 @@ fwi_status fwi_descent_norms(int64_t n, const float *a, const float *b, float *o
  * centres cells [C][2] and P points pts [P][2] ((x, z) in metres), writes
  * G [F][C][P] = G0(pts[p]; cells[c]) and its gradient with respect to the
  * cell position, Gx and Gz (same layout; both NULL or both non-NULL).  The
- * Hankel functions are evaluated in FP64 (ascending series up to k r = 12,
- * Hankel's asymptotic expansion beyond) and rounded to FP32.  A point that
- * coincides with a cell centre gets 0 (the singular self term is left out).
+ * Hankel functions are evaluated in FP64 (fits of their smooth parts, up to
+ * k r = 8 and beyond) and rounded to FP32.  A point that coincides with a
+ * cell centre gets 0 (the singular self term is left out).
  * Tables of the sources (pts = sources) and of the receivers (pts =
  * receivers) feed fwi_born_data and fwi_born_gradient; the direct wave
  * G0(x_r; x_s) is the table with cells = sources and pts = receivers

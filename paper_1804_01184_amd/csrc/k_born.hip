@@ -25,7 +25,6 @@ namespace fwi {
 namespace {
 
 constexpr double kPi = 3.14159265358979323846;
-constexpr double kEulerGamma = 0.57721566490153286061;
 
 __device__ inline void cmac(float2 &acc, float2 a, float2 b)
 {
@@ -35,133 +34,238 @@ __device__ inline void cmac(float2 &acc, float2 a, float2 b)
     acc.y = fmaf(a.y, b.x, acc.y);
 }
 
-// H0 and H1 of the first kind at z > 0, FP64.  For z <= 12 the ascending
-// series of J0, J1, Y0 and Y1 (Abramowitz & Stegun 9.1.10-9.1.13), up to
-// 34 terms; beyond, Hankel's asymptotic expansion (A&S 9.2.5-9.2.10), up to
-// 24 terms (below the smallest term at z = 12).  Both stop once the terms
-// fall below 1e-18 of the sums (series) or 1e-18 absolute (expansion, whose
-// sums are near 1).  Relative error below 1e-11 against library Hankel
-// functions over (0, 600].
-__device__ inline void hankel01(double z, double2 &h0, double2 &h1)
+// H0 and H1 of the first kind, FP64, by polynomials fitted (interpolation at
+// Chebyshev nodes in 50-digit arithmetic) to the smooth parts of the functions
+// (Abramowitz & Stegun 9.1.10-9.1.13 and 9.2.5-9.2.10), with q = z^2:
+//  z <= 8: J0 = kJ0(q), J1 = z kJ1(q), Y0 = (2/pi) ln(z/2) J0 + kY0(q),
+//          Y1 = (2/pi) ln(z/2) J1 - 2/(pi z) + z kY1(q);
+//  beyond: with t = 64/q, H0 = sqrt(2/(pi z)) (kP0(t) + i kQ0(t)/z) e^{i(z -
+//          pi/4)}, H1 the same with kP1, kQ1 and 3 pi/4.
+// The fits hold to 4e-13.  kSin, kCos: (sin r / r - 1) / r^2 and (cos r - 1 +
+// r^2/2) / r^4 in r^2 on |r| <= pi/4; kAtanh: (atanh s / s - 1) / s^2 in s^2 for
+// the logarithm of a number in [sqrt(1/2), sqrt(2)].
+struct HankelFits {
+    double j0[14];
+    double j1[13];
+    double y0[14];
+    double y1[13];
+    double p0[8];
+    double q0[8];
+    double p1[8];
+    double q1[8];
+    double sin[6];
+    double cos[6];
+    double atanh[7];
+};
+
+// Not const: the evaluation reads the coefficients with scalar loads, as scalar
+// operands of the multiply-adds.  Folded into the code each would cost two
+// vector moves, or, hoisted, two vector registers.
+__constant__ HankelFits kHankelFits = {
+    // j0
+    {
+        0.9999999999999572043, -0.24999999999973782578, 0.015624999999733470806,
+        -0.00043402777767097507023, 6.7816840054270305896e-6, -6.7816837473309711815e-8,
+        4.709500514671600133e-10, -2.4027949215353595835e-12, 9.3854789987930326262e-15,
+        -2.8955704111326555279e-17, 7.2165659298467443337e-20, -1.4619900035641834196e-22,
+        2.2916232939754155663e-25, -2.1572475316340808821e-28},
+    // j1
+    {
+        0.49999999999992488639, -0.062499999999603210955, 0.0026041666663190563466,
+        -0.00005425347210246335148, 6.7816838131915695578e-7, -5.6514010654425559235e-9,
+        3.3639148438873005429e-11, -1.5016822309942907482e-13, 5.2121314499462638237e-16,
+        -1.443437545998798192e-18, 3.2172429633435731951e-21, -5.502789423709497323e-24,
+        5.6110340657238926651e-27},
+    // y0
+    {
+        0.36746690519668789215, 0.067288216792300682914, -0.0091791055207200690225,
+        0.00034707870821628387703, -6.5024433166199339449e-6, 7.3659137111036989289e-8,
+        -5.6149081110198401634e-10, 3.0832547273758600763e-12, -1.2790137344919944897e-14,
+        4.150497425842241877e-17, -1.0799648959402175201e-19, 2.2689972911032069787e-22,
+        -3.6608996610966444043e-25, 3.5163693313010823991e-28},
+    // y1
+    {
+        0.024578509506537139641, 0.026769238140771144964, -0.0018061615847086134648,
+        0.000047702192492997437319, -6.9341784126636405219e-7, 6.4380742801699146213e-9,
+        -4.1635927937762061729e-11, 1.98668016056152811e-13, -7.2867028061173489042e-16,
+        2.1141510222845600483e-18, -4.8997388290641789349e-21, 8.6427197945358487798e-24,
+        -9.0030089590404234719e-27},
+    // p0
+    {
+        0.99999999999994500632, -0.0010986328054246964598, 0.000027380731218344226662,
+        -2.1826361458224328399e-6, 3.5653580416357752692e-7, -8.8784284458752349479e-8,
+        2.2779968314839150533e-8, -3.4847854195629241764e-9},
+    // q0
+    {
+        -0.12499999999965337459, 0.0011444091350653774757, -0.000055445324997359559167,
+        6.582591018335405075e-6, -1.4177993431358785477e-6, 4.2391321045424295295e-7,
+        -1.20507062055868782e-7, 1.9422201870656740034e-8},
+    // p1
+    {
+        1.0000000000000594474, 0.0018310546798520035145, -0.000035203828536838568742,
+        2.5796093876226302928e-6, -4.0437007550875756549e-7, 9.8499853783403413323e-8,
+        -2.4999275865222461659e-8, 3.8049125847715505426e-9},
+    // q1
+    {
+        0.37499999999962687244, -0.001602172803530637258, 0.00006776664917162284443,
+        -7.5959349964801027881e-6, 1.5861085097058607519e-6, -4.6621640070498607782e-7,
+        1.3141200534002729273e-7, -2.1094092541175852538e-8},
+    // sin
+    {
+        -0.16666666666666664498, 0.0083333333333308269303, -0.00019841269836575642768,
+        2.7557316008147241632e-6, -2.5051112268671621888e-8, 1.5916725966176020443e-10},
+    // cos
+    {
+        0.04166666666666666531, -0.0013888888888887321196, 0.000024801587298651250119,
+        -2.7557317212671384338e-7, 2.0876134021649628009e-9, -1.1381754511224291529e-11},
+    // atanh
+    {
+        0.33333333333333350761, 0.19999999999943257228, 0.14285714315895303417,
+        0.11111105098130762589, 0.090914783874292007506, 0.076647481537395702497,
+        0.073218370965616570338},
+};
+
+typedef const HankelFits __attribute__((address_space(4))) *FitsPtr;
+
+typedef const double __attribute__((address_space(4))) *CoefPtr;
+
+// The polynomial with M coefficients c at x.
+template <int M>
+__device__ inline double poly(CoefPtr c, double x)
 {
-    if (z <= 12.0) {
-        const double q = 0.25 * z * z;
-        double t0 = 1.0, j0 = 1.0, hk = 0.0, s0 = 0.0;
-        double t1 = 0.5 * z, j1 = t1, ps = 1.0 - 2.0 * kEulerGamma, s1 = ps * t1;
+    // left to itself the compiler copies each c to vector registers (two moves)
+    // to accumulate into it
+    double v;
+    asm("v_mov_b64 %0, %1" : "=v"(v) : "s"(c[M - 1]));
 #pragma unroll
-        for (int k = 1; k <= 33; ++k) {
-            t0 *= -q * (1.0 / ((double)k * k));
-            hk += 1.0 / k;
-            j0 += t0;
-            s0 -= hk * t0;
-            t1 *= -q * (1.0 / ((double)k * (k + 1)));
-            j1 += t1;
-            ps += 1.0 / k + 1.0 / (k + 1);
-            s1 += ps * t1;
-            if (fabs(t0) + fabs(t1) < 1e-18 * (fabs(j0) + fabs(j1)))
-                break;
-        }
-        const double L = log(0.5 * z);
-        const double y0 = (2.0 / kPi) * ((L + kEulerGamma) * j0 + s0);
-        const double y1 = -2.0 / (kPi * z) + (2.0 / kPi) * L * j1 - s1 / kPi;
-        h0 = make_double2(j0, y0);
-        h1 = make_double2(j1, y1);
+    for (int i = M - 2; i >= 0; --i) {
+        double u;
+        asm("v_fma_f64 %0, %1, %2, %3" : "=v"(u) : "v"(v), "v"(x), "s"(c[i]));
+        v = u;
+    }
+    return v;
+}
+
+// 1 / sqrt(x), x > 0: the hardware's estimate and one step of third order.
+__device__ inline double rsqrt_pos(double x)
+{
+    const double y = __builtin_amdgcn_rsq(x);
+    const double e = fma(-x * y, y, 1.0);
+    return fma(y * e, fma(e, 0.375, 0.5), y);
+}
+
+// ln x of a normal x > 0; -inf at 0, NaN below.
+__device__ inline double log_pos(FitsPtr fit, double x)
+{
+    double m = __builtin_amdgcn_frexp_mant(x);
+    int e = __builtin_amdgcn_frexp_exp(x);
+    const bool low = m < 0.70710678118654752;
+    m = low ? m + m : m;
+    e = low ? e - 1 : e;
+    const double d = m + 1.0;
+    double rd = __builtin_amdgcn_rcp(d);
+    rd = fma(fma(-d, rd, 1.0), rd, rd);
+    rd = fma(fma(-d, rd, 1.0), rd, rd);
+    const double s = (m - 1.0) * rd, w = s * s;
+    const double l =
+        fma((double)e, 0.69314718055994530942, 2.0 * fma(s * w, poly<7>(fit->atanh, w), s));
+    return x > 0.0 ? l : (x == 0.0 ? -__builtin_inf() : __builtin_nan(""));
+}
+
+// H0 and H1 at z = k r: rz = 1 / z, lz = (2/pi) ln(z/2), az = sqrt(2/(pi z)).  The
+// reduction of z - pi/4 holds to 2^50; beyond, where a double z no longer
+// carries a phase, it is only kept in range.
+__device__ inline void hankel01(FitsPtr fit, double z, double rz, double lz, double az,
+                                double2 &h0, double2 &h1)
+{
+    if (fabs(z) <= 8.0) {
+        const double q = z * z;
+        const double j0 = poly<14>(fit->j0, q), j1 = z * poly<13>(fit->j1, q);
+        const double y0 = poly<14>(fit->y0, q), y1 = poly<13>(fit->y1, q);
+        h0 = make_double2(j0, fma(lz, j0, y0));
+        h1 = make_double2(j1, fma(lz, j1, fma(z, y1, -(2.0 / kPi) * rz)));
         return;
     }
-    const double r8z = 1.0 / (8.0 * z);
-    // P + i Q with a_k(nu) = prod_{j<=k} (4 nu^2 - (2j - 1)^2) / (j 8 z)
-    double a0 = 1.0, a1 = 1.0, P0 = 1.0, Q0 = 0.0, P1 = 1.0, Q1 = 0.0;
-#pragma unroll
-    for (int k = 1; k < 24; ++k) {
-        const double m = (double)(2 * k - 1) * (2 * k - 1);
-        a0 *= (0.0 - m) * (1.0 / k) * r8z;
-        a1 *= (4.0 - m) * (1.0 / k) * r8z;
-        const double sg = ((k >> 1) & 1) ? -1.0 : 1.0;
-        if (k & 1) {
-            Q0 += sg * a0;
-            Q1 += sg * a1;
-        } else {
-            P0 += sg * a0;
-            P1 += sg * a1;
-        }
-        if (fabs(a0) + fabs(a1) < 1e-18)
-            break;
-    }
-    const double amp = sqrt(2.0 / (kPi * z));
-    double s, c;
-    sincos(z - 0.25 * kPi, &s, &c);
-    // H0 = amp (P0 + i Q0) e^{i(z - pi/4)}; H1 = amp (P1 + i Q1) e^{i(z - 3 pi/4)},
+    const double t = 64.0 * rz * rz;
+    // z - pi/4 = n pi/2 + r, |r| <= pi/4, with pi/2 and pi/4 in two parts; adding
+    // and taking off 1.5 x 2^52 rounds to n and leaves n mod 4 in the low bits
+    const double zc = fmin(z, 0x1p50);
+    const double u = fma(zc, 2.0 / kPi, -0.5) + 0x1.8p52, n = u - 0x1.8p52;
+    const int quadrant = __double2loint(u);
+    double r = fma(-n, 0x1.921fb54442d18p+0, zc) - 0x1.921fb54442d18p-1;
+    r -= fma(n, 0x1.1a62633145c07p-54, 0x1.1a62633145c07p-55);
+    const double w = r * r;
+    const double sn = fma(r * w, poly<6>(fit->sin, w), r);
+    const double cs = fma(w * w, poly<6>(fit->cos, w), fma(-0.5, w, 1.0));
+    const double s1 = quadrant & 1 ? cs : sn, c1 = quadrant & 1 ? -sn : cs;
+    const double amp = __hiloint2double(__double2hiint(az) ^ ((quadrant & 2) << 30),
+                                        __double2loint(az));
+    const double s = amp * s1, c = amp * c1;
+    const double P0 = poly<8>(fit->p0, t), Q0 = poly<8>(fit->q0, t) * rz;
+    const double P1 = poly<8>(fit->p1, t), Q1 = poly<8>(fit->q1, t) * rz;
     // e^{i(z - 3 pi/4)} = -i e^{i(z - pi/4)}
-    h0 = make_double2(amp * (P0 * c - Q0 * s), amp * (P0 * s + Q0 * c));
-    h1 = make_double2(amp * (P1 * s + Q1 * c), -amp * (P1 * c - Q1 * s));
+    h0 = make_double2(P0 * c - Q0 * s, P0 * s + Q0 * c);
+    h1 = make_double2(P1 * s + Q1 * c, Q1 * s - P1 * c);
 }
 
-// One entry: G0 and its gradient between point (px, pz) and cell (cx, cz).
-__device__ inline void green_entry(double cx, double cz, double px, double pz, double k,
-                                   double rho0, float2 &g, float2 &gx, float2 &gz)
+// One entry a thread for a run of frequencies: the distance, its logarithm and
+// its roots serve all of them.  Entries are taken in the order of the table
+// (cell by cell, points contiguous), so that a wave's store is 512 contiguous
+// bytes and k r, and with it the branch of the Hankel evaluation, varies
+// little across it.  Tiles of 64 cells x 32 points through LDS, and waves of 8
+// x 8 or 4 x 16 entries, share fewer branches but write parts of 64-byte
+// pieces: as fast at 360 points, 1.3 to 1.6 times as long at 100 and 211.
+// grid: x, z = pieces of 256 entries, y = runs of frequencies.
+//
+// What bounds it is the FP64 rate: at 401^2 cells, 400 points, 4 frequencies
+// (6.2 GB) 1.40 ms, 4.1 ms with the term-by-term series and one entry and
+// frequency at a time that this replaces; writing alone would take 0.95 ms.
+constexpr int kGreenRun = 64;   // frequencies in a run at most
+
+__global__ __launch_bounds__(256) void k_born_green(int F, int frun, int C, int P,
+                                                    const float *omega, const float *cells,
+                                                    const float *pts, double slow, double rho0,
+                                                    float2 *G, float2 *Gx, float2 *Gz)
 {
-    const double dx = cx - px, dz = cz - pz;
-    const double r = sqrt(dx * dx + dz * dz);
-    g = gx = gz = make_float2(0.f, 0.f);
-    if (r > 0.0) {
+    __shared__ double4 wave[kGreenRun];   // k, 1/k, (2/pi) ln(k/2), sqrt(2/(pi k))
+    FitsPtr fit = (FitsPtr)&kHankelFits;
+    const int f0 = (int)blockIdx.y * frun, f1 = min(f0 + frun, F);
+    if (f0 + (int)threadIdx.x < f1) {
+        const double k = (double)omega[f0 + threadIdx.x] * slow;
+        wave[threadIdx.x] = make_double4(k, 1.0 / k, (2.0 / kPi) * log_pos(fit, 0.5 * k),
+                                         0.79788456080286535588 * rsqrt_pos(k));
+    }
+    __syncthreads();
+    const long long e0 = ((long long)blockIdx.z * gridDim.x + blockIdx.x) * 256;
+    const long long cb = e0 / P;
+    const unsigned t = (unsigned)(e0 - cb * P) + threadIdx.x;
+    const long long c = cb + t / (unsigned)P, q = t % (unsigned)P;
+    if (c >= C)
+        return;
+    const double dx = (double)cells[2 * c] - (double)pts[2 * q];
+    const double dz = (double)cells[2 * c + 1] - (double)pts[2 * q + 1];
+    const double r2 = dx * dx + dz * dz;
+    const double rr = rsqrt_pos(r2), r = r2 * rr, rs = rsqrt_pos(r);
+    const double ux = dx * rr, uz = dz * rr;
+    const double lr = (1.0 / kPi) * log_pos(fit, r2);
+    const double a = 0.25 * rho0;
+    long long at = ((long long)f0 * C + c) * P + q;
+    for (int f = f0; f < f1; ++f, at += (long long)C * P) {
+        asm volatile("" : "+s"(fit));   // read anew for each frequency, not held across
+        const double4 k = wave[f - f0];
         double2 h0, h1;
-        hankel01(k * r, h0, h1);
+        hankel01(fit, k.x * r, k.y * rr, k.z + lr, k.w * rs, h0, h1);
         // G = (i rho0/4)(J0 + i Y0); grad = (rho0 k/4)(Y1 - i J1) (x - y)/r
-        const double a = 0.25 * rho0;
-        g = make_float2((float)(-a * h0.y), (float)(a * h0.x));
-        const double b = a * k / r;
-        gx = make_float2((float)(b * h1.y * dx), (float)(-b * h1.x * dx));
-        gz = make_float2((float)(b * h1.y * dz), (float)(-b * h1.x * dz));
-    }
-}
-
-// Tiles of 64 cells x 32 points for one frequency.  The 64 lanes of a
-// wave take 64 neighbouring cells at one point, so that k r, and with it
-// the branch of the Hankel evaluation, varies little across a wave; the
-// tile goes out through LDS, one table at a time, with the points of a
-// cell contiguous.  grid: x = cell tiles, y = point tiles, z = frequency.
-constexpr int kGTC = 64, kGTP = 32;
-
-__global__ __launch_bounds__(256) void k_born_green(int F, int C, int P, const float *omega,
-                                                    const float *cells, const float *pts,
-                                                    double slow, double rho0, float2 *G,
-                                                    float2 *Gx, float2 *Gz)
-{
-    constexpr int PER = kGTP / 4;   // points per thread
-    __shared__ float2 tile[kGTC][kGTP + 1];
-    const int f = blockIdx.z;
-    const int c0 = blockIdx.x * kGTC, p0 = blockIdx.y * kGTP;
-    const int lc = (int)(threadIdx.x & 63), w = (int)(threadIdx.x >> 6);
-    const int c = c0 + lc;
-    const bool live = c < C;
-    const double cx = live ? (double)cells[2 * c] : 0.0;
-    const double cz = live ? (double)cells[2 * c + 1] : 0.0;
-    const double k = (double)omega[f] * slow;
-    float2 g[PER], gx[PER], gz[PER];
-#pragma unroll
-    for (int j = 0; j < PER; ++j) {
-        const int p = p0 + w * PER + j;
-        g[j] = gx[j] = gz[j] = make_float2(0.f, 0.f);
-        if (live && p < P)
-            green_entry(cx, cz, (double)pts[2 * p], (double)pts[2 * p + 1], k, rho0, g[j],
-                        gx[j], gz[j]);
-    }
-    const long long base = (long long)f * C;
-    const int np = min(kGTP, P - p0);
-#pragma unroll 1
-    for (int t = 0; t < 3; ++t) {
-        float2 *out = t == 0 ? G : (t == 1 ? Gx : Gz);
-        if (!out)
-            break;
-        __syncthreads();
-#pragma unroll
-        for (int j = 0; j < PER; ++j)
-            tile[lc][w * PER + j] = t == 0 ? g[j] : (t == 1 ? gx[j] : gz[j]);
-        __syncthreads();
-        for (int e = (int)threadIdx.x; e < kGTC * kGTP; e += 256) {
-            const int rc = e / kGTP, jp = e % kGTP;
-            if (c0 + rc < C && jp < np)
-                out[(base + c0 + rc) * P + p0 + jp] = tile[rc][jp];
+        float2 g = make_float2((float)(-a * h0.y), (float)(a * h0.x));
+        const double b = a * k.x, by = b * h1.y, bj = -b * h1.x;
+        float2 gx = make_float2((float)(by * ux), (float)(bj * ux));
+        float2 gz = make_float2((float)(by * uz), (float)(bj * uz));
+        if (!(r2 > 0.0))
+            g = gx = gz = make_float2(0.f, 0.f);
+        G[at] = g;
+        if (Gx) {
+            Gx[at] = gx;
+            Gz[at] = gz;
         }
     }
 }
@@ -940,9 +1044,15 @@ void launch_born_green(int F, int C, int P, const float *omega, const float *cel
     const long long n = (long long)F * C * P;
     if (n <= 0)
         return;
-    const dim3 grid((unsigned)((C + kGTC - 1) / kGTC), (unsigned)((P + kGTP - 1) / kGTP),
-                    (unsigned)F);
-    hipLaunchKernelGGL(k_born_green, grid, dim3(256), 0, st, F, C, P, omega, cells, pts,
+    const long long pieces = ((long long)C * P + 255) / 256;
+    // All frequencies in one run where the pieces alone fill the chip (8 resident
+    // workgroups on each of 256 compute units) twice over, shorter runs below.
+    const int runs = (int)std::min<long long>(F, (4095 + pieces) / pieces);
+    const int frun = std::min((F + runs - 1) / runs, kGreenRun);
+    const int nz = (int)((pieces + (1 << 22) - 1) >> 22);
+    const dim3 grid((unsigned)((pieces + nz - 1) / nz), (unsigned)((F + frun - 1) / frun),
+                    (unsigned)nz);
+    hipLaunchKernelGGL(k_born_green, grid, dim3(256), 0, st, F, frun, C, P, omega, cells, pts,
                        std::sqrt(rho0 / K0), rho0, (float2 *)G, (float2 *)Gx, (float2 *)Gz);
 }
 
