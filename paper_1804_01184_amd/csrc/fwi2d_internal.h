@@ -340,20 +340,21 @@ struct BornSplit {
     int ts;               // source chunk width (template instance)
     int ns;               // data on the matrix cores: 16-wide source tiles per wave (0: off)
     int nrg, sgroups;     // matrix-core data: 32-receiver groups, source groups
-    int gns, gsgroups;    // gradient on the matrix cores: source tiles per wave (0: off),
-                          // source groups
+    int gns, gsgroups;    // gradient: source tiles per wave (0: no sources), source groups
     int block, rtiles;    // data: receivers per block, receiver tiles
     int schunks;          // source chunks
     int nsplit;           // data: cell ranges summed by the finishing kernel
     int cells_per_split;
-    int cblocks;          // gradient: blocks of 256 cells
+    int cblocks;          // gradient: blocks of cells
     int fsplit;           // gradient: frequency ranges
     int freqs_per_split;
 };
 BornSplit born_data_split(int F, int S, int R, int C);
-// Byte offset, in the gradient workspace, of the transposed weights of the
-// matrix-core gradient (F S R complex) after the 2 fsplit C partial sums.
+// Byte offset, in the gradient workspace, of the weights of the gradient after
+// the 2 fsplit C partial sums, and their size: for each frequency 12 bytes a
+// complex weight, sources rounded up to the tiles of a group, receivers to 16.
 size_t born_grad_wt_offset(const BornSplit &b, int C);
+size_t born_grad_wt_bytes(const BornSplit &b, int F, int R);
 void launch_born_green(int F, int C, int P, const float *omega, const float *cells,
                        const float *pts, double K0, double rho0, float *G, float *Gx, float *Gz,
                        hipStream_t st);
@@ -363,8 +364,7 @@ void launch_born_data(const BornSplit &b, int F, int S, int R, int C, const floa
                       const float *xiR, const float *Gs, const float *Gsx, const float *Gsz,
                       const float *Gr, const float *Grx, const float *Grz, const float *Gd,
                       float *d, float *part, hipStream_t st);
-// part: 2 * fsplit * C floats (and, on the matrix-core path, F S R complex
-// weights at born_grad_wt_offset).
+// part: 2 * fsplit * C floats, and the weights at born_grad_wt_offset.
 void launch_born_gradient(const BornSplit &b, int F, int S, int R, int C, const float *omega,
                           const float *spec, double K0, double rho0, double dA,
                           const float *resid, const float *Gs, const float *Gsx,

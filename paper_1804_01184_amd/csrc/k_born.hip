@@ -355,37 +355,116 @@ __global__ __launch_bounds__(512) void k_born_data(int F, int S, int R, int C, i
 }
 
 typedef float v4f __attribute__((ext_vector_type(4)));
+typedef float v4f8 __attribute__((ext_vector_type(4), aligned(8)));   // two float2 of a table
+typedef __bf16 v8bf __attribute__((ext_vector_type(8)));
+
+// Three bf16 parts of a pair of FP32 values, one pair in a register (x below):
+// x = h + m + l to 24 bits and more, each the rest's nearest bf16.  Sums of
+// products on the bf16 matrix cores take the six products h h, h m, m h, m m,
+// h l, l h; the dropped ones are within 2^-24 of the product, the size of an FP32
+// rounding of it.  Against FP64 sums over the same tables the data are off by 1.3
+// to 2.3e-7 at 9 to 53 sources (FP32 matrix instructions: 1.3 to 4.9e-7), the
+// gradients by 0.5 to 3.7e-7 (0.6 to 4.4e-7).
+struct Split3 {
+    unsigned h, m, l;
+};
+
+__device__ inline unsigned bf16_pair(float x, float y)
+{
+    typedef float v2f __attribute__((ext_vector_type(2)));
+    typedef __bf16 v2bf __attribute__((ext_vector_type(2)));
+    return __builtin_bit_cast(unsigned, __builtin_convertvector((v2f){x, y}, v2bf));
+}
+
+__device__ inline Split3 split3(float x, float y)
+{
+    Split3 s;
+    s.h = bf16_pair(x, y);
+    x -= __uint_as_float(s.h << 16);
+    y -= __uint_as_float(s.h & 0xffff0000u);
+    s.m = bf16_pair(x, y);
+    x -= __uint_as_float(s.m << 16);
+    y -= __uint_as_float(s.m & 0xffff0000u);
+    s.l = bf16_pair(x, y);
+    return s;
+}
+
+// A matrix operand of v_mfma_f32_16x16x32_bf16 in parts [h, m, l]: 4 pairs a
+// lane.  Lane l holds row (or column) l % 16 and 8 of 32 k, which of them is for
+// the caller to choose, the same for both operands; D[4 (l / 16) + v][l % 16] is
+// left in register v of lane l.
+struct Frag3 {
+    uint4 part[3];
+};
+
+__device__ inline Frag3 frag3(const Split3 (&p)[4])
+{
+    Frag3 f;
+    f.part[0] = make_uint4(p[0].h, p[1].h, p[2].h, p[3].h);
+    f.part[1] = make_uint4(p[0].m, p[1].m, p[2].m, p[3].m);
+    f.part[2] = make_uint4(p[0].l, p[1].l, p[2].l, p[3].l);
+    return f;
+}
+
+// (re, -im) and (im, re) of pairs (re, im).
+__device__ inline uint4 conj_form(uint4 u)
+{
+    const unsigned n = 0x80000000u;
+    return make_uint4(u.x ^ n, u.y ^ n, u.z ^ n, u.w ^ n);
+}
+
+__device__ inline uint4 swap_form(uint4 u)
+{
+    return make_uint4(__builtin_amdgcn_alignbit(u.x, u.x, 16),
+                      __builtin_amdgcn_alignbit(u.y, u.y, 16),
+                      __builtin_amdgcn_alignbit(u.z, u.z, 16),
+                      __builtin_amdgcn_alignbit(u.w, u.w, 16));
+}
+
+__device__ inline v4f mfma_bf16(uint4 a, uint4 b, v4f d)
+{
+    return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(v8bf, a),
+                                                   __builtin_bit_cast(v8bf, b), d, 0, 0, 0);
+}
+
+// The six products, the small ones first: part of the first operand, of the second.
+constexpr int kProducts = 6;
+constexpr int kProdA[kProducts] = {2, 0, 1, 1, 0, 0}, kProdB[kProducts] = {0, 2, 1, 0, 1, 0};
 
 // The same partial sums on the matrix cores: per frequency and cell range,
 // D[r][s] = sum_k A[k][r] B[k][s] with k running over (table, cell) and
-// complex entries, A = coefficient x receiver table, B = source table.
-// v_mfma_f32_16x16x4f32 takes A[i][k] from lane 16k + i, B[k][j] from lane
-// 16k + j and leaves D[4 (l / 16) + v][l % 16] in register v of lane l.  A
-// complex product is two real ones over k = (cell pair) x (re, im part):
-// lanes 0-31 carry two cells' real parts, lanes 32-63 their imaginary
-// parts, so that Re D = sum ar br - ai bi and Im D = sum ar bi + ai br.
-// A wave computes 32 receivers x 16 NS sources; the four waves of a block
-// take consecutive receiver groups of one (frequency, cell range, source
-// group) and share, per chunk of 8 cells, the source tables and cell
-// coefficients staged in LDS (two buffers).  The next chunk is loaded while
-// one is computed: its source side into registers, stored to the other
-// buffer after the computation, and each lane's receiver-table parts of a
-// cell pair as soon as the current chunk's pair has been consumed.  Blocks
-// are remapped so that those of one cell range run on one XCD.
+// complex entries, A = receiver table, B = coefficient x source table, both in
+// three bf16 parts.  A complex product is two real ones over k = (cell, re / im
+// part): Re D = sum ar br - ai bi, Im D = sum ar bi + ai br, so that the
+// receiver side comes in two forms, (ar, -ai) and (ai, ar).
+// A wave computes 32 receivers x 16 NS sources from chunks of 16 cells; a lane
+// reads two neighbouring receivers at once (rows of two tiles) at four cells.
+// The four waves of a block take consecutive receiver groups of one (frequency,
+// cell range, source group) and share, per chunk, the source side in LDS (two
+// buffers).  The next chunk is loaded while one is computed.  Blocks are
+// remapped so that those of one cell range run on one XCD.
+//
+// Reading the tables and the matrix instructions bound it together: at three
+// source tiles a chunk is 12 KB and 216 instructions of 16 cycles a wave (432 of
+// 32 cycles with FP32 operands, which alone were the bound).  401^2 cells, 40 x
+// 360 pairs, 16 frequencies (24.8 GB of tables): 5.9 ms, 10.5 ms with FP32
+// operands; 4.4 ms with the first of the six products alone.  16 receivers a
+// wave, for three or four waves a SIMD, take 6.9 to 8.0 ms; splitting one tile
+// between the products of another, 6.2 to 6.5 ms.
 // Cells per chunk of the matrix-core data kernel.
-constexpr int kDCH = 8;
+constexpr int kDCH = 16;
 
-template <int NS>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void k_born_data_mfma(
+template <int NS, bool PAIRS>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k_born_data_mfma(
     int F, int S, int R, int C, int nsplit, int cells_per_split, int sgroups, int nrg,
     long long nblocks, const float *omega, float dA_K0, float cR, const float *xiK,
     const float *xiR, const float2 *Gs, const float2 *Gsx, const float2 *Gsz, const float2 *Gr,
     const float2 *Grx, const float2 *Grz, float2 *part)
 {
     constexpr int SW = 16 * NS;
-    constexpr int NST = (3 * kDCH * SW + 255) / 256;
-    __shared__ float2 sB[2][3][kDCH][SW];
-    __shared__ float sq[2][2][kDCH];
+    constexpr int kItems = 3 * 4 * SW;   // (table, four cells, source) staged per chunk
+    constexpr int NST = (kItems + 255) / 256;
+    __shared__ uint4 sB[2][3][3][4][SW];   // [buffer][table][part][cell % 4][source]
     const long long per = (nblocks + 7) / 8;
     const long long w = (long long)(blockIdx.x % 8) * per + blockIdx.x / 8;
     if (w >= nblocks)
@@ -402,20 +481,16 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void k
     // others; it computes and stores nothing
     const bool active = rg < nrg;
     const int l = threadIdx.x & 63;
-    const int li = l & 15, kk = l >> 4, cpar = kk & 1;
-    const bool second = kk >= 2;
-    const int r0 = (active ? rg : 0) * 32, s0 = sg * SW;
-    int rA[2];
-#pragma unroll
-    for (int t = 0; t < 2; ++t)
-        rA[t] = min(r0 + 16 * t + li, R - 1);
+    const int li = l & 15, kk = l >> 4;
+    // the last group is moved back to end with the last receiver; below 32
+    // receivers (PAIRS false) rows past the end repeat the last one
+    const int r_first = (active ? rg : 0) * 32, r0 = max(0, min(r_first, R - 32)), s0 = sg * SW;
+    const int ra = min(r0 + 2 * li, R - 1), rb1 = min(ra + 1, R - 1);
     const int c_begin = split * cells_per_split;
     const int c_end = min(C, c_begin + cells_per_split);
     const float wf = omega[f];
     const float aK = wf * wf * dA_K0;
     const long long fC = (long long)f * C;
-    const int part_off = second ? 1 : 0;
-    const float *Gr1 = (const float *)Gr, *Grx1 = (const float *)Grx, *Grz1 = (const float *)Grz;
     v4f dre[2][NS], dim[2][NS];
 #pragma unroll
     for (int a = 0; a < 2; ++a)
@@ -424,127 +499,145 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void k
             dre[a][b] = v4f{0.f, 0.f, 0.f, 0.f};
             dim[a][b] = v4f{0.f, 0.f, 0.f, 0.f};
         }
-    float av[kDCH / 2][3][2];
-    float2 stg[NST];
-    float sqv = 0.f;
-    const int qc = threadIdx.x % kDCH;
-    const bool isK = (threadIdx.x / kDCH) % 2 == 0;
-    const float *xq = isK ? xiK : xiR;
-    const float qcoef = threadIdx.x < 2 * kDCH ? (isK ? aK : cR) : 0.f;
-    // receiver-table parts of cell pair P of the chunk at CN
-#define LOAD_PAIR(CN, P)                                                                   \
-    {                                                                                      \
-        const int nc_ = min(kDCH, c_end - (CN));                                           \
-        const int c_ = (CN) + min(2 * (P) + cpar, nc_ - 1);                                \
-        _Pragma("unroll") for (int a = 0; a < 2; ++a)                                      \
-        {                                                                                  \
-            const long long o = 2 * (((fC + c_) * R) + rA[a]) + part_off;                  \
-            av[P][0][a] = Gr1[o];                                                          \
-            av[P][1][a] = Grx1[o];                                                         \
-            av[P][2][a] = Grz1[o];                                                         \
-        }                                                                                  \
+    v4f av[3][4];           // [table][cell / 4]: two receivers, re and im
+    float2 stg[NST][4];
+    float sq[NST][4];
+    // this thread's items of the source side: a table and a source (a column
+    // past the last one repeats it and is not stored) at cells 4 j + ig
+    const float2 *ib[NST];
+    const float *ix[NST];
+    float ic[NST];
+    int ig[NST];
+#pragma unroll
+    for (int i = 0; i < NST; ++i) {
+        const int e = min((int)threadIdx.x + 256 * i, kItems - 1), t = e / (4 * SW);
+        ib[i] = (t == 0 ? Gs : (t == 1 ? Gsx : Gsz)) + (fC + c_begin) * S + min(s0 + e % SW, S - 1);
+        ix[i] = (t == 0 ? xiK : xiR) + c_begin;
+        ic[i] = t == 0 ? aK : cR;
+        ig[i] = e / SW % 4;
     }
-    // this thread's share of the chunk's source tables and coefficients
-#define LOAD_STAGE(CN)                                                                     \
+    // offsets of this lane's cells 4 j + kk of the chunk at CN, the last cell
+    // again past the end
+    long long off[4];
+#define CHUNK_OFFSETS(CN)                                                                  \
+    _Pragma("unroll") for (int j = 0; j < 4; ++j)                                          \
+        off[j] = (long long)min(4 * j + kk, c_end - 1 - (CN)) * R;
+    // receiver table T of the chunk at CN
+#define LOAD_TABLE(CN, T)                                                                  \
     {                                                                                      \
-        const int nc_ = min(kDCH, c_end - (CN));                                           \
-        _Pragma("unroll") for (int j = 0; j < NST; ++j)                                    \
+        const float2 *base = ((T) == 0 ? Gr : ((T) == 1 ? Grx : Grz)) + (fC + (CN)) * R;   \
+        _Pragma("unroll") for (int j = 0; j < 4; ++j)                                      \
         {                                                                                  \
-            const int e = (int)threadIdx.x + 256 * j;                                      \
-            const int t = e / (kDCH * SW), rem = e % (kDCH * SW);                          \
-            const int cc = rem / SW, sc = rem % SW;                                        \
-            const float2 *B = t == 0 ? Gs : (t == 1 ? Gsx : Gsz);                          \
-            const bool ok = e < 3 * kDCH * SW && cc < nc_ && s0 + sc < S;                  \
-            const float2 v = B[ok ? (fC + (CN) + cc) * S + s0 + sc : 0];                   \
-            stg[j] = ok ? v : make_float2(0.f, 0.f);                                       \
-        }                                                                                  \
-        const float x_ = xq[(CN) + min(qc, nc_ - 1)];                                      \
-        sqv = qc < nc_ ? qcoef * x_ : 0.f;                                                 \
-    }
-#define STORE_STAGE(BUF)                                                                   \
-    {                                                                                      \
-        _Pragma("unroll") for (int j = 0; j < NST; ++j)                                    \
-        {                                                                                  \
-            const int e = (int)threadIdx.x + 256 * j;                                      \
-            if (e < 3 * kDCH * SW) {                                                       \
-                const int t = e / (kDCH * SW), rem = e % (kDCH * SW);                      \
-                sB[BUF][t][rem / SW][rem % SW] = stg[j];                                   \
+            const float2 *row = base + off[j];                                             \
+            if (PAIRS) {                                                                   \
+                av[T][j] = *(const v4f8 *)(row + ra);                                      \
+            } else {                                                                       \
+                const float2 u = row[ra], v = row[rb1];                                    \
+                av[T][j] = v4f{u.x, u.y, v.x, v.y};                                        \
             }                                                                              \
         }                                                                                  \
-        if (threadIdx.x < 2 * kDCH)                                                        \
-            sq[BUF][threadIdx.x / kDCH][threadIdx.x % kDCH] = sqv;                         \
+    }
+    // this thread's share of the chunk's source side; cells past the end have
+    // coefficient 0
+#define LOAD_STAGE(CN)                                                                     \
+    _Pragma("unroll") for (int i = 0; i < NST; ++i)                                        \
+    {                                                                                      \
+        if (256 * (i + 1) <= kItems || (int)threadIdx.x < kItems - 256 * i) {              \
+            const int last = c_end - 1 - (CN);                                             \
+            const float2 *B = ib[i] + (long long)((CN) - c_begin) * S;                     \
+            const float *x = ix[i] + ((CN) - c_begin);                                     \
+            _Pragma("unroll") for (int j = 0; j < 4; ++j)                                  \
+            {                                                                              \
+                const int g = 4 * j + ig[i], k = min(g, last);                             \
+                stg[i][j] = B[(long long)k * S];                                           \
+                sq[i][j] = (g <= last ? ic[i] : 0.f) * x[k];                               \
+            }                                                                              \
+        }                                                                                  \
+    }
+#define STORE_STAGE(BUF)                                                                   \
+    _Pragma("unroll") for (int i = 0; i < NST; ++i)                                        \
+    {                                                                                      \
+        const int e = (int)threadIdx.x + 256 * i;                                          \
+        if (256 * (i + 1) <= kItems || e < kItems) {                                       \
+            const int t = e / (4 * SW), g = e / SW % 4, s = e % SW;                        \
+            const Split3 p0 = split3(sq[i][0] * stg[i][0].x, sq[i][0] * stg[i][0].y);      \
+            const Split3 p1 = split3(sq[i][1] * stg[i][1].x, sq[i][1] * stg[i][1].y);      \
+            const Split3 p2 = split3(sq[i][2] * stg[i][2].x, sq[i][2] * stg[i][2].y);      \
+            const Split3 p3 = split3(sq[i][3] * stg[i][3].x, sq[i][3] * stg[i][3].y);      \
+            sB[BUF][t][0][g][s] = make_uint4(p0.h, p1.h, p2.h, p3.h);                      \
+            sB[BUF][t][1][g][s] = make_uint4(p0.m, p1.m, p2.m, p3.m);                      \
+            sB[BUF][t][2][g][s] = make_uint4(p0.l, p1.l, p2.l, p3.l);                      \
+        }                                                                                  \
     }
     if (c_begin < c_end) {
-#pragma unroll
-        for (int p = 0; p < kDCH / 2; ++p)
-            LOAD_PAIR(c_begin, p)
         LOAD_STAGE(c_begin)
-        STORE_STAGE(0)
+        CHUNK_OFFSETS(c_begin)
+        LOAD_TABLE(c_begin, 0)
+        LOAD_TABLE(c_begin, 1)
+        LOAD_TABLE(c_begin, 2)
     }
-    __syncthreads();
     int buf = 0;
-    for (int c0 = c_begin; c0 < c_end; c0 += kDCH) {
-        // the next chunk (this one again after the last) is loaded while
-        // this one is computed: its source side into registers for the next
-        // LDS buffer, each cell pair's receiver side once this chunk's pair
-        // has been consumed
+    for (int c0 = c_begin; c0 < c_end; c0 += kDCH, buf ^= 1) {
+        // a buffer is written two chunks after its last readers, who have
+        // passed the barrier between
+        STORE_STAGE(buf)
+        __syncthreads();
+        // the next chunk (this one again after the last) is loaded while this
+        // one is computed, each receiver table once it has been split
         const int cn = c0 + kDCH < c_end ? c0 + kDCH : c0;
         LOAD_STAGE(cn)
+        CHUNK_OFFSETS(cn)
 #pragma unroll
-        for (int p = 0; p < kDCH / 2; ++p) {
-            const int cc = 2 * p + cpar;
-            float aRe[3][2], aIm[3][2];
+        for (int t = 0; t < 3; ++t) {
+            Frag3 fre[2], fim[2];
 #pragma unroll
-            for (int t = 0; t < 3; ++t) {
-                const float q = sq[buf][t == 0 ? 0 : 1][cc];
+            for (int a = 0; a < 2; ++a) {
+                const Split3 p[4] = {split3(av[t][0][2 * a], av[t][0][2 * a + 1]),
+                                     split3(av[t][1][2 * a], av[t][1][2 * a + 1]),
+                                     split3(av[t][2][2 * a], av[t][2][2 * a + 1]),
+                                     split3(av[t][3][2 * a], av[t][3][2 * a + 1])};
+                fim[a] = frag3(p);
+                fre[a] = fim[a];
 #pragma unroll
-                for (int a = 0; a < 2; ++a) {
-                    const float v = q * av[p][t][a];
-                    aRe[t][a] = second ? -v : v;
-                    aIm[t][a] = v;
+                for (int k = 0; k < 3; ++k) {
+                    fre[a].part[k] = conj_form(fim[a].part[k]);
+                    fim[a].part[k] = swap_form(fim[a].part[k]);
                 }
             }
-            LOAD_PAIR(cn, p)
+            LOAD_TABLE(cn, t)
             if (active) {
 #pragma unroll
-                for (int t = 0; t < 3; ++t) {
-                    float bRe[NS], bIm[NS];
+                for (int b = 0; b < NS; ++b) {
+                    uint4 g[3];
 #pragma unroll
-                    for (int b = 0; b < NS; ++b) {
-                        const float2 v = sB[buf][t][cc][16 * b + li];
-                        bRe[b] = second ? v.y : v.x;
-                        bIm[b] = second ? v.x : v.y;
-                    }
+                    for (int k = 0; k < 3; ++k)
+                        g[k] = sB[buf][t][k][kk][16 * b + li];
 #pragma unroll
-                    for (int a = 0; a < 2; ++a)
+                    for (int k = 0; k < kProducts; ++k)
 #pragma unroll
-                        for (int b = 0; b < NS; ++b) {
-                            dre[a][b] = __builtin_amdgcn_mfma_f32_16x16x4f32(
-                                aRe[t][a], bRe[b], dre[a][b], 0, 0, 0);
-                            dim[a][b] = __builtin_amdgcn_mfma_f32_16x16x4f32(
-                                aIm[t][a], bIm[b], dim[a][b], 0, 0, 0);
+                        for (int a = 0; a < 2; ++a) {
+                            dre[a][b] = mfma_bf16(fre[a].part[kProdA[k]], g[kProdB[k]], dre[a][b]);
+                            dim[a][b] = mfma_bf16(fim[a].part[kProdA[k]], g[kProdB[k]], dim[a][b]);
                         }
                 }
             }
         }
-        STORE_STAGE(buf ^ 1)
-        __syncthreads();
-        buf ^= 1;
     }
-#undef LOAD_PAIR
+#undef CHUNK_OFFSETS
+#undef LOAD_TABLE
 #undef LOAD_STAGE
 #undef STORE_STAGE
     if (!active)
         return;
     float2 *out = part + ((long long)split * F + f) * S * R;
 #pragma unroll
-    for (int a = 0; a < 2; ++a)
+    for (int b = 0; b < NS; ++b)
 #pragma unroll
-        for (int b = 0; b < NS; ++b)
+        for (int v = 0; v < 4; ++v)
 #pragma unroll
-            for (int v = 0; v < 4; ++v) {
-                const int r = r0 + 16 * a + 4 * kk + v, sc = s0 + 16 * b + li;
-                if (r < R && sc < S)
+            for (int a = 0; a < 2; ++a) {
+                const int r = r0 + 2 * (4 * kk + v) + a, sc = s0 + 16 * b + li;
+                if (r >= r_first && r < R && sc < S)
                     out[(long long)sc * R + r] = make_float2(dre[a][b][v], dim[a][b][v]);
             }
 }
@@ -558,6 +651,7 @@ __global__ __launch_bounds__(256) void k_born_finish(long long n, int SR, int ns
     for (long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x; i < n;
          i += (long long)gridDim.x * blockDim.x) {
         float2 v = Gd ? Gd[i] : make_float2(0.f, 0.f);
+#pragma unroll 8
         for (int k = 0; k < nsplit; ++k) {
             const float2 p = part[(long long)k * n + i];
             v.x += p.x;
@@ -568,273 +662,214 @@ __global__ __launch_bounds__(256) void k_born_finish(long long n, int SR, int ns
     }
 }
 
-// Receivers staged per step of the gradient kernel.
-constexpr int kRC = 16;
-constexpr int kGradBlock = 256;
+// Receivers per chunk of the matrix-core gradient kernel.
+constexpr int kGRC = 16;
 
-// Partial gradient over a range of frequencies, one lane per cell:
-//   U_t[s] = sum_r W[f][s][r] Gr_t[f][c][r],  W = conj(resid) spec,
-//   acc_t += Re sum_s Gs_t[f][c][s] U_t[s],
-// partK[split][c] = sum_f w_f^2 acc_G, partR[split][c] = sum_f (acc_x + acc_z).
-// The receiver tables of a block's cells are staged through LDS (coalesced
-// rows in, one row per lane out); W is read by every lane at the same
-// address.  grid: x = cell blocks, y = frequency splits.
-template <int TS>
-__global__ __launch_bounds__(kGradBlock) void k_born_grad(int F, int S, int R, int C,
-                                                          int freqs_per_split,
-                                                          const float *omega,
-                                                          const float2 *spec,
-                                                          const float2 *resid,
-                                                          const float2 *Gs, const float2 *Gsx,
-                                                          const float2 *Gsz, const float2 *Gr,
-                                                          const float2 *Grx, const float2 *Grz,
-                                                          float *partK, float *partR)
+// Receiver of pair j of lane group kk in a chunk: two neighbours at a time.
+__device__ inline int grad_receiver(int kk, int j)
 {
-    __shared__ float2 sA[kGradBlock][kRC + 1];
-    __shared__ float2 sW[kRC][TS];
-    const int c_first = blockIdx.x * kGradBlock;
-    const int c = c_first + threadIdx.x;
-    const bool live = c < C;
-    const int cl = live ? c : C - 1;
-    const int f_begin = blockIdx.y * freqs_per_split;
-    const int f_end = min(F, f_begin + freqs_per_split);
-    float accK = 0.f, accR = 0.f;
-
-    for (int f = f_begin; f < f_end; ++f) {
-        const float2 sp = spec[f];
-        const long long fC = (long long)f * C;
-        const float2 *res = resid + (long long)f * S * R;
-#pragma unroll 1
-        for (int t = 0; t < 3; ++t) {
-            const float2 *A = t == 0 ? Gr : (t == 1 ? Grx : Grz);
-            const float2 *B = t == 0 ? Gs : (t == 1 ? Gsx : Gsz);
-            float acc_t = 0.f;
-            for (int s0 = 0; s0 < S; s0 += TS) {
-                float2 U[TS];
-#pragma unroll
-                for (int s = 0; s < TS; ++s)
-                    U[s] = make_float2(0.f, 0.f);
-                for (int r0 = 0; r0 < R; r0 += kRC) {
-                    const int nr = min(kRC, R - r0);
-                    __syncthreads();
-                    // receiver table rows of this block's cells
-                    for (int e = threadIdx.x; e < kGradBlock * kRC; e += kGradBlock) {
-                        const int row = e / kRC, j = e % kRC;
-                        const int cc = c_first + row;
-                        float2 v = make_float2(0.f, 0.f);
-                        if (cc < C && j < nr)
-                            v = A[(fC + cc) * R + r0 + j];
-                        sA[row][j] = v;
-                    }
-                    // W[s][r] = conj(resid) spec, stored [r][s]
-                    for (int e = threadIdx.x; e < kRC * TS; e += kGradBlock) {
-                        const int j = e / TS, s = e % TS;
-                        float2 v = make_float2(0.f, 0.f);
-                        if (j < nr && s0 + s < S) {
-                            const float2 q = res[(long long)(s0 + s) * R + r0 + j];
-                            v = make_float2(q.x * sp.x + q.y * sp.y, q.x * sp.y - q.y * sp.x);
-                        }
-                        sW[j][s] = v;
-                    }
-                    __syncthreads();
-                    for (int j = 0; j < nr; ++j) {
-                        const float2 a = sA[threadIdx.x][j];
-#pragma unroll
-                        for (int s = 0; s < TS; ++s)
-                            cmac(U[s], sW[j][s], a);
-                    }
-                }
-                if (live) {
-                    const float2 *b = B + (fC + cl) * S + s0;
-#pragma unroll
-                    for (int s = 0; s < TS; ++s) {
-                        if (s0 + s < S) {
-                            const float2 v = b[s];
-                            acc_t = fmaf(v.x, U[s].x, acc_t);
-                            acc_t = fmaf(-v.y, U[s].y, acc_t);
-                        }
-                    }
-                }
-            }
-            if (t == 0) {
-                const float w = omega[f];
-                accK = fmaf(w * w, acc_t, accK);
-            } else {
-                accR += acc_t;
-            }
-        }
-    }
-    if (live) {
-        partK[(long long)blockIdx.y * C + c] = accK;
-        partR[(long long)blockIdx.y * C + c] = accR;
-    }
+    return 8 * (j / 2) + 2 * kk + j % 2;
 }
 
-// Wt[f][r][s] = conj(resid[f][s][r]) spec[f]: the weights of the gradient
-// sums, sources contiguous for the matrix-core kernel.
-__global__ __launch_bounds__(256) void k_born_wt(int F, int S, int R, const float2 *spec,
-                                                 const float2 *resid, float2 *Wt)
+// The weights W[s][r] = conj(resid[f][s][r]) spec[f] of the gradient sums as
+// first matrix operands (rows: 16 sources; k: 16 receivers, (wr, wi)) in three
+// bf16 parts: Wf[f][source group][receiver chunk][source tile][part][lane].
+// Zero past the last source and receiver.
+__global__ __launch_bounds__(256) void k_born_weights(long long n, int S, int R, int sgroups,
+                                                      int ns, int nchunk, const float2 *spec,
+                                                      const float2 *resid, uint4 *Wf)
 {
-    const long long n = (long long)F * S * R;
     for (long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x; i < n;
          i += (long long)gridDim.x * blockDim.x) {
-        const int s = (int)(i % S);
-        const long long fr = i / S;
-        const int r = (int)(fr % R);
-        const int f = (int)(fr / R);
-        const float2 q = resid[((long long)f * S + s) * R + r];
+        const int l = (int)(i % 64), li = l & 15, kk = l >> 4;
+        long long k = i / 64;
+        const int b = (int)(k % ns);
+        k /= ns;
+        const int ch = (int)(k % nchunk);
+        k /= nchunk;
+        const int sg = (int)(k % sgroups);
+        const int f = (int)(k / sgroups);
+        const int s = (sg * ns + b) * 16 + li;
         const float2 sp = spec[f];
-        Wt[i] = make_float2(q.x * sp.x + q.y * sp.y, q.x * sp.y - q.y * sp.x);
+        Split3 p[4];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const int r = ch * kGRC + grad_receiver(kk, j);
+            float2 q = make_float2(0.f, 0.f);
+            if (s < S && r < R) {
+                q = resid[((long long)f * S + s) * R + r];
+                q = make_float2(q.x * sp.x + q.y * sp.y, q.x * sp.y - q.y * sp.x);
+            }
+            p[j] = split3(q.x, q.y);
+        }
+        uint4 *out = Wf + (i / 64 * 3) * 64 + l;
+        const Frag3 w = frag3(p);
+#pragma unroll
+        for (int k = 0; k < 3; ++k)
+            out[64 * k] = w.part[k];
     }
 }
-
-// Receivers staged per step of the matrix-core gradient kernel.
-constexpr int kGRC = 8;
 
 // The gradient sums on the matrix cores.  Per frequency and table,
 // U_t[s][c] = sum_r W[s][r] A_t[c][r] is a complex product with k over
-// (receiver pair, re/im part), laid out as in k_born_data_mfma: D[s][c] with
-// the weights as the first operand (rows: 16 sources) and the receiver
-// table as the second (columns: 16 cells).  A block stages, per chunk of 8
-// receivers, the rows of its 64 cells (four waves of 16 cells) in the three
-// tables and the weights once, in LDS; the three tables' products share the
-// weights.  The next chunk is loaded into registers while one is computed
-// (three waves per SIMD; two for four source tiles, whose accumulators take
-// 96 registers).  The epilogue adds Re sum_s Gs_t[c][s] U_t[s][c] per lane
-// and the four lane groups holding one cell are summed at the end.
+// (receiver, re / im part), in three bf16 parts as in k_born_data_mfma: D[s][c]
+// with the weights as the first operand (rows: 16 sources) and the receiver
+// table as the second (columns: 16 cells).  A block takes 64 cells, 16 a wave; a
+// lane reads its cell's rows, two neighbouring receivers at once, straight from
+// the tables, and the weights of a chunk of 16 receivers go through LDS (two
+// buffers, in the forms of the real and of the imaginary part), once for the
+// block and its three tables.  The next chunk, across source groups and
+// frequencies, is loaded while one is computed.  The epilogue of a frequency
+// and source group adds Re sum_s Gs_t[c][s] U_t[s][c] per lane; the four lane
+// groups holding one cell are summed at the end.
 // grid: x = blocks of 64 cells, y = frequency ranges.
+//
+// Bound as the data kernel is: at the sizes named there 6.4 ms, 10.2 ms with FP32
+// operands, 5.3 ms with one product of the six.  Three waves a SIMD take 7.9 ms
+// (at one source tile, without spills, 5 % more than two), tables loaded two
+// chunks ahead 6.6 ms.
 template <int NS>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(NS >= 4 ? 2 : 3))) void
-k_born_grad_mfma(int F, int S, int R, int C, int freqs_per_split, int sgroups,
-                 const float *omega, const float2 *Wt, const float2 *Gs, const float2 *Gsx,
-                 const float2 *Gsz, const float2 *Gr, const float2 *Grx, const float2 *Grz,
-                 float *partK, float *partR)
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k_born_grad_mfma(
+    int F, int S, int R, int C, int freqs_per_split, int sgroups, const float *omega,
+    const uint4 *Wf, const float2 *Gs, const float2 *Gsx, const float2 *Gsz, const float2 *Gr,
+    const float2 *Grx, const float2 *Grz, float *partK, float *partR)
 {
-    constexpr int SW = 16 * NS;
-    constexpr int kGA = 64 * kGRC / 256, kGW = (kGRC * SW + 255) / 256;
-    static_assert(64 * kGRC % 256 == 0, "receiver rows split evenly over the block");
-    __shared__ float2 sA[3][64][kGRC + 1];
-    __shared__ float2 sW[kGRC][SW];
+    constexpr int kWords = NS * 3 * 64;   // operand words of a chunk, one form
+    constexpr int NW = (kWords + 255) / 256;
+    __shared__ uint4 sW[2][2][kWords];   // [buffer][real, imaginary][tile, part, lane]
     const int wave = (int)(threadIdx.x >> 6), l = (int)(threadIdx.x & 63);
-    const int li = l & 15, kk = l >> 4, rpar = kk & 1;
-    const bool second = kk >= 2;
-    const int cb0 = blockIdx.x * 64;
-    const int cw = wave * 16 + li;
-    const int c = cb0 + cw;
+    const int li = l & 15, kk = l >> 4;
+    const int c = blockIdx.x * 64 + wave * 16 + li;
     const bool live = c < C;
     const int cl = live ? c : C - 1;
     const int f_begin = blockIdx.y * freqs_per_split;
     const int f_end = min(F, f_begin + freqs_per_split);
-    float accK = 0.f, accR = 0.f;
+    const int nchunk = (R + kGRC - 1) / kGRC;
+    float accK = 0.f, accR = 0.f, acc[3] = {0.f, 0.f, 0.f};
 
-    for (int f = f_begin; f < f_end; ++f) {
-        const long long fC = (long long)f * C;
-        const float2 *W = Wt + (long long)f * R * S;
-        float acc[3] = {0.f, 0.f, 0.f};
-        for (int sg = 0; sg < sgroups; ++sg) {
-            const int s0 = sg * SW;
-            v4f dre[3][NS], dim[3][NS];
+    v4f av[3][2];   // [table][receiver pair]
+    uint4 rw[NW];
+    auto load_weights = [&](const uint4 *W) {
 #pragma unroll
-            for (int t = 0; t < 3; ++t)
+        for (int k = 0; k < NW; ++k) {
+            const int e = (int)threadIdx.x + 256 * k;
+            rw[k] = W[e < kWords ? e : 0];
+        }
+    };
+    auto load_tables = [&](int f, int ch) {
+        const long long row = ((long long)f * C + cl) * R;
+        const int r0 = ch * kGRC;
 #pragma unroll
-                for (int b = 0; b < NS; ++b) {
-                    dre[t][b] = v4f{0.f, 0.f, 0.f, 0.f};
-                    dim[t][b] = v4f{0.f, 0.f, 0.f, 0.f};
-                }
-            // a chunk's receiver rows of the block's cells (three tables) and
-            // weights, loaded into registers one chunk ahead
-            float2 ra[kGA][3], rw[kGW];
-#define GRAD_LOAD(R0)                                                                      \
-    {                                                                                      \
-        const int nr_ = min(kGRC, R - (R0));                                               \
-        _Pragma("unroll") for (int k = 0; k < kGA; ++k)                                    \
-        {                                                                                  \
-            const int e = (int)threadIdx.x + 256 * k;                                      \
-            const int row = e / kGRC, j = e % kGRC;                                        \
-            const bool ok = cb0 + row < C && j < nr_;                                      \
-            const long long o = ok ? (fC + cb0 + row) * R + (R0) + j : 0;                  \
-            const float2 v0 = Gr[o], v1 = Grx[o], v2 = Grz[o];                             \
-            ra[k][0] = make_float2(ok ? v0.x : 0.f, ok ? v0.y : 0.f);                      \
-            ra[k][1] = make_float2(ok ? v1.x : 0.f, ok ? v1.y : 0.f);                      \
-            ra[k][2] = make_float2(ok ? v2.x : 0.f, ok ? v2.y : 0.f);                      \
-        }                                                                                  \
-        _Pragma("unroll") for (int k = 0; k < kGW; ++k)                                    \
-        {                                                                                  \
-            const int e = (int)threadIdx.x + 256 * k;                                      \
-            const int j = e / SW, s = e % SW;                                              \
-            const bool ok = e < kGRC * SW && j < nr_ && s0 + s < S;                        \
-            const float2 v = W[ok ? (long long)((R0) + j) * S + s0 + s : 0];               \
-            rw[k] = make_float2(ok ? v.x : 0.f, ok ? v.y : 0.f);                           \
-        }                                                                                  \
-    }
-            GRAD_LOAD(0)
-            for (int r0 = 0; r0 < R; r0 += kGRC) {
-                __syncthreads();
+        for (int t = 0; t < 3; ++t) {
+            const float2 *A = (t == 0 ? Gr : (t == 1 ? Grx : Grz)) + row;
 #pragma unroll
-                for (int k = 0; k < kGA; ++k) {
-                    const int e = (int)threadIdx.x + 256 * k;
-#pragma unroll
-                    for (int t = 0; t < 3; ++t)
-                        sA[t][e / kGRC][e % kGRC] = ra[k][t];
-                }
-#pragma unroll
-                for (int k = 0; k < kGW; ++k) {
-                    const int e = (int)threadIdx.x + 256 * k;
-                    if (e < kGRC * SW)
-                        sW[e / SW][e % SW] = rw[k];
-                }
-                __syncthreads();
-                // the next chunk (this one again after the last) is in
-                // flight while this one is computed
-                const int rn = r0 + kGRC < R ? r0 + kGRC : r0;
-                GRAD_LOAD(rn)
-#pragma unroll 2
-                for (int p = 0; p < kGRC / 2; ++p) {
-                    const int j = 2 * p + rpar;
-                    float are[NS], aim[NS];
-#pragma unroll
-                    for (int b = 0; b < NS; ++b) {
-                        const float2 w = sW[j][16 * b + li];
-                        are[b] = second ? -w.y : w.x;
-                        aim[b] = second ? w.y : w.x;
-                    }
-#pragma unroll
-                    for (int t = 0; t < 3; ++t) {
-                        const float2 a = sA[t][cw][j];
-                        const float bre = second ? a.y : a.x;
-                        const float bim = second ? a.x : a.y;
-#pragma unroll
-                        for (int b = 0; b < NS; ++b) {
-                            dre[t][b] = __builtin_amdgcn_mfma_f32_16x16x4f32(are[b], bre,
-                                                                             dre[t][b], 0, 0, 0);
-                            dim[t][b] = __builtin_amdgcn_mfma_f32_16x16x4f32(aim[b], bim,
-                                                                             dim[t][b], 0, 0, 0);
-                        }
-                    }
-                }
-            }
-#undef GRAD_LOAD
-            if (live) {
-#pragma unroll
-                for (int t = 0; t < 3; ++t) {
-                    const float2 *brow = (t == 0 ? Gs : (t == 1 ? Gsx : Gsz)) + (fC + cl) * S;
-#pragma unroll
-                    for (int b = 0; b < NS; ++b)
-#pragma unroll
-                        for (int v = 0; v < 4; ++v) {
-                            const int s = s0 + 16 * b + 4 * kk + v;
-                            if (s < S) {
-                                const float2 g = brow[s];
-                                acc[t] = fmaf(g.x, dre[t][b][v], acc[t]);
-                                acc[t] = fmaf(-g.y, dim[t][b][v], acc[t]);
-                            }
-                        }
+            for (int h = 0; h < 2; ++h) {
+                const int r = r0 + grad_receiver(kk, 2 * h);
+                if (r0 + kGRC <= R) {
+                    av[t][h] = *(const v4f8 *)(A + r);
+                } else {
+                    const float2 u = A[min(r, R - 1)], v = A[min(r + 1, R - 1)];
+                    av[t][h] = v4f{u.x, u.y, v.x, v.y};
                 }
             }
         }
-        const float w = omega[f];
-        accK = fmaf(w * w, acc[0], accK);
-        accR += acc[1] + acc[2];
+    };
+    v4f dre[3][NS], dim[3][NS];
+#pragma unroll
+    for (int t = 0; t < 3; ++t)
+#pragma unroll
+        for (int b = 0; b < NS; ++b) {
+            dre[t][b] = v4f{0.f, 0.f, 0.f, 0.f};
+            dim[t][b] = v4f{0.f, 0.f, 0.f, 0.f};
+        }
+    int f = f_begin, sg = 0, ch = 0, buf = 0;
+    const uint4 *W = Wf + (long long)f_begin * sgroups * nchunk * kWords;
+    if (f < f_end) {
+        load_weights(W);
+        load_tables(f, 0);
+    }
+    while (f < f_end) {
+        // a buffer is written two chunks after its last readers, who have
+        // passed the barrier between
+#pragma unroll
+        for (int k = 0; k < NW; ++k) {
+            const int e = (int)threadIdx.x + 256 * k;
+            if (e < kWords) {
+                sW[buf][0][e] = conj_form(rw[k]);
+                sW[buf][1][e] = swap_form(rw[k]);
+            }
+        }
+        __syncthreads();
+        Frag3 tab[3];
+#pragma unroll
+        for (int t = 0; t < 3; ++t) {
+            Split3 p[4];
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+                p[j] = split3(av[t][j / 2][2 * (j % 2)], av[t][j / 2][2 * (j % 2) + 1]);
+            tab[t] = frag3(p);
+        }
+        // the next chunk; this one again after the last
+        int fn = f, sn = sg, cn = ch + 1;
+        if (cn == nchunk) {
+            cn = 0;
+            if (++sn == sgroups) {
+                sn = 0;
+                ++fn;
+            }
+        }
+        const bool more = fn < f_end;
+        W += more ? kWords : 0;
+        load_weights(W);
+        load_tables(more ? fn : f, more ? cn : ch);
+#pragma unroll
+        for (int b = 0; b < NS; ++b) {
+            uint4 wre[3], wim[3];
+#pragma unroll
+            for (int k = 0; k < 3; ++k) {
+                wre[k] = sW[buf][0][(b * 3 + k) * 64 + l];
+                wim[k] = sW[buf][1][(b * 3 + k) * 64 + l];
+            }
+#pragma unroll
+            for (int k = 0; k < kProducts; ++k)
+#pragma unroll
+                for (int t = 0; t < 3; ++t) {
+                    dre[t][b] = mfma_bf16(wre[kProdA[k]], tab[t].part[kProdB[k]], dre[t][b]);
+                    dim[t][b] = mfma_bf16(wim[kProdA[k]], tab[t].part[kProdB[k]], dim[t][b]);
+                }
+        }
+        if (cn == 0) {   // the last chunk of this frequency and source group
+            const int s0 = sg * 16 * NS;
+#pragma unroll
+            for (int t = 0; t < 3; ++t) {
+                const float2 *brow =
+                    (t == 0 ? Gs : (t == 1 ? Gsx : Gsz)) + ((long long)f * C + cl) * S;
+#pragma unroll
+                for (int b = 0; b < NS; ++b) {
+#pragma unroll
+                    for (int v = 0; v < 4; ++v) {
+                        const int s = s0 + 16 * b + 4 * kk + v;
+                        if (s < S) {
+                            const float2 g = brow[s];
+                            acc[t] = fmaf(g.x, dre[t][b][v], acc[t]);
+                            acc[t] = fmaf(-g.y, dim[t][b][v], acc[t]);
+                        }
+                    }
+                    dre[t][b] = v4f{0.f, 0.f, 0.f, 0.f};
+                    dim[t][b] = v4f{0.f, 0.f, 0.f, 0.f};
+                }
+            }
+            if (sn == 0) {
+                const float w = omega[f];
+                accK = fmaf(w * w, acc[0], accK);
+                accR += acc[1] + acc[2];
+                acc[0] = acc[1] = acc[2] = 0.f;
+            }
+        }
+        f = fn;
+        sg = sn;
+        ch = cn;
+        buf ^= 1;
     }
     // lanes li, li + 16, li + 32, li + 48 hold the same cell
     accK += __shfl_xor(accK, 16);
@@ -1079,27 +1114,34 @@ static int data_mfma_blocks_per_cu(int ns)
         int n = 0;
         hipError_t e = hipErrorInvalidValue;
         switch (ns) {
-        case 1: e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, k_born_data_mfma<1>, 256, 0); break;
-        case 2: e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, k_born_data_mfma<2>, 256, 0); break;
-        case 3: e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, k_born_data_mfma<3>, 256, 0); break;
-        case 4: e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, k_born_data_mfma<4>, 256, 0); break;
+        case 1: e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, k_born_data_mfma<1, true>, 256, 0); break;
+        case 2: e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, k_born_data_mfma<2, true>, 256, 0); break;
+        case 3: e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, k_born_data_mfma<3, true>, 256, 0); break;
+        case 4: e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, k_born_data_mfma<4, true>, 256, 0); break;
         }
         cache[ns].store((e == hipSuccess && n > 0) ? n : 4, std::memory_order_relaxed);
     }
     return cache[ns].load(std::memory_order_relaxed);
 }
 
+// Shortest cell range, over one round, that the matrix-core data kernel is split
+// to: every range pays for filling its pipeline and writes its partial sums, which
+// the finishing kernel reads (121^2 cells, 10 x 100 pairs, 15 frequencies: 150,
+// 133, 119, 118 us at 64, 128, 256, 512; always 8 rounds: 264).
+constexpr long long kRangeCells = 256;
+
 BornSplit born_data_split(int F, int S, int R, int C)
 {
     BornSplit b;
     b.ts = born_ts(S);
-    // matrix cores for the data from 9 sources (below, the vector kernel's
-    // chunk of 8 wastes less than a 16-wide tile) and for the gradient from
-    // 2 (measured with 360 receivers, 401^2 cells and 32 frequencies: the
-    // vector gradient takes 18-21 ms at 4-11 sources, the matrix-core one
-    // 11 ms)
+    // matrix cores for the data from 9 sources: below, both read the tables near
+    // the memory rate and the vector kernel's chunk of 8 wastes less than a
+    // 16-wide tile (201^2 cells, 200 receivers, 16 frequencies, vector and
+    // matrix: 588 and 612 us at 4 sources, 602 and 645 at 8).  The gradient is on
+    // the matrix cores for any number (one source, 401^2 cells, 360 receivers:
+    // 4.1 ms, 8.5 with the vector kernel that there was)
     b.ns = S >= 9 ? std::min(4, (S + 15) / 16) : 0;
-    b.gns = S >= 2 ? std::min(4, (S + 15) / 16) : 0;
+    b.gns = S >= 1 ? std::min(4, (S + 15) / 16) : 0;
     b.gsgroups = b.gns ? (S + 16 * b.gns - 1) / (16 * b.gns) : 0;
     int step = kCB;
     long long base;
@@ -1108,8 +1150,7 @@ BornSplit born_data_split(int F, int S, int R, int C)
         b.nrg = (R + 31) / 32;
         b.sgroups = (S + 16 * b.ns - 1) / (16 * b.ns);
         base = (long long)F * b.sgroups * b.nrg;       // waves per cell range
-        target = 16384;
-        step = 2;
+        target = 0;   // set below
         b.block = 256;
         b.rtiles = b.schunks = 0;
     } else {
@@ -1125,12 +1166,14 @@ BornSplit born_data_split(int F, int S, int R, int C)
     long long want = base > 0 ? (target + base - 1) / base : 1;
     if (b.ns && base > 0) {
         // whole rounds of resident blocks (256 CUs x the blocks of 4 waves
-        // that fit one CU at this kernel's register count); 8 rounds,
-        // rounded down so that the last round is full rather than nearly
-        // empty
-        const long long cap = 256LL * data_mfma_blocks_per_cu(b.ns) * 8;
-        const long long blocks_per_range = base / b.nrg * ((b.nrg + 3) / 4);
-        want = std::max(1LL, cap / std::max(1LL, blocks_per_range));
+        // that fit one CU at this kernel's register count), rounded down so that
+        // the last round is full rather than nearly empty: 8, or fewer where the
+        // ranges would get short
+        const long long slots = 256LL * data_mfma_blocks_per_cu(b.ns);
+        const long long per_range = std::max(1LL, base / b.nrg * ((b.nrg + 3) / 4));
+        const long long rounds =
+            std::max(1LL, std::min(8LL, C / kRangeCells * per_range / slots));
+        want = std::max(1LL, rounds * slots / per_range);
     }
     b.nsplit = (int)std::max(1LL, std::min<long long>(want, max_split));
     if (C == 0)
@@ -1140,11 +1183,11 @@ BornSplit born_data_split(int F, int S, int R, int C)
     b.cells_per_split = per;
     if (per > 0)
         b.nsplit = (C + per - 1) / per;
-    // gradient: cell blocks x frequency splits (matrix cores: blocks of 64
-    // cells, about 8192 in all, 10 or more rounds of the 3 blocks that fit
-    // one CU; each block's frequencies are summed in registers)
-    b.cblocks = b.gns ? (C + 63) / 64 : (C + kGradBlock - 1) / kGradBlock;
-    const long long gtarget = b.gns ? 8192 : 2048;
+    // gradient: blocks of 64 cells x frequency splits, about 8192 in all, 16
+    // rounds of the 2 blocks that fit one CU (4096 and 16384: within 2 %);
+    // each block's frequencies are summed in registers
+    b.cblocks = (C + 63) / 64;
+    const long long gtarget = 8192;
     const long long gw = b.cblocks > 0 ? (gtarget + b.cblocks - 1) / b.cblocks : 1;
     b.fsplit = (int)std::max(1LL, std::min<long long>(gw, std::max(F, 1)));
     b.freqs_per_split = F > 0 ? (F + b.fsplit - 1) / b.fsplit : 0;
@@ -1158,6 +1201,11 @@ size_t born_grad_wt_offset(const BornSplit &b, int C)
     return ((size_t)2 * std::max(b.fsplit, 1) * C * sizeof(float) + 255) / 256 * 256;
 }
 
+size_t born_grad_wt_bytes(const BornSplit &b, int F, int R)
+{
+    return (size_t)F * b.gsgroups * ((R + kGRC - 1) / kGRC) * b.gns * 3 * 64 * sizeof(uint4);
+}
+
 template <int NS>
 static void data_mfma(const BornSplit &b, int F, int S, int R, int C, const float *omega,
                       float dA_K0, float cR, const float *xiK, const float *xiR,
@@ -1166,9 +1214,10 @@ static void data_mfma(const BornSplit &b, int F, int S, int R, int C, const floa
 {
     const long long nblocks = (long long)F * b.nsplit * b.sgroups * ((b.nrg + 3) / 4);
     const long long grid = (nblocks + 7) / 8 * 8;
-    hipLaunchKernelGGL(k_born_data_mfma<NS>, dim3((unsigned)grid), dim3(256), 0, st, F, S, R, C,
-                       b.nsplit, b.cells_per_split, b.sgroups, b.nrg, nblocks, omega, dA_K0, cR,
-                       xiK, xiR, Gs, Gsx, Gsz, Gr, Grx, Grz, part);
+    const auto kernel = R >= 32 ? k_born_data_mfma<NS, true> : k_born_data_mfma<NS, false>;
+    hipLaunchKernelGGL(kernel, dim3((unsigned)grid), dim3(256), 0, st, F, S, R, C, b.nsplit,
+                       b.cells_per_split, b.sgroups, b.nrg, nblocks, omega, dA_K0, cR, xiK, xiR,
+                       Gs, Gsx, Gsz, Gr, Grx, Grz, part);
 }
 
 template <int TS>
@@ -1216,17 +1265,6 @@ void launch_born_data(const BornSplit &b, int F, int S, int R, int C, const floa
                        b.nsplit, g2(spec), g2(Gd), (const float2 *)part, (float2 *)d);
 }
 
-template <int TS>
-static void grad_ts(const BornSplit &b, int F, int S, int R, int C, const float *omega,
-                    const float2 *spec, const float2 *resid, const float2 *Gs,
-                    const float2 *Gsx, const float2 *Gsz, const float2 *Gr, const float2 *Grx,
-                    const float2 *Grz, float *partK, float *partR, hipStream_t st)
-{
-    hipLaunchKernelGGL(k_born_grad<TS>, dim3(b.cblocks, b.fsplit), dim3(kGradBlock), 0, st, F,
-                       S, R, C, b.freqs_per_split, omega, spec, resid, Gs, Gsx, Gsz, Gr, Grx,
-                       Grz, partK, partR);
-}
-
 void launch_born_gradient(const BornSplit &b, int F, int S, int R, int C, const float *omega,
                           const float *spec, double K0, double rho0, double dA,
                           const float *resid, const float *Gs, const float *Gsx,
@@ -1243,26 +1281,19 @@ void launch_born_gradient(const BornSplit &b, int F, int S, int R, int C, const 
         return;
     }
     auto g2 = [](const float *p) { return (const float2 *)p; };
-    if (b.gns > 0) {
-        float2 *Wt = (float2 *)((char *)part + born_grad_wt_offset(b, C));
-        const long long n = (long long)F * S * R;
-        hipLaunchKernelGGL(k_born_wt, dim3(grid_for(n, 256)), dim3(256), 0, st, F, S, R,
-                           g2(spec), g2(resid), Wt);
+    uint4 *Wf = (uint4 *)((char *)part + born_grad_wt_offset(b, C));
+    const int nchunk = (R + kGRC - 1) / kGRC;
+    const long long n = (long long)F * b.gsgroups * nchunk * b.gns * 64;
+    hipLaunchKernelGGL(k_born_weights, dim3(grid_for(n, 256)), dim3(256), 0, st, n, S, R,
+                       b.gsgroups, b.gns, nchunk, g2(spec), g2(resid), Wf);
 #define BORN_GMFMA(N)                                                                      \
     case N:                                                                                \
         hipLaunchKernelGGL(k_born_grad_mfma<N>, dim3(b.cblocks, b.fsplit), dim3(256), 0, st, \
-                           F, S, R, C, b.freqs_per_split, b.gsgroups, omega, Wt, g2(Gs),     \
+                           F, S, R, C, b.freqs_per_split, b.gsgroups, omega, Wf, g2(Gs),     \
                            g2(Gsx), g2(Gsz), g2(Gr), g2(Grx), g2(Grz), partK, partR);        \
         break;
-        switch (b.gns) { BORN_GMFMA(1) BORN_GMFMA(2) BORN_GMFMA(3) BORN_GMFMA(4) }
+    switch (b.gns) { BORN_GMFMA(1) BORN_GMFMA(2) BORN_GMFMA(3) BORN_GMFMA(4) }
 #undef BORN_GMFMA
-        hipLaunchKernelGGL(k_born_grad_finish, dim3((C + 255) / 256), dim3(256), 0, st, C,
-                           b.fsplit, dA_K0, cR, partK, partR, gK, gR);
-        return;
-    }
-    // one source (gns == 0 only for S == 1)
-    grad_ts<1>(b, F, S, R, C, omega, g2(spec), g2(resid), g2(Gs), g2(Gsx), g2(Gsz), g2(Gr),
-               g2(Grx), g2(Grz), partK, partR, st);
     hipLaunchKernelGGL(k_born_grad_finish, dim3((C + 255) / 256), dim3(256), 0, st, C, b.fsplit,
                        dA_K0, cR, partK, partR, gK, gR);
 }
