@@ -526,7 +526,7 @@ __global__ void k_descent_apply(long long n, const float *m, const float *m0, co
 
 // out[0] = sum a^2 + sum b^2, out[1] = max |a|, |b| in one workgroup (there is
 // no memory for the partial sums of several): per-thread strided passes in a
-// fixed order, then a fixed tree (the same bits on every call).
+// fixed order, then a fixed tree, in FP64 (the same bits on every call).
 //
 // Memory latency bounds it: one compute unit, so as many bytes in flight as it
 // can hold.  16 waves, each thread with four loads of a and four of b at a time, V
@@ -541,7 +541,8 @@ __global__ void __launch_bounds__(kNormThreads) k_norms2(long long n, const floa
                                                          const float *b, float *out)
 {
     typedef float vec __attribute__((ext_vector_type(V)));
-    __shared__ float part[kNormThreads / 64], top[kNormThreads / 64];
+    __shared__ double part[kNormThreads / 64];
+    __shared__ float top[kNormThreads / 64];
     float acc[kNormLoads], mx = 0.0f;
 #pragma unroll
     for (int j = 0; j < kNormLoads; ++j)
@@ -575,7 +576,7 @@ __global__ void __launch_bounds__(kNormThreads) k_norms2(long long n, const floa
         acc[0] += y * y;
         mx = fmaxf(mx, fmaxf(fabsf(x), fabsf(y)));
     }
-    float s = (acc[0] + acc[1]) + (acc[2] + acc[3]);
+    double s = ((double)acc[0] + acc[1]) + ((double)acc[2] + acc[3]);
 #pragma unroll
     for (int w = 32; w > 0; w >>= 1) {
         s += __shfl_xor(s, w);
@@ -587,12 +588,13 @@ __global__ void __launch_bounds__(kNormThreads) k_norms2(long long n, const floa
     }
     __syncthreads();
     if (threadIdx.x == 0) {
-        float sum = part[0], m = top[0];
+        double sum = part[0];
+        float m = top[0];
         for (int w = 1; w < kNormThreads / 64; ++w) {
             sum += part[w];
             m = fmaxf(m, top[w]);
         }
-        out[0] = sum;
+        out[0] = (float)sum;
         out[1] = m;
     }
 }
