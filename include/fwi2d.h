@@ -154,11 +154,11 @@ typedef struct {
     int32_t adj_two_step_band_rows;   /* its band rows (4..4096), 0: default */
     int32_t adj_two_step_lane_cols;   /* its columns per lane, 0: default    */
     /* With every field from band_rows on left 0, batched plans of up to about
-     * two million padded nodes over all shots run on tile kernels instead
-     * (several steps per launch with a tile's state in registers; the same
-     * traces bit for bit, gradients within FP32 rounding), where the plan
-     * estimates them faster.  fwi_plan_info always describes the strip
-     * kernels.                                                              */
+     * two million padded nodes over all shots (a forward call: four) run on
+     * tile kernels instead (several steps per launch with a tile's state in
+     * registers; the same traces bit for bit, gradients within FP32
+     * rounding), where the plan estimates them faster.  fwi_plan_info always
+     * describes the strip kernels.                                          */
 } fwi_exec;
 
 typedef struct {

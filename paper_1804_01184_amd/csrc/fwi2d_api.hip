@@ -70,7 +70,8 @@ struct fwi_plan {
     // steps per launch and axes of the forward and adjoint tiles, shots per
     // partial gradient, levels of the forward call's sampling buffer
     struct Tiles {
-        bool on = false;
+        bool on = false;    // the sweeps of a gradient
+        bool fwd = false;   // a forward sweep by itself
         int fT = 0, aT = 0, levels = 0;
         TileAxis fx{}, fz{}, ax{}, az{};
     } tile;
@@ -233,7 +234,7 @@ Layout layout(const fwi_plan *p, int op)
     L.Q = take((size_t)p->S * p->grid.nt);
     L.work[0] = take((size_t)B * p->SS);
     L.work[1] = take((size_t)B * p->SS);
-    if (p->tile.on && op == FWI_OP_FORWARD)
+    if (p->tile.fwd && op == FWI_OP_FORWARD)
         L.hist = take((size_t)p->tile.levels * p->S * align64(g.N));
     if (p->two_step)
         L.mid = take((size_t)B * p->ST);
@@ -1087,12 +1088,15 @@ TileAxis tile_axis(int len, int span, int halo, int unit)
 // plus about 3.2 between launches: the load and the store of the tile, then
 // the arithmetic of its T steps.  More steps spread the first over more time
 // but shrink the owned part of a tile (64 - 6 T nodes a side), so T grows until
-// the tiles no longer fit one round.  The strip kernels take 24.5 us a step
-// for both sweeps while the launch is what bounds them and about 20.5 + 9.3
-// per million nodes (all shots) beyond.  The tiles win up to about two million
-// nodes (one shot of 141 x 141: 6.7 against 25.0; 10 of 161 x 161: 7.9 against
-// 26.9; 8 of 241 x 241: 11.9 against 26.8; 16 of 341 x 341: 28.9 against
-// 38.8; 16 of 441 x 441, 3.1 million: 52.8 against 52.2).
+// the tiles no longer fit one round.  The strip kernels take 24.5 us a step for
+// both sweeps of a gradient while the launch is what bounds them and about 14.5
+// + 9.8 per million nodes (all shots) beyond, a forward sweep by itself 13.5 and
+// 9.2 + 3.3.  So the tiles win up to about two million nodes, and for a forward
+// sweep up to three and a half (us a step, tiles and strips; gradient: 3 shots
+// of 156 x 327 7.4 and 23.1; 12 of 281 x 281 19.4 and 26.5; 12 of 253 x 419 22.0
+// and 30.1; 7 of 537 x 599, 2.3 million, 40.1 and 35.0; 13 of 413 x 531, 2.9
+// million, 46.5 and 42.8; forward: 8.0 and 14.2 for the second, 14.9 and 15.8 for
+// the fourth, 17.2 and 17.5 for the fifth).
 //
 // A plan that sets any part of the decomposition keeps the strip kernels.
 fwi_plan::Tiles choose_tiles(const fwi_plan *p, const fwi_exec &ex)
@@ -1105,7 +1109,8 @@ fwi_plan::Tiles choose_tiles(const fwi_plan *p, const fwi_exec &ex)
         ex.adj_two_step_lane_cols || g.Nz > 32767 || g.Nx > 32767)
         return t;
     const double nodes = (double)g.N * p->S;
-    const double strips = std::max(24.5, 20.5 + 9.3e-6 * nodes);
+    const double strips = std::max(24.5, 14.5 + 9.8e-6 * nodes);
+    const double strips_f = std::max(13.5, 9.2 + 3.3e-6 * nodes);
     if (nodes > 4e6)
         return t;
     double best[2] = {1e30, 1e30};
@@ -1131,6 +1136,7 @@ fwi_plan::Tiles choose_tiles(const fwi_plan *p, const fwi_exec &ex)
         }
     }
     t.on = best[0] + best[1] < strips;
+    t.fwd = t.on || best[0] < strips_f;
     // levels that a forward call buffers for sampling: about 64 MB, whole
     // launches
     const double level = (double)p->S * (double)align64(g.N) * sizeof(float);
@@ -1854,7 +1860,7 @@ fwi_status fwi_forward(fwi_plan *p, int32_t param, const float *m1, const float 
     if (p->mode == FWI_EXEC_PLAIN) {
         for (int s = 0; s < p->S; ++s)
             sweep_forward(c, s, 1, false, traces + s * per_shot);
-    } else if (p->tile.on) {
+    } else if (p->tile.fwd) {
         tile_forward(c, false, traces);
     } else {
         sweep_forward(c, 0, p->Spad, false, traces);
