@@ -1348,25 +1348,31 @@ fwi_status fwi_plan_create(const fwi_grid *grid, const fwi_acq *acq, const fwi_e
         // Shots per wave and band height of the two-step adjoint: a row of a
         // workgroup takes kRowUs[n - 1] us where a compute unit runs n
         // workgroups at once (measured on MI355X at one column per lane;
-        // wider lanes are taken in proportion), a band H + 10 rows (its halo
-        // and the start of its windows), and taller bands lose some of the
-        // cache lines that the groups of a band share.  With more shots a wave
-        // moves fewer bytes (the model and the partial gradient once for all)
-        // but fewer waves run.  Against the best of all heights measured, the
-        // choice takes 1.02 times as long at 64 shots of 1081 x 1081 padded
-        // nodes (4 shots, 91 rows: 898 us against 1004 with 2 shots), 1.00 at
-        // 32 of 2081 x 2081 (4, 49: 1537 against 1749), 1.00 at 40 of 481 x
-        // 481 (2, 49: 155; 171 with 1, 177 with 4) and 1.00 at 13 of 413 x 531
-        // (1, 20: 57; 67 with 2).  Shots that only fill up a group cost the
-        // forward sweeps too.
+        // wider lanes are taken in proportion); with more workgroups than run
+        // at once their rounds overlap, kRound of the time that they would take
+        // one after the other, and the last ends kTail late.  A band takes H +
+        // 6 rows (its halo), and taller bands lose some of the cache lines that
+        // the groups of a band share.  With more shots a wave moves fewer bytes
+        // (the model and the partial gradient once for all) but fewer waves
+        // run.  Over twelve sizes of 413 x 531 to 2081 x 2081 padded nodes with
+        // 12 to 64 shots, against the best of all heights and groups measured,
+        // the choice takes 1.02 times as long on average and 1.11 at most (with
+        // the rounds one after the other 1.07 and 1.25): 64 shots of 1081 x
+        // 1081 (4 shots a wave, 47 rows) 902 us, best 897; 32 of 2081 x 2081
+        // (4, 64) 1585, best 1553; 40 of 481 x 481 (2, 20) 167, the best (172
+        // with 1, 185 with 4); 13 of 413 x 531 (1, 20) 57, the best (67 with 2).
+        // Shots that only fill up a group cost the forward sweeps too.
         auto adj_cost = [&](int sg, int cl, int H) {
-            static const double kRowUs[3][4] = {{1.2, 1.55, 1.9, 2.6}, {2.1, 2.55, 3.4, 0}, {3.6, 4.4, 0, 0}};
+            static const double kRowUs[3][4] = {
+                {1.2, 1.55, 2.1, 2.7}, {2.1, 2.55, 3.4, 0}, {3.6, 4.7, 0, 0}};
+            static const double kRound[3] = {0.95, 0.95, 0.85}, kTail = 0.3;
             const int i = sg == 1 ? 0 : sg == 2 ? 1 : 2, most = sg == 1 ? 4 : sg == 2 ? 3 : 2;
             const long long b = (sweep_of(g, p->S, H, sg, cl, 2).nwaves + 1023) / 1024;
-            const double us = (double)(b / most) * kRowUs[i][most - 1] +
-                              (b % most ? kRowUs[i][b % most - 1] : 0.0);
+            const double us = b <= most ? kRowUs[i][std::max(b, 1LL) - 1]
+                                        : kRowUs[i][most - 1] *
+                                              (kRound[i] * (double)b / most + kTail);
             const double pad = (double)((p->S + sg - 1) / sg * sg) / p->S;
-            return us * cl * (H + 10) * (1.0 + H / 800.0) * (1.0 + 1.2 * (pad - 1.0));
+            return us * cl * (H + 6) * (1.0 + H / 1600.0) * (1.0 + 1.5 * (pad - 1.0));
         };
         static const int kRowsAdj2[] = {12, 16, 20, 24, 32, 48, 64, 96, 128, 160, 192};
         auto adj_rows = [&](int sg, int cl, double &cost) {
