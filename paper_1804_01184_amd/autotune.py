@@ -30,7 +30,8 @@ from .api import Grid, Plan
 # much as the height), then coarser steps.  Each is lowered to the smallest
 # height with the same number of bands (see balanced_rows).
 ROWS = (8, 9, 10, 11, 12, 13, 14, 15, 16, 20, 24, 32, 48, 64, 96, 128)
-ROWS2 = (12, 14, 16, 18, 20, 24, 28, 32, 48, 64, 96)
+ROWS2 = (12, 14, 16, 18, 20, 22, 24, 26, 28, 30, 32, 34, 36, 40, 44, 48, 52, 56, 60, 64, 68, 72,
+         76, 80, 88, 96)
 ROWSA = (12, 16, 20, 24, 32, 48, 64, 96, 128, 160, 192, 256)
 # supported (shots per group, columns per lane) pairs of the one-step
 # kernels and of the two-step forward kernel

@@ -1349,30 +1349,29 @@ fwi_status fwi_plan_create(const fwi_grid *grid, const fwi_acq *acq, const fwi_e
         // workgroup takes kRowUs[n - 1] us where a compute unit runs n
         // workgroups at once (measured on MI355X at one column per lane;
         // wider lanes are taken in proportion); with more workgroups than run
-        // at once their rounds overlap, kRound of the time that they would take
-        // one after the other, and the last ends kTail late.  A band takes H +
-        // 6 rows (its halo), and taller bands lose some of the cache lines that
-        // the groups of a band share.  With more shots a wave moves fewer bytes
-        // (the model and the partial gradient once for all) but fewer waves
-        // run.  Over twelve sizes of 413 x 531 to 2081 x 2081 padded nodes with
-        // 12 to 64 shots, against the best of all heights and groups measured,
-        // the choice takes 1.02 times as long on average and 1.11 at most (with
-        // the rounds one after the other 1.07 and 1.25): 64 shots of 1081 x
-        // 1081 (4 shots a wave, 47 rows) 902 us, best 897; 32 of 2081 x 2081
-        // (4, 64) 1585, best 1553; 40 of 481 x 481 (2, 20) 167, the best (172
-        // with 1, 185 with 4); 13 of 413 x 531 (1, 20) 57, the best (67 with 2).
-        // Shots that only fill up a group cost the forward sweeps too.
+        // at once their rounds overlap, and each full round takes kRoundUs.  A
+        // band takes kStart rows more (its halo and the start of its windows),
+        // and taller bands lose some of the cache lines that the groups of a
+        // band share.  With more shots a wave moves fewer bytes (the model and
+        // the partial gradient once for all) but fewer waves run.  Over thirty
+        // sizes of 121 x 585 to 2081 x 2081 padded nodes with 3 to 64 shots,
+        // against the best of all heights and groups measured, the choice takes
+        // 1.002 times as long on average and 1.03 at most (with the rounds one
+        // after the other 1.04 and 1.21): 64 shots of 1081 x 1081 (4 shots a
+        // wave, 91 rows) 897 us, 2 shots 1005; 32 of 2081 x 2081 (4, 64) 1585,
+        // best 1553, 2 shots 1748; 40 of 481 x 481 (2, 20) 167, 1 shot 172, 4
+        // shots 185; 13 of 413 x 531 (1, 20) 57, 2 shots 67.  Shots that only
+        // fill up a group cost the forward sweeps too.
         auto adj_cost = [&](int sg, int cl, int H) {
             static const double kRowUs[3][4] = {
-                {1.2, 1.55, 2.1, 2.7}, {2.1, 2.55, 3.4, 0}, {3.6, 4.7, 0, 0}};
-            static const double kRound[3] = {0.95, 0.95, 0.85}, kTail = 0.3;
+                {1.14, 1.49, 1.94, 2.36}, {2.1, 2.4, 3.08, 0}, {3.14, 3.76, 0, 0}};
+            static const double kRoundUs[3] = {2.68, 3.18, 3.8}, kStart[3] = {10.4, 9.5, 9.9};
             const int i = sg == 1 ? 0 : sg == 2 ? 1 : 2, most = sg == 1 ? 4 : sg == 2 ? 3 : 2;
-            const long long b = (sweep_of(g, p->S, H, sg, cl, 2).nwaves + 1023) / 1024;
-            const double us = b <= most ? kRowUs[i][std::max(b, 1LL) - 1]
-                                        : kRowUs[i][most - 1] *
-                                              (kRound[i] * (double)b / most + kTail);
+            const long long b =
+                std::max(1LL, (sweep_of(g, p->S, H, sg, cl, 2).nwaves + 1023LL) / 1024);
+            const double us = b <= most ? kRowUs[i][b - 1] : kRoundUs[i] * (double)b / most;
             const double pad = (double)((p->S + sg - 1) / sg * sg) / p->S;
-            return us * cl * (H + 6) * (1.0 + H / 1600.0) * (1.0 + 1.5 * (pad - 1.0));
+            return us * cl * (H + kStart[i]) * (1.0 + H / 590.0) * (1.0 + 0.87 * (pad - 1.0));
         };
         static const int kRowsAdj2[] = {12, 16, 20, 24, 32, 48, 64, 96, 128, 160, 192};
         auto adj_rows = [&](int sg, int cl, double &cost) {
@@ -1389,7 +1388,8 @@ fwi_status fwi_plan_create(const fwi_grid *grid, const fwi_acq *acq, const fwi_e
             }
             return best;
         };
-        static const int kRowsFwd2[] = {12, 14, 16, 18, 20, 24, 28, 32, 48, 64, 96};
+        static const int kRowsFwd2[] = {12, 14, 16, 18, 20, 22, 24, 26, 28, 30, 32, 34, 36,
+                                        40, 44, 48, 52, 56, 60, 64, 68, 72, 76, 80, 88, 96};
         // the batched kernels address a shot group's records, the model and
         // a partial gradient with 32-bit byte offsets below 2^31
         const long long lim = (1LL << 31) - 64LL * Nx;
