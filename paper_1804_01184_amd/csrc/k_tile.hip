@@ -21,7 +21,11 @@
 // memory, where their smaller traffic counts.
 //
 // Every update is written with the strip kernels' expressions, so the
-// wavefields agree with theirs bit for bit.
+// wavefields agree with theirs bit for bit.  (1 / h stays out of the stored
+// coefficients for the same reason: beta K / h, rounded, is another medium than
+// the forward sweep's beta K, alike at every node of a homogeneous model, and
+// the phase error grows with the steps.  Against FP64, 8 shots of 201 x 201,
+// 1000 steps, the gradient was off by up to 7.5e-7 with it, 4.3e-7 without.)
 #include "wave_dev.h"
 
 #include <hip/hip_ext.h>
@@ -400,8 +404,8 @@ __global__ void __launch_bounds__(NW * WAVE)
         ahz[r] = zt[2 * ZP + i];
         bhz[r] = zt[3 * ZP + i];
     }
-    // coefficients as the products the step uses: beta_x K / dx, beta_z K / dz,
-    // beta_h bx / dx, beta_h bz / dz (formed once every load is under way)
+    // coefficients as the products the step uses: beta_x K, beta_z K, beta_h bx,
+    // beta_h bz (formed once every load is under way)
     const int s = id.s;
     const Base bIn = base_of(a.in, s), bOut = base_of(a.out, s);
     const rsrc_t rIn = res(bIn.p, bIn.bytes), rOut = res(bOut.p, bOut.bytes);
@@ -425,20 +429,15 @@ __global__ void __launch_bounds__(NW * WAVE)
                 MZ[r][c] = bld(rIn, pick(z.full, w.zf[c], w.zs[c]), z.base + 3u * FB);
         }
     }
-    float hx[C], hz[RW];   // -beta_h / dx, -beta_h / dz
-#pragma unroll
-    for (int c = 0; c < C; ++c)
-        hx[c] = -bhx[c] * g.rdx;
 #pragma unroll
     for (int r = 0; r < RW; ++r) {
         const bool rp = row_pml(g, w.row0 + r);
-        hz[r] = -bhz[r] * g.rdz;
 #pragma unroll
         for (int c = 0; c < C; ++c) {
-            BX[r][c] = bhx[c] * BX[r][c] * g.rdx;
-            BZ[r][c] = bhz[r] * BZ[r][c] * g.rdz;
-            KZ[r][c] = btz[r] * KX[r][c] * g.rdz;
-            KX[r][c] = btx[c] * KX[r][c] * g.rdx;
+            BX[r][c] = bhx[c] * BX[r][c];
+            BZ[r][c] = bhz[r] * BZ[r][c];
+            KZ[r][c] = btz[r] * KX[r][c];
+            KX[r][c] = btx[c] * KX[r][c];
             MZ[r][c] = w.row0 + r < g.Nz && (rp || w.pml[c]) ? MZ[r][c] : MU[r][c];
             gK[r][c] = gX[r][c] = gZ[r][c] = 0.f;
         }
@@ -468,7 +467,7 @@ __global__ void __launch_bounds__(NW * WAVE)
             const int i = w.row0 + r - 1;
             tile_load<C>(bH, w, row_ok(g, i), rowb(g, i), PN[r]);
         }
-        // q = beta_z K mu_z / dz, rows -1 .. RW+1
+        // q = beta_z K mu_z, rows -1 .. RW+1
         float q[RW + 3][C];
 #pragma unroll
         for (int r = 0; r < RW; ++r)
@@ -483,7 +482,7 @@ __global__ void __launch_bounds__(NW * WAVE)
         edge_get<C, NW>(eq, w.wv - 1, 2, w.lane, q[0]);
         edge_get<C, NW>(eq, w.wv + 1, 0, w.lane, q[RW + 1]);
         edge_get<C, NW>(eq, w.wv + 1, 1, w.lane, q[RW + 2]);
-        // lvz_mid at rows i + 1/2, and beta_h bz lvz_mid / dz rows -2 .. RW
+        // lvz_mid at rows i + 1/2, and beta_h bz lvz_mid rows -2 .. RW
         float WZ[RW + 3][C];
 #pragma unroll
         for (int r = 0; r < RW; ++r) {
@@ -491,7 +490,7 @@ __global__ void __launch_bounds__(NW * WAVE)
 #pragma unroll
             for (int c = 0; c < C; ++c) {
                 const float l = LZ[r][c] + (kC1 * (q[r + 2][c] - q[r + 1][c]) +
-                                            kC2 * (q[r + 3][c] - q[r][c]));
+                                            kC2 * (q[r + 3][c] - q[r][c])) * g.rdz;
                 LZ[r][c] = ok ? l : 0.f;
                 WZ[r + 2][c] = BZ[r][c] * LZ[r][c];
             }
@@ -511,11 +510,11 @@ __global__ void __launch_bounds__(NW * WAVE)
             dfwd<C>(PN[r + 1], dpx);
 #pragma unroll
             for (int c = 0; c < C; ++c) {
-                const float l = LX[r][c] + dqx[c];
+                const float l = LX[r][c] + dqx[c] * g.rdx;
                 LX[r][c] = w.ok[c] ? l : 0.f;
-                gX[r][c] += LX[r][c] * (hx[c] * dpx[c]);
-                gZ[r][c] += LZ[r][c] * (hz[r] * (kC1 * (PN[r + 2][c] - PN[r + 1][c]) +
-                                                 kC2 * (PN[r + 3][c] - PN[r][c])));
+                gX[r][c] += LX[r][c] * (-bhx[c] * dpx[c] * g.rdx);
+                gZ[r][c] += LZ[r][c] * (-bhz[r] * (kC1 * (PN[r + 2][c] - PN[r + 1][c]) +
+                                                   kC2 * (PN[r + 3][c] - PN[r][c])) * g.rdz);
                 wx[c] = BX[r][c] * LX[r][c];
             }
             dbwd<C>(wx, dwx[r]);
@@ -540,7 +539,7 @@ __global__ void __launch_bounds__(NW * WAVE)
 #pragma unroll
             for (int c = 0; c < C; ++c) {
                 const float dwz = kC1 * (WZ[r + 2][c] - WZ[r + 1][c]) + kC2 * (WZ[r + 3][c] - WZ[r][c]);
-                const float t = dwx[r][c] + dwz;
+                const float t = dwx[r][c] * g.rdx + dwz * g.rdz;
                 gK[r][c] += PN[r + 1][c] * (t + v[c]);
                 MU[r][c] = ax[c] * MU[r][c] + t;
                 MU[r][c] += v[c];
