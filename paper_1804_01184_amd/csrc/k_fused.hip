@@ -781,7 +781,7 @@ __global__ void __launch_bounds__(NTHR)
 //   gbx += lvx_mid * (-bhx Dx+ p^m),  gbz likewise
 //   t = D-(beta_h b lv_mid);  mu_p' = alpha mu_p + t + R^T r^{m-1};
 //   lv' = alpha_h lv_mid                                  (T1^T)
-//   gK  += p^m (t + R^T r^{m-1}) / K
+//   gK  += p^m (mu_px' - alpha_x mu_px) / K
 // The bulk-modulus sensitivity of the discrete scheme is the sum over steps of
 // mu_x (px^{m+1} - alpha_x px^m) + mu_z (pz^{m+1} - alpha_z pz^m).  Collecting
 // the terms of each level (summation by parts in time; the field is zero before
@@ -789,7 +789,12 @@ __global__ void __launch_bounds__(NTHR)
 // mu_x and pz^m meets mu_z' - alpha_z mu_z, which are the same t + R^T r^{m-1}.
 // So a step needs the pressure of one level and no split.  At smooth-1001 (64
 // shots of 1081 x 1081) that took two of five pressure reads and four of six
-// split reads per shot and row out of the two-step kernel.
+// split reads per shot and row out of the two-step kernel.  The difference is
+// taken of the stored values: with t + R^T r^{m-1} the sum misses the rounding of
+// mu'.  Error of the K gradient against FP64, over 60 problems of 10 000 to 3
+// million nodes, as a multiple of that of the direct sum: 0.996 on average and 1.39
+// at most with the difference, 1.018 and 1.28 with t (single shots are the worst:
+// the running sum carries the boundary term p^m mu of the parts).
 // Outside the layer the split forms reduce to the unsplit ones (alpha = 1,
 // pz = 0).
 
@@ -797,14 +802,12 @@ __global__ void __launch_bounds__(NTHR)
 // Ring slots S0 .. S3 of MU, MZ, PN hold rows i .. i+3 of mu_px, mu_pz and
 // p^m, bK rows i .. i+3 of beta_z K, and WZ rows i-2 .. i+1 of
 // beta_h bz lvz_mid (slot S3 receives row i+1 here).  Adds the shot's buoyancy
-// sensitivities (gbx at row i, gbz at row i+1) to accX, accZ, and returns t of
-// row i and the new adjoint state of row i without R^T r^{m-1} (lvz of row
-// i+1).  Both adjoint kernels call it, so one step rounds the same way in
+// sensitivities (gbx at row i, gbz at row i+1) to accX, accZ, and returns the
+// new adjoint state of row i without R^T r^{m-1} (lvz of row i+1).  Both adjoint kernels call it, so one step rounds the same way in
 // either.
 template <int C>
 struct AdjOut {
     float opx[C], opz[C], ovx[C], ovz[C];   // mu_px, mu_pz, lvx at row i; lvz at row i+1
-    float t[C];
 };
 
 template <int C, int S0, int S1, int S2, int S3>
@@ -816,7 +819,7 @@ __device__ inline void adj_shot(const Geo &g, const XTab<C> &xt, const WaveGeo<C
                                 const float (&bx)[C], const float (&bz1)[C], float (&accX)[C],
                                 float (&accZ)[C], AdjOut<C> &o)
 {
-    float lvzm[C], qx[C], dqx[C], dpx[C], lvxm[C], wx[C], dwx[C];
+    float lvzm[C], qx[C], dqx[C], dpx[C], lvxm[C], wx[C], dwx[C], t[C];
 #pragma unroll
     for (int c = 0; c < C; ++c) {
         // lvz_mid at row (i+1): D+z of beta_z K mu_pz
@@ -841,12 +844,12 @@ __device__ inline void adj_shot(const Geo &g, const XTab<C> &xt, const WaveGeo<C
 #pragma unroll
     for (int c = 0; c < C; ++c) {
         const float dwz = kC1 * (WZ[S2][c] - WZ[S1][c]) + kC2 * (WZ[S3][c] - WZ[S0][c]);
-        o.t[c] = dwx[c] * g.rdx + dwz * g.rdz;
+        t[c] = dwx[c] * g.rdx + dwz * g.rdz;
     }
 #pragma unroll
     for (int c = 0; c < C; ++c) {
-        o.opx[c] = xt.ax[c] * MU[S0][c] + o.t[c];
-        o.opz[c] = az * MZ[S0][c] + o.t[c];
+        o.opx[c] = xt.ax[c] * MU[S0][c] + t[c];
+        o.opz[c] = az * MZ[S0][c] + t[c];
         o.ovx[c] = xt.ahx[c] * lvxm[c];
         o.ovz[c] = ahz1 * lvzm[c];
     }
@@ -854,10 +857,10 @@ __device__ inline void adj_shot(const Geo &g, const XTab<C> &xt, const WaveGeo<C
 
 // R^T r of a step at the receiver nodes of one row that lie in the wave's
 // window (ie: the packed range of AdjNodes, counted from node nbase), added to
-// the row's new adjoint pressure and to t.
+// the row's new adjoint pressure.
 template <int C>
 __device__ inline void add_nodes(const AdjNodes &nd, const float *val, NodeLanes &nl, int nbase,
-                                 unsigned ie, int lane, int j0, float (&mu)[C], float (&t)[C])
+                                 unsigned ie, int lane, int j0, float (&mu)[C])
 {
     const int first = nbase + (int)(ie >> 9), last = first + (int)(ie & 511u);
     for (int e = first; e < last; ++e) {
@@ -867,10 +870,8 @@ __device__ inline void add_nodes(const AdjNodes &nd, const float *val, NodeLanes
         const float v = nl.val_at(e);
 #pragma unroll
         for (int c = 0; c < C; ++c)
-            if (j0 + c == j) {
+            if (j0 + c == j)
                 mu[c] += v;
-                t[c] += v;
-            }
     }
 }
 
@@ -1135,10 +1136,10 @@ __global__ void __launch_bounds__(NTHR)
                                         PN[k], WZ[k], b.lvz1[k], b.lvx[k], b.bx, b.bz1, accX,
                                         accZ, o);
             if (b.inj[k] != 0u)
-                add_nodes<C>(a.nd, a.injv, nl[k], nbase[k], b.inj[k], w.lane, w.j0, o.opx, o.t);
+                add_nodes<C>(a.nd, a.injv, nl[k], nbase[k], b.inj[k], w.lane, w.j0, o.opx);
 #pragma unroll
             for (int c = 0; c < C; ++c)
-                numK[c] += PN[k][S0][c] * o.t[c];
+                numK[c] += PN[k][S0][c] * fmaf(-xt.ax[c], MU[k][S0][c], o.opx[c]);
             const unsigned ko = skoff(a.lout, k);
             vst_row<C>(rLout, w, true, rb + 2u * FB + ko, o.opx);
 #pragma unroll
@@ -1511,10 +1512,10 @@ __global__ void __launch_bounds__(NTHR) __attribute__((amdgpu_waves_per_eu(C > 1
                 mA[c] = okt && w.colok[c] ? oA.opx[c] : 0.f;
             const unsigned ieA = rl.node(k, t);
             if (ieA != 0u)
-                add_nodes<C>(a.nd, a.injA, nlA[k], nbase[k], ieA, w.lane, w.j0, mA, oA.t);
+                add_nodes<C>(a.nd, a.injA, nlA[k], nbase[k], ieA, w.lane, w.j0, mA);
 #pragma unroll
             for (int c = 0; c < C; ++c) {
-                numA[c] += PNA[k][S0][c] * oA.t[c];
+                numA[c] += PNA[k][S0][c] * fmaf(-xt.ax[c], MUA[k][S0][c], mA[c]);
                 const bool in = okt && w.colok[c];
                 MUB[k][S3][c] = mA[c];
                 MZB[k][S3][c] = rpt || w.colpml[c] ? (in ? oA.opz[c] : 0.f) : mA[c];
@@ -1527,11 +1528,10 @@ __global__ void __launch_bounds__(NTHR) __attribute__((amdgpu_waves_per_eu(C > 1
                                             dly[RX + k], dly[RBX], dly[RBZ], axB, azB_, oB);
                 const unsigned ieB = own && a.injB ? rl.node(k, r) : 0u;
                 if (ieB != 0u)
-                    add_nodes<C>(a.nd, a.injB, nlB[k], nbase[k], ieB, w.lane, w.j0, oB.opx,
-                                 oB.t);
+                    add_nodes<C>(a.nd, a.injB, nlB[k], nbase[k], ieB, w.lane, w.j0, oB.opx);
 #pragma unroll
                 for (int c = 0; c < C; ++c)
-                    numB[c] += PMB[k][S0][c] * oB.t[c];
+                    numB[c] += PMB[k][S0][c] * fmaf(-xt.ax[c], MUB[k][S0][c], oB.opx[c]);
                 const unsigned ko = skoff(a.lout, k);
                 vst_row<C>(rLout, w, own, rbB + 2u * FB + ko, oB.opx);
 #pragma unroll

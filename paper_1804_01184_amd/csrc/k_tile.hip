@@ -358,12 +358,13 @@ __global__ void __launch_bounds__(NW * WAVE) __attribute__((amdgpu_waves_per_eu(
 // R^T r^m already added (zero before the first step, m = nt).  Step m:
 //   lv_mid = lv + D+(beta K mu),  gb += lv_mid (-beta_h D+ p^m)
 //   t = D-(beta_h b lv_mid),  mu' = alpha mu + t + R^T r^{m-1}
-//   gK += p^m (t + R^T r^{m-1}) / K,  lv' = alpha_h lv_mid
+//   gK += p^m (mu_x' - alpha_x mu_x) / K,  lv' = alpha_h lv_mid
 // The bulk-modulus sensitivity is the sum over steps of mu_x (px^{m+1} -
 // alpha_x px^m) + mu_z (pz^{m+1} - alpha_z pz^m) with the terms of each level
 // collected (summation by parts in time): px^m meets mu_x' - alpha_x mu_x and
 // pz^m the same of mu_z, and both differences are t + R^T r^{m-1}.  So one
-// pressure level a step is enough, without its split.
+// pressure level a step is enough, without its split.  The difference is taken
+// of the stored values, rounding included, as in the strip kernels.
 
 template <int C, int RW, int NW>
 __global__ void __launch_bounds__(NW * WAVE)
@@ -540,9 +541,10 @@ __global__ void __launch_bounds__(NW * WAVE)
             for (int c = 0; c < C; ++c) {
                 const float dwz = kC1 * (WZ[r + 2][c] - WZ[r + 1][c]) + kC2 * (WZ[r + 3][c] - WZ[r][c]);
                 const float t = dwx[r][c] * g.rdx + dwz * g.rdz;
-                gK[r][c] += PN[r + 1][c] * (t + v[c]);
-                MU[r][c] = ax[c] * MU[r][c] + t;
+                const float mu = MU[r][c];
+                MU[r][c] = ax[c] * mu + t;
                 MU[r][c] += v[c];
+                gK[r][c] += PN[r + 1][c] * fmaf(-ax[c], mu, MU[r][c]);
                 MZ[r][c] = az[r] * MZ[r][c] + t;
                 MZ[r][c] += v[c];
                 LX[r][c] = ahx[c] * LX[r][c];
