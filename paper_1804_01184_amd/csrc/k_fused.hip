@@ -439,10 +439,8 @@ struct RowLanes {
 };
 
 // A run of 64 receiver nodes of one shot and strip, one a lane: their grid
-// columns and, in the adjoint, a value each.  A strip's nodes lie in row order,
-// so a wave marching down its band reads a run every 64 nodes; walking them
-// with scalar loads, one or two memory round trips a node, set the length of
-// the waves that hold receivers.
+// columns and a value each.  A strip's nodes lie in row order, so a wave marching
+// down its band reads a run every 64 nodes.
 struct NodeLanes {
     int base = 0, end = 0;   // node indices [base, end) held
     int col;
@@ -452,14 +450,8 @@ struct NodeLanes {
         base = first;
         end = first + WAVE;
         col = cols[first + lane];
-        val = vals ? vals[first + lane] : 0.f;
+        val = vals[first + lane];
         asm volatile("" ::"v"(col), "v"(val));   // (wait here, as RowLanes::load)
-    }
-    __device__ int col_at(int e) const { return __builtin_amdgcn_readlane(col, e - base); }
-    __device__ float val_at(int e) const
-    {
-        return __builtin_bit_cast(
-            float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, val), e - base));
     }
 };
 
@@ -857,21 +849,31 @@ __device__ inline void adj_shot(const Geo &g, const XTab<C> &xt, const WaveGeo<C
 
 // R^T r of a step at the receiver nodes of one row that lie in the wave's
 // window (ie: the packed range of AdjNodes, counted from node nbase), added to
-// the row's new adjoint pressure.
+// the row's new adjoint pressure.  The lanes holding the row's nodes push them
+// to the lanes holding their columns, all at once; the others push 0 to lane 0,
+// a halo lane that no result depends on.  (Taken one by one with v_readlane they
+// set the length of the waves that hold receivers: us a pair of steps, before and
+// after, 63 shots of 511 x 189 with 349 receivers 135 and 103, 40 of 367 x 250 with
+// 289 93 and 71, 40 of 481 x 481 with 360 166 and 158.)
 template <int C>
 __device__ inline void add_nodes(const AdjNodes &nd, const float *val, NodeLanes &nl, int nbase,
-                                 unsigned ie, int lane, int j0, float (&mu)[C])
+                                 unsigned ie, int lane, int col0, float (&mu)[C])
 {
-    const int first = nbase + (int)(ie >> 9), last = first + (int)(ie & 511u);
-    for (int e = first; e < last; ++e) {
+    const int last = nbase + (int)(ie >> 9) + (int)(ie & 511u);
+    for (int e = nbase + (int)(ie >> 9); e < last;) {
         if (e < nl.base || e >= nl.end)
             nl.load(nd.col, val, e, lane);
-        const int j = nl.col_at(e);
-        const float v = nl.val_at(e);
+        const int n = imin(last, nl.end) - e;
+        const bool in = (unsigned)(lane - (e - nl.base)) < (unsigned)n;
+        const int j = nl.col - col0;
 #pragma unroll
-        for (int c = 0; c < C; ++c)
-            if (j0 + c == j)
-                mu[c] += v;
+        for (int c = 0; c < C; ++c) {
+            const bool on = in && (C == 1 || j % C == c);
+            mu[c] += __builtin_bit_cast(
+                float, __builtin_amdgcn_ds_permute(on ? j / C * 4 : 0,
+                                                   on ? __builtin_bit_cast(int, nl.val) : 0));
+        }
+        e += n;
     }
 }
 
@@ -1136,7 +1138,7 @@ __global__ void __launch_bounds__(NTHR)
                                         PN[k], WZ[k], b.lvz1[k], b.lvx[k], b.bx, b.bz1, accX,
                                         accZ, o);
             if (b.inj[k] != 0u)
-                add_nodes<C>(a.nd, a.injv, nl[k], nbase[k], b.inj[k], w.lane, w.j0, o.opx);
+                add_nodes<C>(a.nd, a.injv, nl[k], nbase[k], b.inj[k], w.lane, w.j0 - w.lane * C, o.opx);
 #pragma unroll
             for (int c = 0; c < C; ++c)
                 numK[c] += PN[k][S0][c] * fmaf(-xt.ax[c], MU[k][S0][c], o.opx[c]);
@@ -1512,7 +1514,7 @@ __global__ void __launch_bounds__(NTHR) __attribute__((amdgpu_waves_per_eu(C > 1
                 mA[c] = okt && w.colok[c] ? oA.opx[c] : 0.f;
             const unsigned ieA = rl.node(k, t);
             if (ieA != 0u)
-                add_nodes<C>(a.nd, a.injA, nlA[k], nbase[k], ieA, w.lane, w.j0, mA);
+                add_nodes<C>(a.nd, a.injA, nlA[k], nbase[k], ieA, w.lane, w.j0 - w.lane * C, mA);
 #pragma unroll
             for (int c = 0; c < C; ++c) {
                 numA[c] += PNA[k][S0][c] * fmaf(-xt.ax[c], MUA[k][S0][c], mA[c]);
@@ -1528,7 +1530,7 @@ __global__ void __launch_bounds__(NTHR) __attribute__((amdgpu_waves_per_eu(C > 1
                                             dly[RX + k], dly[RBX], dly[RBZ], axB, azB_, oB);
                 const unsigned ieB = own && a.injB ? rl.node(k, r) : 0u;
                 if (ieB != 0u)
-                    add_nodes<C>(a.nd, a.injB, nlB[k], nbase[k], ieB, w.lane, w.j0, oB.opx);
+                    add_nodes<C>(a.nd, a.injB, nlB[k], nbase[k], ieB, w.lane, w.j0 - w.lane * C, oB.opx);
 #pragma unroll
                 for (int c = 0; c < C; ++c)
                     numB[c] += PMB[k][S0][c] * fmaf(-xt.ax[c], MUB[k][S0][c], oB.opx[c]);
