@@ -66,14 +66,16 @@ struct fwi_plan {
     Sweep sweep_a2;          // its decomposition, with shot groups of its own
     int adj_list = 0;        // listed nodes of the strip adjoints (0: they do not add R^T r)
     int samp_list = 0;       // listed nodes of the two-step forward kernel
-    // tile kernels (several steps per launch, state in registers): shapes,
-    // steps per launch and axes of the forward and adjoint tiles, shots per
-    // partial gradient, levels of the forward call's sampling buffer
+    // tile kernels (several steps per launch, state in registers)
+    struct TileRun {   // most steps per launch and the axes of its tiles
+        int T = 0;
+        TileAxis x{}, z{};
+    };
     struct Tiles {
         bool on = false;    // the sweeps of a gradient
         bool fwd = false;   // a forward sweep by itself
-        int fT = 0, aT = 0, levels = 0;
-        TileAxis fx{}, fz{}, ax{}, az{};
+        TileRun call, keep, adj;   // forward call; forward and adjoint sweeps of a gradient
+        int levels = 0;            // of the forward call's sampling buffer
     } tile;
     int device;
     Geo geo;
@@ -732,13 +734,13 @@ Recd tile_rec(const fwi_plan *p, float *base)
 // Forward steps n0 .. n1-1 of every shot from the state record batch `cur`;
 // p^{n0+1} .. p^{n1} go to hist (unless null).  The last state is written to
 // `last`, or to a work buffer if that is null; returns where it is.
-float *tile_steps_fwd(const Ctx &c, float *cur, int n0, int n1, float *hist, long long lvl,
-                      long long ss, float *last)
+float *tile_steps_fwd(const Ctx &c, const fwi_plan::TileRun &run, float *cur, int n0, int n1,
+                      float *hist, long long lvl, long long ss, float *last)
 {
     const fwi_plan *p = c.pl;
     float *w0 = c.f(c.L.work[0]), *w1 = c.f(c.L.work[1]);
     for (int n = n0; n < n1;) {
-        const int t = std::min(p->tile.fT, n1 - n);
+        const int t = std::min(run.T, n1 - n);
         float *out = n + t == n1 && last ? last : (cur == w0 ? w1 : w0);
         FwdTile a;
         a.in = tile_rec(p, cur);
@@ -753,8 +755,8 @@ float *tile_steps_fwd(const Ctx &c, float *cur, int n0, int n1, float *hist, lon
         a.nt = p->grid.nt;
         a.T = t;
         a.S = p->S;
-        a.x = p->tile.fx;
-        a.z = p->tile.fz;
+        a.x = run.x;
+        a.z = run.z;
         Timed tm(c.pl, c.st, FWI_KC_FWD_STEP, true);
         launch_tile_fwd(p->geo, c.tb.pml, c.tb.zpad, c.m.K, a, c.st, tm.b, tm.e);
         cur = out;
@@ -779,7 +781,8 @@ void tile_forward(const Ctx &c, bool keep, float *traces)
     for (int n0 = 0; n0 < nt; n0 += run) {
         const int n1 = std::min(n0 + run, nt);
         float *ck = keep && n1 < nt ? c.f(c.L.ckpt) + (size_t)(n0 / run) * B * p->SS : nullptr;
-        cur = tile_steps_fwd(c, cur, n0, n1, traces || n1 == nt ? hist : nullptr, lvl, ss, ck);
+        cur = tile_steps_fwd(c, keep ? p->tile.keep : p->tile.call, cur, n0, n1,
+                             traces || n1 == nt ? hist : nullptr, lvl, ss, ck);
         if (traces) {
             Timed tm(c.pl, c.st, FWI_KC_SAMPLE);
             launch_sample_hist(g, hist, lvl, ss, rec_of(c, 0), p->S, traces, nt, n0, n1 - n0,
@@ -809,7 +812,7 @@ void tile_backward(const Ctx &c, const float *resid, float *gpart)
                 zero_state(c, cur, B);
             else
                 cur = c.f(c.L.ckpt) + (size_t)(sg - 1) * B * p->SS;
-            tile_steps_fwd(c, cur, n0, n1, store + lvl, lvl, p->ST, nullptr);
+            tile_steps_fwd(c, p->tile.keep, cur, n0, n1, store + lvl, lvl, p->ST, nullptr);
         }
         // adjoint steps m = n1 .. n0+1; step m takes p^m and adds R^T r^{m-1}
         for (int m = n1; m > n0;) {
@@ -820,7 +823,7 @@ void tile_backward(const Ctx &c, const float *resid, float *gpart)
                                     c.st);
             }
             for (int j = 0; j < cnt;) {
-                const int t = std::min(p->tile.aT, cnt - j);
+                const int t = std::min(p->tile.adj.T, cnt - j);
                 AdjTile a;
                 a.in = tile_rec(p, lam[li]);
                 a.out = tile_rec(p, lam[li ^ 1]);
@@ -834,8 +837,8 @@ void tile_backward(const Ctx &c, const float *resid, float *gpart)
                 a.gpart = gpart;
                 a.T = t;
                 a.S = p->S;
-                a.x = p->tile.ax;
-                a.z = p->tile.az;
+                a.x = p->tile.adj.x;
+                a.z = p->tile.adj.z;
                 Timed tm(c.pl, c.st, FWI_KC_ADJ_STEP, true);
                 launch_tile_adj(g, c.tb.pml, c.tb.zpad, c.m.K, a, c.st, tm.b, tm.e);
                 li ^= 1;
@@ -1098,6 +1101,13 @@ TileAxis tile_axis(int len, int span, int halo, int unit)
 // million, 46.5 and 42.8; forward: 8.0 and 14.2 for the second, 14.9 and 15.8 for
 // the fourth, 17.2 and 17.5 for the fifth).
 //
+// Launches end at checkpoints and after the last step, so the run between them
+// counts (and about 8 us for its sampling and staging launches, with checkpoints);
+// the strip kernels' pairs cross checkpoints in the adjoint.  Checkpoints on every
+// step, a tile launch and its overlap for one step: 8 shots of 241 x 241, 120 steps,
+// 7.8 ms, strips 4.9; 10 of 381 x 381 13.6 and 7.3, every second step 7.6 and 6.4,
+// every third 5.6 and 6.3.
+//
 // A plan that sets any part of the decomposition keeps the strip kernels.
 fwi_plan::Tiles choose_tiles(const fwi_plan *p, const fwi_exec &ex)
 {
@@ -1109,39 +1119,43 @@ fwi_plan::Tiles choose_tiles(const fwi_plan *p, const fwi_exec &ex)
         ex.adj_two_step_lane_cols || g.Nz > 32767 || g.Nx > 32767)
         return t;
     const double nodes = (double)g.N * p->S;
-    const double strips = std::max(24.5, 14.5 + 9.8e-6 * nodes);
-    const double strips_f = std::max(13.5, 9.2 + 3.3e-6 * nodes);
     if (nodes > 4e6)
         return t;
-    double best[2] = {1e30, 1e30};
-    for (int T = 2; T <= 8; ++T) {
-        const TileAxis x = tile_axis(g.Nx, kTileX, 3 * T, kTileCols);
-        const TileAxis z = tile_axis(g.Nz, kTileZ, 3 * T, 1);
-        if (!x.n || !z.n)
-            continue;
-        const long long h = ((long long)x.n * z.n * p->S + 255) / 256;
-        const double f = 6.2 + (double)(h / 2) * (11 + 1.9 * T) + (double)(h % 2) * (6.3 + 1.15 * T);
-        const double a = 5.7 + (double)h * (7.5 + 1.95 * T);
-        if (f / T < best[0]) {
-            best[0] = f / T;
-            t.fT = T;
-            t.fx = x;
-            t.fz = z;
+    // us a step of a sweep in runs of `len` steps, by launches of at most T
+    auto cost = [&](const fwi_plan::TileRun &r, bool adj, int len) {
+        const long long h = ((long long)r.x.n * r.z.n * p->S + 255) / 256;
+        auto launch = [&](int n) {
+            return adj ? 5.7 + (double)h * (7.5 + 1.95 * n)
+                       : 6.2 + (double)(h / 2) * (11 + 1.9 * n) + (double)(h % 2) * (6.3 + 1.15 * n);
+        };
+        const int full = len / r.T, rest = len % r.T;
+        return (full * launch(r.T) + (rest ? launch(rest) : 0.0)) / len;
+    };
+    auto choose = [&](bool adj, int len, fwi_plan::TileRun &best) {
+        double least = 1e30;
+        for (int T = 1; T <= std::min(8, len); ++T) {
+            const fwi_plan::TileRun r = {T, tile_axis(g.Nx, kTileX, 3 * T, kTileCols),
+                                         tile_axis(g.Nz, kTileZ, 3 * T, 1)};
+            if (!r.x.n || !r.z.n)
+                continue;
+            const double us = cost(r, adj, len);
+            if (us < least) {
+                least = us;
+                best = r;
+            }
         }
-        if (a / T < best[1]) {
-            best[1] = a / T;
-            t.aT = T;
-            t.ax = x;
-            t.az = z;
-        }
-    }
-    t.on = best[0] + best[1] < strips;
-    t.fwd = t.on || best[0] < strips_f;
+        return least;
+    };
+    const double strips_f = std::max(13.5, 9.2 + 3.3e-6 * nodes);
+    const double strips = std::max(24.5, 14.5 + 9.8e-6 * nodes) + (p->nseg > 1 ? strips_f : 0.0);
+    const double f = choose(false, p->k, t.keep), a = choose(true, std::min(p->k, kStageSteps), t.adj);
+    t.on = (p->nseg > 1 ? 2.0 * f + a + 8.0 / p->k : f + a) < strips;
+    t.fwd = choose(false, p->grid.nt, t.call) < strips_f || t.on;
     // levels that a forward call buffers for sampling: about 64 MB, whole
     // launches
     const double level = (double)p->S * (double)align64(g.N) * sizeof(float);
     const int lv = (int)std::min(64.0, std::max(8.0, 64e6 / level));
-    t.levels = std::max(t.fT, lv / std::max(t.fT, 1) * t.fT);
+    t.levels = std::max(1, lv / std::max(t.call.T, 1) * t.call.T);
     return t;
 }
 
@@ -1490,7 +1504,6 @@ fwi_status fwi_plan_create(const fwi_grid *grid, const fwi_acq *acq, const fwi_e
                         "(records of a group must stay below 2 GiB)", (long long)g.N, spg);
         }
     }
-    p->tile = choose_tiles(p, ex);
     {
         // checkpoint interval: with ckpt_every = 0 the whole pressure history
         // is kept when it fits (plain: one shot's history <= 64 GiB;
@@ -1513,6 +1526,7 @@ fwi_status fwi_plan_create(const fwi_grid *grid, const fwi_acq *acq, const fwi_e
         p->k = std::max(1, std::min(k, G.nt));
         p->nseg = (G.nt + p->k - 1) / p->k;
     }
+    p->tile = choose_tiles(p, ex);
 
     // geometry: bilinear cell and weights of every source and receiver
     const int S = p->S, nr = p->nrec;

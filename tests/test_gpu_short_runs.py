@@ -1,0 +1,39 @@
+"""Checkpoints on every step or two: a tile launch does not get to spread its
+load, store and overlap over several steps there, and the default plan is not
+slower than the strip kernels for it.  (1.15 times allows for the placement of
+the two workspaces; with the steps per launch chosen regardless of the
+checkpoints the three took 2.0, 1.26 and 1.5 times as long.)"""
+import time
+
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("nz,nx,S,nt,ckpt", [(341, 341, 10, 60, 1), (341, 341, 10, 60, 2),
+                                             (101, 101, 1, 60, 1)])
+def test_close_checkpoints_not_slower_than_strips(nz, nx, S, nt, ckpt):
+    torch = pytest.importorskip("torch")
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_1804_01184_amd import api
+    rng = np.random.default_rng(nz + ckpt)
+    h, vmax = 5.0, 2400.0
+    rec = np.stack([rng.uniform(0, (nx - 1.01) * h, 40), rng.uniform(0, (nz - 1.01) * h, 40)],
+                   axis=1)
+    src = np.stack([rng.uniform(h, (nx - 2) * h, S), rng.uniform(h, (nz - 2) * h, S)], axis=1)
+    grid = api.Grid(nz, nx, h, h, 20, nt, 0.5 * h / vmax, vmax)
+    vp = torch.full((nz, nx), 2000.0, device="cuda")
+    f = torch.as_tensor(rng.standard_normal(nt).astype(np.float32), device="cuda")
+    obs = torch.zeros((S, 40, nt), device="cuda")
+    plans = [api.Plan(grid, src, rec, ckpt_every=ckpt, **kw) for kw in ({}, {"two_step": 2})]
+    best = [np.inf, np.inf]
+    for _ in range(6):
+        for i, p in enumerate(plans):
+            torch.cuda.synchronize()
+            t = time.perf_counter()
+            p.gradient("vp-rho", vp, vp, f, obs)
+            torch.cuda.synchronize()
+            best[i] = min(best[i], time.perf_counter() - t)
+    assert best[0] <= 1.15 * best[1], best
