@@ -37,3 +37,20 @@ def test_close_checkpoints_not_slower_than_strips(nz, nx, S, nt, ckpt):
             torch.cuda.synchronize()
             best[i] = min(best[i], time.perf_counter() - t)
     assert best[0] <= 1.15 * best[1], best
+
+
+def test_one_step_takes_one_step_launch():
+    """A gradient of one time step has no pair of adjoint steps to advance."""
+    torch = pytest.importorskip("torch")
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_1804_01184_amd import api
+    n, h = 301, 5.0
+    grid = api.Grid(n, n, h, h, 20, 1, 0.001, 2400.0)
+    p = api.Plan(grid, [[700.0, 700.0]] * 12, [[600.0, 640.0], [800.0, 801.0]])
+    vp = torch.full((n, n), 2000.0, device="cuda")
+    f, obs = torch.ones(1, device="cuda"), torch.ones((12, 2, 1), device="cuda")
+    p.timing(True)
+    p.gradient("vp-rho", vp, vp, f, obs)
+    t = p.timing_read()
+    assert t["adj_pair"][0] == 0 and t["adj_step"][0] == 1
