@@ -1056,6 +1056,20 @@ fwi_status run_gradient(fwi_plan *p, int param, const float *m1, const float *m2
 
 namespace {
 
+// Whether the whole pressure history of `shots` shots of a sweep is kept by
+// default: plain (one shot) up to 64 GiB, batched up to half the device memory.
+bool history_fits(const fwi_plan *p, int shots)
+{
+    const double bytes = (double)(p->grid.nt + 1) * shots * p->ST * sizeof(float);
+    double budget = 64.0 * (1ull << 30);
+    if (p->mode != FWI_EXEC_PLAIN) {
+        size_t free_b = 0, total_b = 0;
+        budget = hipMemGetInfo(&free_b, &total_b) == hipSuccess ? 0.5 * (double)total_b : 0.0;
+        (void)hipGetLastError();
+    }
+    return bytes <= budget;
+}
+
 // n tiles of `span` nodes over an axis of `len`, overlapping enough that each
 // owned node lies `halo` or more from the inner edges of its tile; n = 0 if
 // the span is too short.
@@ -1442,14 +1456,18 @@ fwi_status fwi_plan_create(const fwi_grid *grid, const fwi_acq *acq, const fwi_e
                                       8, (Nz + bands - 1) / bands)));
         }
         // shot groups of the two-step adjoint: those of the one-step kernels
-        // where the caller set them, else by its cost
+        // where the caller set them, else by its cost, leaving out groups whose
+        // padding shots would cost the plan its whole pressure history
+        const auto padded = [&](int sg) { return (p->S + sg - 1) / sg * sg; };
+        const bool kept = ex.ckpt_every == 0 && history_fits(p, padded(spg));
         int spg_a = spg;
         if (ex.shots_per_group == 0 && adj2_wanted && adj2_supported(spg, ca)) {
             double best = 0.0;
             for (int sg = 1; sg <= 4; sg *= 2) {
                 double c = 0.0;
                 if (sg > p->S || !adj2_supported(sg, ca) || !adj2_fits(sg) ||
-                    (long long)sg * p->SS * 4 >= lim)
+                    (long long)sg * p->SS * 4 >= lim ||
+                    (kept && !history_fits(p, padded(std::max(spg, sg)))))
                     continue;
                 (void)adj_rows(sg, ca, c);
                 if (best == 0.0 || c < best) {
@@ -1459,7 +1477,7 @@ fwi_status fwi_plan_create(const fwi_grid *grid, const fwi_acq *acq, const fwi_e
             }
         }
         const int fill = std::max(spg, spg_a);   // (powers of two)
-        p->Spad = p->mode == FWI_EXEC_PLAIN ? p->S : (p->S + fill - 1) / fill * fill;
+        p->Spad = p->mode == FWI_EXEC_PLAIN ? p->S : padded(fill);
         p->sweep = sweep_of(g, p->Spad, H, spg, cols);
         // two-step forward kernel over the same padded shots: two columns
         // per lane; two shots a wave from 800 padded columns up, else one
@@ -1508,23 +1526,11 @@ fwi_status fwi_plan_create(const fwi_grid *grid, const fwi_acq *acq, const fwi_e
     }
     {
         // checkpoint interval: with ckpt_every = 0 the whole pressure history
-        // is kept when it fits (plain: one shot's history <= 64 GiB;
-        // batched: all shots' history <= half the device memory), so the
-        // backward sweep needs no recompute; else every ceil(sqrt(nt)) steps
+        // is kept when it fits, so the backward sweep needs no recompute; else
+        // every ceil(sqrt(nt)) steps
         int k = ex.ckpt_every > 0 ? ex.ckpt_every : (int)std::ceil(std::sqrt((double)G.nt));
-        if (ex.ckpt_every == 0) {
-            const int B = p->mode == FWI_EXEC_PLAIN ? 1 : p->Spad;
-            const double bytes = (double)(G.nt + 1) * B * p->ST * sizeof(float);
-            double budget = 64.0 * (1ull << 30);
-            if (p->mode != FWI_EXEC_PLAIN) {
-                size_t free_b = 0, total_b = 0;
-                budget = hipMemGetInfo(&free_b, &total_b) == hipSuccess ? 0.5 * (double)total_b
-                                                                         : 0.0;
-                (void)hipGetLastError();
-            }
-            if (bytes <= budget)
-                k = G.nt;
-        }
+        if (ex.ckpt_every == 0 && history_fits(p, batch_of(p)))
+            k = G.nt;
         p->k = std::max(1, std::min(k, G.nt));
         p->nseg = (G.nt + p->k - 1) / p->k;
     }
