@@ -373,7 +373,7 @@ def main():
         # this shape (cached per shape and GPU), outside the timed region
         from paper_1804_01184_amd import autotune
         t = time.perf_counter()
-        decomp = autotune.tune(grid, w.src_xz, w.rec_xz)
+        decomp = autotune.plan_keywords(grid, w.src_xz, w.rec_xz)
         tuned = {"seconds": round(time.perf_counter() - t, 2)}
         print(f"bench: decomposition {decomp} ({tuned['seconds']} s)", file=sys.stderr,
               flush=True)

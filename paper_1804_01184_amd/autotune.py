@@ -1,18 +1,23 @@
-"""Decomposition autotuner for the batched kernels.
+"""Decomposition autotuner for the batched strip kernels.
 
 The one-step adjoint kernel, the two-step adjoint kernel and the two-step
 forward kernel have decompositions of their own (band rows swept per wave,
 shots advanced together per wave, grid columns per lane), so they are tuned
 separately on a short run of the real grid and shot count, with the whole
 pressure history kept: each candidate is timed by its own launches, using
-the library's per-launch HIP event timing.  The two-step adjoint shares the
-shot groups (and so their partial gradients) with the one-step adjoint,
-which then runs only for a leftover odd step of a segment; it is chosen
-when its time per step beats the one-step kernel's.  The one-step forward
-kernel (a leftover odd forward step) shares the one-step adjoint
-decomposition.  Results are cached in a JSON file keyed by the shape and the
-GPU; the package ships the results measured on MI355X for the benchmark
-shapes (tuned_gfx950.json), consulted when the cache has none.
+the library's per-launch HIP event timing.  Setting any of them puts a plan
+on the strip kernels; a plan that sets none may run on the tile kernels, and
+chooses by the library's own rules.  So the best decomposition is timed
+against that plan at the end, over a whole gradient, and plan_keywords and
+tuned_plan leave the decomposition out where the default plan is faster.
+
+The two-step adjoint takes the shot groups of the one-step kernels (which the
+tuner sets); it is chosen when its time per step beats the one-step kernel's,
+and then advances every step.  The one-step forward kernel (a leftover odd
+forward step) shares the one-step adjoint decomposition.  Results are cached
+in a JSON file keyed by the shape, the GPU and the kernels' version; the
+package ships the results measured on MI355X for the benchmark shapes
+(tuned_gfx950.json), consulted when the cache has none.
 """
 from __future__ import annotations
 
@@ -23,6 +28,7 @@ import time
 import numpy as np
 import torch
 
+from . import _lib as L
 from .api import Grid, Plan
 
 # band heights: every height from 8 to 16 (the kernels are bounded per CU,
@@ -56,7 +62,8 @@ def cache_path():
 
 
 def _key(Nz, Nx, S, npml, arch):
-    return f"{arch}:{Nz}x{Nx}:S{S}:pml{npml}:v6"
+    # the last part is raised whenever the kernels' best decompositions move
+    return f"{arch}:{Nz}x{Nx}:S{S}:pml{npml}:v7"
 
 
 def _arch():
@@ -153,17 +160,49 @@ def measure(grid: Grid, src_xz, rec_xz, nt_probe=24, reps=2, device=None, **deco
     return {k: ms / n for k, (n, ms) in t.items() if n > 0}
 
 
-def tune(grid: Grid, src_xz, rec_xz, force=False, verbose=False, device=None):
-    """Plan keywords of the tuned decomposition for this shape (from the
-    cache or by measuring): band_rows, shots_per_group, lane_cols of the
-    one-step kernels and the two_step_* fields of the two-step kernel."""
+def _gradient_ms(grid, src_xz, rec_xz, ws, device, reps, **decomp):
+    """Device time (ms) of one gradient's sweeps over the grid's steps, the whole
+    pressure history kept, in the workspace `ws` (None: returns the bytes it takes)."""
+    plan = Plan(grid, src_xz, rec_xz, ckpt_every=grid.nt, device=device, **decomp)
+    if ws is None:
+        return plan.workspace_bytes(L.FWI_OP_GRADIENT)
+    dev = plan.device
+    K = torch.full((grid.nz, grid.nx), 2000.0 * 2000.0 ** 2, device=dev)
+    rho = torch.full((grid.nz, grid.nx), 2000.0, device=dev)
+    f = torch.zeros(grid.nt, device=dev)
+    f[1] = 1.0
+    adj = torch.ones((plan.nshots, plan.nrec, grid.nt), device=dev)
+    ev = [torch.cuda.Event(enable_timing=True) for _ in range(reps + 1)]
+    for k in range(-1, reps):   # the first is a warm-up
+        ev[max(k, 0)].record(torch.cuda.current_stream(dev))
+        plan.forward_keep("k-rho", K, rho, f, ws)
+        plan.adjoint_kept("k-rho", K, rho, f, adj, ws)
+    ev[reps].record(torch.cuda.current_stream(dev))
+    torch.cuda.synchronize(dev)
+    return min(a.elapsed_time(b) for a, b in zip(ev, ev[1:]))
+
+
+def default_wins(grid, src_xz, rec_xz, best, nt_probe=48, reps=3, device=None):
+    """Whether the plan without a decomposition runs a gradient faster than the
+    one with `best`, both in the same workspace (the strip kernels' time moves
+    by some percent with its placement); within 3 % `best` is kept."""
+    g = _probe_grid(grid, nt_probe)
+    need = max(_gradient_ms(g, src_xz, rec_xz, None, device, reps, **d) for d in ({}, best))
+    with torch.cuda.device(device if device is not None else torch.cuda.current_device()):
+        ws = torch.empty(need, dtype=torch.uint8, device="cuda")
+        ms = [_gradient_ms(g, src_xz, rec_xz, ws, device, reps, **d) for d in ({}, best)]
+    return ms[0] < 0.97 * ms[1]
+
+
+def _tuned_entry(grid, src_xz, rec_xz, force, verbose, device):
+    """The shape's entry from the cache, the shipped table or by measuring."""
     src = np.asarray(src_xz).reshape(-1, 2)
     S = src.shape[0]
     Nz, Nx = grid.padded
     key = _key(Nz, Nx, S, grid.npml, _arch())
     cache = load_cache()
     if not force and key in cache:
-        return dict(cache[key]["best"])
+        return cache[key]
     if not force:
         try:
             with open(SHIPPED) as fh:
@@ -171,7 +210,7 @@ def tune(grid: Grid, src_xz, rec_xz, force=False, verbose=False, device=None):
         except (OSError, ValueError):
             shipped = {}
         if key in shipped:
-            return dict(shipped[key]["best"])
+            return shipped[key]
     t0 = time.perf_counter()
     res1, resa, res2 = [], [], []
     for H, spg, cols in candidates_adj2(Nz, Nx, S):
@@ -236,18 +275,36 @@ def tune(grid: Grid, src_xz, rec_xz, force=False, verbose=False, device=None):
             best["two_step"] = 1
     else:
         best["two_step"] = 1
+    wins = default_wins(grid, src_xz, rec_xz, best, device=device)
+    if verbose:
+        print(f"  default plan {'faster' if wins else 'not faster'}", flush=True)
     cache = load_cache()
-    cache[key] = {"best": best, "adjoint": res1, "adj_two_step": resa, "two_step": res2,
-                  "seconds": time.perf_counter() - t0}
+    cache[key] = {"best": best, "default": wins, "adjoint": res1, "adj_two_step": resa,
+                  "two_step": res2, "seconds": time.perf_counter() - t0}
     save_cache(cache)
-    return dict(best)
+    return cache[key]
+
+
+def tune(grid: Grid, src_xz, rec_xz, force=False, verbose=False, device=None):
+    """Plan keywords of the strip kernels' tuned decomposition for this shape
+    (from the cache or by measuring): band_rows, shots_per_group, lane_cols of
+    the one-step kernels, the adj_two_step_* and two_step_* fields of the
+    two-step kernels."""
+    return dict(_tuned_entry(grid, src_xz, rec_xz, force, verbose, device)["best"])
+
+
+def plan_keywords(grid: Grid, src_xz, rec_xz, force=False, verbose=False, device=None):
+    """The same, or {} where the default plan runs this shape faster."""
+    e = _tuned_entry(grid, src_xz, rec_xz, force, verbose, device)
+    return {} if e.get("default") else dict(e["best"])
 
 
 def tuned_plan(grid: Grid, src_xz, rec_xz, **kw):
-    """A batched Plan with the tuned decomposition."""
-    best = tune(grid, src_xz, rec_xz, device=kw.get("device"))
+    """A batched Plan with the tuned decomposition, or the default plan where
+    that runs this shape faster."""
+    best = plan_keywords(grid, src_xz, rec_xz, device=kw.get("device"))
     return Plan(grid, src_xz, rec_xz, **{**best, **kw})
 
 
-__all__ = ["tune", "tuned_plan", "candidates", "candidates2", "candidates_adj2", "measure",
+__all__ = ["tune", "plan_keywords", "tuned_plan", "candidates", "candidates2", "candidates_adj2", "measure",
            "balanced_rows"]

@@ -1,0 +1,61 @@
+"""The tuner times its best strip decomposition against the default plan, which
+small problems run on the tile kernels: the tuned plan is not slower (1.1 times
+allows for the placement of two workspaces; on strips it took over three times
+as long), and measurements of earlier kernels are not taken from a cache."""
+import json
+import time
+
+import numpy as np
+import pytest
+
+from paper_1804_01184_amd import workloads as W
+
+pytestmark = pytest.mark.gpu
+
+
+def test_tuned_plan_is_not_slower_than_the_default(tmp_path, monkeypatch):
+    torch = pytest.importorskip("torch")
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_1804_01184_amd import api, autotune
+    cache = tmp_path / "tune.json"
+    monkeypatch.setenv("FWI2D_TUNE_CACHE", str(cache))
+    w = W.gauss_problem(121, 10, 100, 300, npml=20, seed=4)
+    g = api.Grid.of(w)
+    old = autotune._key(*g.padded, w.nshots, g.npml, autotune._arch()).rsplit(":", 1)[0] + ":v6"
+    stale = {"band_rows": 128, "shots_per_group": 8, "lane_cols": 1, "adj_two_step": 1,
+             "two_step": 1}
+    cache.write_text(json.dumps({old: {"best": stale}}))
+    plans = [api.Plan(g, w.src_xz, w.rec_xz), autotune.tuned_plan(g, w.src_xz, w.rec_xz)]
+    assert autotune.tune(g, w.src_xz, w.rec_xz) != stale
+    f = w.wavelet()
+    obs = plans[0].forward("vp-rho", w.vp_true, w.rho_true, f)
+    best = [np.inf, np.inf]
+    for _ in range(6):
+        for i, p in enumerate(plans):
+            torch.cuda.synchronize()
+            t = time.perf_counter()
+            p.gradient("vp-rho", w.vp_start, w.rho_start, f, obs)
+            torch.cuda.synchronize()
+            best[i] = min(best[i], time.perf_counter() - t)
+    assert best[1] <= 1.1 * best[0], best
+
+
+def test_a_decomposition_that_wins_is_kept(tmp_path, monkeypatch):
+    """plan_keywords gives the decomposition unless the entry says otherwise."""
+    torch = pytest.importorskip("torch")
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_1804_01184_amd import api, autotune
+    cache = tmp_path / "tune.json"
+    monkeypatch.setenv("FWI2D_TUNE_CACHE", str(cache))
+    g = api.Grid(61, 61, 5.0, 5.0, 10, 40, 0.001, 2400.0)
+    key = autotune._key(*g.padded, 2, g.npml, autotune._arch())
+    best = {"band_rows": 16, "shots_per_group": 2, "lane_cols": 1}
+    src, rec = [[100.0, 100.0], [120.0, 90.0]], [[200.0, 210.0]]
+    for default, want in ((False, best), (True, {})):
+        cache.write_text(json.dumps({key: {"best": best, "default": default}}))
+        assert autotune.plan_keywords(g, src, rec) == want
+        assert autotune.tune(g, src, rec) == best
+        assert autotune.tuned_plan(g, src, rec).info["band_rows"] == \
+            api.Plan(g, src, rec, **want).info["band_rows"]
