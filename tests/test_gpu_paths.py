@@ -1,0 +1,115 @@
+"""Which kernels run: the sizes that test the tile kernels do run on them, those
+that test the strip kernels on those, and the two-step adjoint's default shot
+groups are the ones its cost model is meant to choose.  The launches of a kernel
+class tell: a tile launch is a forward or adjoint step launch of several steps, so
+there are fewer of them than steps; the strip kernels advance pairs.
+
+The strip kernels' defaults (decomposition and shot groups) are held to the
+oracle on small problems too, where a default plan runs on tiles: every
+parameterization, a wavelet per shot, whole history and checkpoints."""
+import numpy as np
+import pytest
+
+import oracle as O
+import test_gpu_tiles
+
+pytestmark = pytest.mark.gpu
+
+TOL = 1e-4
+
+
+@pytest.fixture(scope="module")
+def api():
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_1804_01184_amd import api as A
+    return A
+
+
+def launches(api, plan, op):
+    """{kernel class: launches} of a forward call or a gradient."""
+    import torch
+    g = plan.grid
+    m = torch.full((g.nz, g.nx), 2000.0, device="cuda")
+    f = torch.ones((plan.nshots, g.nt) if plan.wavelet_per_shot else g.nt, device="cuda")
+    plan.timing(True)
+    if op == "forward":
+        plan.forward("vp-rho", m, m, f)
+    else:
+        plan.adjoint("vp-rho", m, m, f, torch.ones((plan.nshots, plan.nrec, g.nt), device="cuda"))
+    return {k: n for k, (n, _) in plan.timing_read().items()}
+
+
+def acquisition(nz, nx, S, h=5.0):
+    rng = np.random.default_rng(nz + nx + S)
+    return (np.stack([rng.uniform(h, (nx - 2) * h, S), rng.uniform(h, (nz - 2) * h, S)], axis=1),
+            np.stack([rng.uniform(0, (nx - 1.01) * h, 9), rng.uniform(0, (nz - 1.01) * h, 9)],
+                     axis=1))
+
+
+def grid_of(api, nz, nx, npml, nt):
+    return api.Grid(nz, nx, 5.0, 5.0, npml, nt, 0.001, 2400.0)
+
+
+@pytest.mark.parametrize("nz,nx,npml,nt,S,ckpt",
+                         [c[:6] for c in test_gpu_tiles.CASES if c[3] > 1])
+def test_tile_sizes_run_on_tiles(api, nz, nx, npml, nt, S, ckpt):
+    src, rec = acquisition(nz, nx, S)
+    p = api.Plan(grid_of(api, nz, nx, npml, nt), src, rec, ckpt_every=ckpt)
+    n = launches(api, p, "forward")
+    assert 0 < n["fwd_step"] < nt and n["fwd_pair"] == 0
+    n = launches(api, p, "gradient")
+    assert 0 < n["fwd_step"] < 2 * nt and n["fwd_pair"] == 0
+    assert 0 < n["adj_step"] < nt and n["adj_pair"] == 0
+
+
+@pytest.mark.parametrize("nz,nx,npml,nt,S", [(560, 559, 20, 17, 7), (201, 401, 40, 70, 19)])
+def test_between_the_rules(api, nz, nx, npml, nt, S):
+    src, rec = acquisition(nz, nx, S)
+    p = api.Plan(grid_of(api, nz, nx, npml, nt), src, rec)
+    n = launches(api, p, "forward")
+    assert 0 < n["fwd_step"] < nt and n["fwd_pair"] == 0
+    n = launches(api, p, "gradient")
+    assert n["fwd_pair"] == nt // 2 and n["adj_pair"] == (nt + 1) // 2
+    n = launches(api, api.Plan(grid_of(api, nz, nx, npml, nt), src, rec, two_step=2), "forward")
+    assert n["fwd_pair"] == nt // 2
+
+
+@pytest.mark.parametrize("nz,nx,npml,S,spg", [(1001, 1001, 40, 64, 4), (401, 401, 40, 40, 2),
+                                              (333, 451, 40, 13, 1), (2001, 2001, 40, 32, 4)])
+def test_default_groups_of_the_two_step_adjoint(api, nz, nx, npml, S, spg):
+    """The gradient's workspace holds a partial gradient per group."""
+    src, rec = acquisition(nz, nx, S)
+    g = grid_of(api, nz, nx, npml, 20)
+    need = {k: api.Plan(g, src, rec, ckpt_every=20, shots_per_group=k,
+                        two_step=2).workspace_bytes(api.L.FWI_OP_GRADIENT) for k in (0, 1, 2, 4)}
+    assert need[0] == need[spg]
+    assert all(need[k] != need[spg] for k in (1, 2, 4) if k != spg)
+
+
+@pytest.mark.parametrize("param", ["k-rho", "vp-rho", "ip-rho", "vp-ip", "invk-invrho"])
+@pytest.mark.parametrize("ckpt,per_shot", [(0, False), (9, True)])
+def test_default_strips_against_oracle(api, param, ckpt, per_shot):
+    nz, nx, npml, nt, S, h, vmax = 61, 149, 12, 60, 6, 5.0, 2400.0
+    rng = np.random.default_rng(nt + ckpt)
+    src, rec = acquisition(nz, nx, S)
+    rec = np.ascontiguousarray(np.broadcast_to(rec, (S,) + rec.shape))
+    rho = 2000.0 * (1 + 0.1 * rng.random((nz, nx)))
+    K = rho * (2000.0 * (1 + 0.1 * rng.random((nz, nx)))) ** 2
+    f = rng.standard_normal((S, nt) if per_shot else nt)
+    adj = rng.standard_normal((S, rec.shape[1], nt)).astype(np.float32)
+    dt = 0.5 * h / vmax
+    g = O.Grid(nz, nx, h, h, npml, nt, dt, vmax)
+    tr = O.forward_krho(g, src, rec, K, rho, f)
+    want = O.chain_rule(O.PARAMS[param], K, rho,
+                        *O.adjoint_krho(g, src, rec, K, rho, f, adj.astype(np.float64)))
+    m = O.krho_to_model(O.PARAMS[param], K, rho)
+    p = api.Plan(api.Grid(nz, nx, h, h, npml, nt, dt, vmax), src, rec, wavelet_per_shot=per_shot,
+                 ckpt_every=ckpt, two_step=2)
+    assert p.info["adj_two_step"] == 1
+    got = p.forward(param, *m, f).cpu().numpy()
+    for s in range(S):
+        assert np.abs(got[s] - tr[s]).max() <= TOL * np.abs(tr[s]).max()
+    for a, b in zip(p.adjoint(param, *m, f, adj), want):
+        assert np.abs(a.cpu().numpy() - b).max() <= TOL * np.abs(b).max()
