@@ -114,12 +114,12 @@ def algorithmic_bytes(plan_info, S, k):
                                           gK and the buoyancy gradient pair
                                           read and written once
     and, per kernel class, the cell-steps one launch advances (a two-step
-    forward launch advances two).  The forward kernels in a gradient store
-    the pressure, so both are charged the recompute figure.  The kernels'
-    own minimum for one launch (a one-step adjoint must read both pressure
-    levels and their splits, and in this design reads the model and
-    read-modify-writes the gradient once per shot group) is larger; the
-    counter traffic shows what they move."""
+    launch advances two; tile launches are step launches of several steps, see
+    step_launches).  The forward kernels in a gradient store the pressure, so
+    both are charged the recompute figure.  The kernels' own minimum for one
+    launch differs (the strip kernels read the model, and in the adjoint
+    read-modify-write the gradient, once per shot group and launch, and move
+    the state once per two steps); the counter traffic shows what they move."""
     N = plan_info["Nz"] * plan_info["Nx"]
     fp = plan_info["pml_cells"] / N
     fwd = 24 + 8 * fp + 8 / S + 12 / k
@@ -131,10 +131,38 @@ def algorithmic_bytes(plan_info, S, k):
             "gradient_per_cell": rec + rec + adj - 4 - 12 / k}
 
 
-KERNEL_SOURCE = os.path.join(ROOT, "paper_1804_01184_amd", "csrc", "k_fused.hip")
+def step_launches(ab, per_class, info, nt):
+    """The same with the cell-steps a launch of the step classes advances in a
+    gradient that had none of the pair class: its steps (nt, and in the forward
+    sweeps the recomputed ones) over its launches.  One for the strip kernels'
+    one-step launches; on the tile kernels several."""
+    k, nseg = info["ckpt_every"], info["segments"]
+    steps = {"fwd": nt + (nseg - 1) * k, "adj": nt}
+    cells = dict(ab["cell_steps"])
+    for s, n in steps.items():
+        launches = per_class.get(s + "_step", (0, 0.0))[0]
+        if launches and not per_class.get(s + "_pair", (0, 0.0))[0]:
+            cells[s + "_step"] = round(cells[s + "_step"] * n / launches)
+    return dict(ab, cell_steps=cells)
+
+
+def sources(*names):
+    return tuple(os.path.join(ROOT, "paper_1804_01184_amd", "csrc", n) for n in names)
+
+
+# what the counted kernels are compiled from
+KERNEL_SOURCE = sources("k_fused.hip", "wave_dev.h", "fwi2d_internal.h")
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "traffic.json")
-BORN_SOURCE = os.path.join(ROOT, "paper_1804_01184_amd", "csrc", "k_born.hip")
+BORN_SOURCE = sources("k_born.hip", "fwi2d_internal.h")
 BORN_TRAFFIC_FILE = os.path.join(ROOT, "profiles", "traffic_born.json")
+
+
+def source_sha256(paths):
+    h = hashlib.sha256()
+    for p in paths:
+        with open(p, "rb") as fh:
+            h.update(fh.read())
+    return h.hexdigest()
 
 
 def measured_traffic(kernel, decomposition, traffic_file=TRAFFIC_FILE, source=KERNEL_SOURCE):
@@ -144,8 +172,7 @@ def measured_traffic(kernel, decomposition, traffic_file=TRAFFIC_FILE, source=KE
     try:
         with open(traffic_file) as fh:
             prof = json.load(fh)
-        with open(source, "rb") as fh:
-            sha = hashlib.sha256(fh.read()).hexdigest()
+        sha = source_sha256(source)
     except (OSError, ValueError):
         return None
     # entries are keyed "<kernel class>@<workload>" (or by the class alone)
@@ -422,7 +449,7 @@ def main():
     value = cells / (ms * 1e-3) / 1e9
 
     S, G = w.nshots, info["shot_groups"]
-    ab = algorithmic_bytes(info, S, info["ckpt_every"])
+    ab = step_launches(algorithmic_bytes(info, S, info["ckpt_every"]), per_class, info, w.nt)
     roof, roof_all = None, {}
     if not args.no_kernel_timing:
         # every sweep kernel that ran: achieved = its per-cell-step algorithmic
