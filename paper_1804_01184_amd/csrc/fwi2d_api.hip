@@ -196,8 +196,15 @@ int partials_of(const fwi_plan *p)
                                      : p->sweep.ngroups;
 }
 
-// steps of R^T r staged at a time for the batched adjoints (even)
+// Steps of R^T r staged at a time for the batched adjoints (even): 64, fewer where
+// the sums of a dense acquisition's nodes would take more than 256 MB (a receiver
+// on every node of 64 shots of 1081 x 1081 would stage 23 GB).
 constexpr int kStageSteps = 64;
+int stage_steps(const fwi_plan *p)
+{
+    const long long nodes = std::max(1, std::max(p->inj_nodes, p->adj_list));
+    return (int)std::max(2LL, std::min<long long>(kStageSteps, (1LL << 26) / nodes / 2 * 2));
+}
 
 Layout layout(const fwi_plan *p, int op)
 {
@@ -254,7 +261,7 @@ Layout layout(const fwi_plan *p, int op)
         L.partials = take(misfit_blocks(ntr));
         if (p->mode != FWI_EXEC_PLAIN)
             L.injacc = take((size_t)std::max(std::max(p->inj_nodes, p->adj_list), 1) *
-                                std::min(kStageSteps, p->grid.nt) + 64);
+                                std::min(stage_steps(p), p->grid.nt) + 64);
     }
     L.total = off;
     if (op == FWI_OP_GRADIENT)   // a gradient workspace also serves a forward call
@@ -646,7 +653,8 @@ void sweep_backward(const Ctx &c, int s0, int nb, const float *resid, float *gpa
     zero_state(c, c.f(c.L.lam[0]), nb);
     int li = 0;
     // batched: next adjoint step; R^T r^n of levels n = top .. staged lie in
-    // injv, kStageSteps (an even number) at a time
+    // injv, an even number of them at a time
+    const int stage = stage_steps(p);
     int m = nt, top = -1, staged = nt;
     float *injv = c.f(c.L.injacc);
     const Inj inj = inj_of(c, 0, p->S);
@@ -703,7 +711,7 @@ void sweep_backward(const Ctx &c, int s0, int nb, const float *resid, float *gpa
         // level n0 is slot 0 (step 0, of level 0, adds nothing)
         while (m > n0) {
             if (m - 1 < staged) {
-                staged = m - std::min(kStageSteps, m);
+                staged = m - std::min(stage, m);
                 top = m - 1;
                 Timed tm(c.pl, c.st, FWI_KC_INJECT);
                 launch_inject_stage(inj, list, nlist, resid, p->nrec, nt, top, top - staged + 1,
@@ -816,7 +824,7 @@ void tile_backward(const Ctx &c, const float *resid, float *gpart)
         }
         // adjoint steps m = n1 .. n0+1; step m takes p^m and adds R^T r^{m-1}
         for (int m = n1; m > n0;) {
-            const int cnt = std::min(kStageSteps, m - n0);
+            const int cnt = std::min(stage_steps(p), m - n0);
             {
                 Timed tm(c.pl, c.st, FWI_KC_INJECT);
                 launch_inject_stage(inj, nullptr, inj.nnodes, resid, p->nrec, nt, m - 1, cnt, injv,
