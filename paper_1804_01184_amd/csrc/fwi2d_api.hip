@@ -1081,24 +1081,22 @@ bool history_fits(const fwi_plan *p, int shots)
 // n tiles of `span` nodes over an axis of `len`, overlapping enough that each
 // owned node lies `halo` or more from the inner edges of its tile; n = 0 if
 // the span is too short.
-TileAxis tile_axis(int len, int span, int halo, int unit)
+TileAxis tile_axis(int len, int span, int halo)
 {
-    const int hu = (halo + unit - 1) / unit * unit;   // owned ranges start at a whole lane
     if (len <= span)
-        return {1, len, 0, hu, unit};
-    const int last = (len - span + unit - 1) / unit * unit;
-    const int most = span - halo - hu;
-    if (most < unit)
-        return {0, len, 0, hu, unit};
+        return {1, len, 0, halo};
+    const int last = len - span, most = span - 2 * halo;
+    if (most < 1)
+        return {0, len, 0, halo};
     for (int n = 2;; ++n) {
         int gap = 0, prev = 0;
         for (int k = 1; k < n; ++k) {
-            const int f = k * last / (n - 1) / unit * unit;
+            const int f = k * last / (n - 1);
             gap = std::max(gap, f - prev);
             prev = f;
         }
         if (gap <= most)
-            return {n, len, last, hu, unit};
+            return {n, len, last, halo};
     }
 }
 
@@ -1156,8 +1154,8 @@ fwi_plan::Tiles choose_tiles(const fwi_plan *p, const fwi_exec &ex)
     auto choose = [&](bool adj, int len, fwi_plan::TileRun &best) {
         double least = 1e30;
         for (int T = 1; T <= std::min(8, len); ++T) {
-            const fwi_plan::TileRun r = {T, tile_axis(g.Nx, kTileX, 3 * T, kTileCols),
-                                         tile_axis(g.Nz, kTileZ, 3 * T, 1)};
+            const fwi_plan::TileRun r = {T, tile_axis(g.Nx, kTileX, 3 * T),
+                                         tile_axis(g.Nz, kTileZ, 3 * T)};
             if (!r.x.n || !r.z.n)
                 continue;
             const double us = cost(r, adj, len);

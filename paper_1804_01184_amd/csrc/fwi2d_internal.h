@@ -285,15 +285,14 @@ void launch_fused_fwd2(const Geo &g, const float *tabs, const float *model,
 
 // ------------------------------------------------------------------ tiles
 // One axis of the tile kernels' decomposition: n tiles of a fixed span cover
-// `len` nodes, tile k starting at k last / (n - 1) rounded down to a multiple
-// of `unit` (columns per lane; 1 along z) and owning the nodes `halo` or more
-// from the edges it shares with other tiles.  last: start of the last tile.
+// `len` nodes, tile k starting at k last / (n - 1) and owning the nodes `halo` or
+// more from the edges it shares with other tiles.  last: start of the last tile.
 struct TileAxis {
-    int n, len, last, halo, unit;
+    int n, len, last, halo;
 };
-// Columns per lane, rows per wave and waves of a workgroup: 64 x 64 nodes.
-constexpr int kTileCols = 1, kTileRows = 4, kTileWaves = 16;
-constexpr int kTileX = 64 * kTileCols, kTileZ = kTileRows * kTileWaves;
+// Rows per wave and waves of a workgroup: 64 x 64 nodes, one column a lane.
+constexpr int kTileRows = 4, kTileWaves = 16;
+constexpr int kTileX = 64, kTileZ = kTileRows * kTileWaves;
 // T forward steps from state n of every shot (record: vx, vz, p, pz N floats
 // apart); p^{n+1+j} of shot s also goes to hist + j lvl + s ss (floats) unless
 // hist is null.
