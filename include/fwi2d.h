@@ -121,7 +121,7 @@ typedef struct {
     int32_t shots_per_group; /* batched kernels: shots a wave advances together;
                              0: default (one-step kernels: with the two-step
                              adjoint 2, or 1 when 16-row bands of two-shot
-                             waves would not fill the device once; without
+                             waves number fewer than 2048; without
                              it up to 4.  The two-step adjoint then takes 1,
                              2 or 4 by its own estimate, which fwi_plan_info
                              does not report)                               */
@@ -140,25 +140,28 @@ typedef struct {
     int32_t two_step_shots_per_group; /* kernel, 0: defaults; supported    */
     int32_t two_step_lane_cols;       /* (shots, cols): (1|2, 1|2), (1, 4).
                              Defaults: 2 columns per lane, 2 shots per wave
-                             from 800 padded columns up (else 1).  Default
-                             band rows of both two-step kernels: among the
-                             heights the autotuner tries, the one with the
+                             from 800 padded columns up (else 1); of the
+                             band rows the autotuner tries, those with the
                              fewest rounds of resident waves times rows per
-                             band (H + 6), the taller on a tie              */
+                             band (H + 6), the taller on a tie.  (The
+                             two-step adjoint's by a cost estimate.)        */
     int32_t adj_two_step; /* batched adjoint sweeps advance two time steps per
                              launch (the intermediate adjoint state stays on
                              chip; same results bit for bit): 0 default (on
-                             where supported), 1 off, 2 on.  The two-step
+                             where supported and nt > 1), 1 off, 2 on.  The two-step
                              adjoint uses shots_per_group where that is set;
                              supported (shots, cols): (1|2|4, 1), (1|2, 2)   */
     int32_t adj_two_step_band_rows;   /* its band rows (4..4096), 0: default */
     int32_t adj_two_step_lane_cols;   /* its columns per lane, 0: default    */
     /* With every field from band_rows on left 0, batched plans of up to about
-     * two million padded nodes over all shots (a forward call: four) run on
-     * tile kernels instead (several steps per launch with a tile's state in
-     * registers; the same traces bit for bit, gradients within FP32
-     * rounding), where the plan estimates them faster.  fwi_plan_info always
-     * describes the strip kernels.                                          */
+     * two million padded nodes over all shots (a forward call: three and a
+     * half) run on tile kernels instead (several steps per launch with a
+     * tile's state in registers; the same traces bit for bit, gradients
+     * within FP32 rounding), where the plan, taken alone on the device and
+     * with its checkpoints, estimates them faster.  From about three quarters
+     * of a million nodes up, several calls at once on streams of their own
+     * take less of the device on the strip kernels: two_step = 2 selects them.
+     * fwi_plan_info always describes the strip kernels.                     */
 } fwi_exec;
 
 typedef struct {
@@ -347,8 +350,8 @@ fwi_status fwi_born_green(int32_t F, const float *omega, int32_t C, const float 
 
 /* Workspace bytes (256-byte aligned) that fwi_born_data, fwi_born_gradient
  * and fwi_born_misfit need for these sizes: the partial sums of the split
- * launches and, for the gradient with 2 sources or more, the residual
- * weights transposed for the matrix cores.  The workspace is only used
+ * launches and, for the gradient, the residual weights laid out for the
+ * matrix cores.  The workspace is only used
  * during the call's kernels; calls on one workspace must be ordered (same
  * stream).  0 for sizes the calls reject. */
 size_t fwi_born_workspace_bytes(int32_t F, int32_t S, int32_t R, int32_t C);
@@ -356,9 +359,11 @@ size_t fwi_born_workspace_bytes(int32_t F, int32_t S, int32_t R, int32_t C);
 /* Born data d [F][S][R] (formula above) from the contrasts xiK, xiR [C], the
  * source tables Gs, Gsx, Gsz [F][C][S], the receiver tables Gr, Grx, Grz
  * [F][C][R] and the direct wave Gd [F][S][R] (NULL: scattered data only).
- * spec [F] complex.  FP32 arithmetic with FP32 accumulation, on the FP32
- * matrix cores from 9 sources up: per frequency the cells are cut into
- * ranges summed in a fixed order (bitwise repeatable).  FWI_EINVAL for
+ * spec [F] complex.  FP32 products (to 2^-24) with FP32 accumulation, from 9
+ * sources up as three bf16 parts a factor on the matrix cores: per frequency
+ * the cells are cut into ranges summed in a fixed order (bitwise
+ * repeatable).  There factors below about 1e-33 lose low bits, and a
+ * non-finite one makes the sums that it enters NaN.  FWI_EINVAL for
  * sizes out of range (F > 65535, S > 4194240, S R >= 2^31) or a NULL
  * required array; FWI_EWORKSPACE if work is NULL, misaligned or smaller
  * than fwi_born_workspace_bytes. */
@@ -378,7 +383,8 @@ fwi_status fwi_born_misfit(int64_t n, const float *d, const float *q, float *res
  * [F][S][R] complex: gK[c] = dJ/dxi_{1/K}(c), gR[c] = dJ/dxi_{1/rho}(c), the
  * real part of sum conj(resid) dd/dxi, i.e. the adjoint of the Born
  * operator applied to the residual.  Tables as fwi_born_data.  Frequencies
- * are cut into ranges summed in a fixed order. */
+ * are cut into ranges summed in a fixed order.  The sums over the receivers
+ * run as fwi_born_data's do from 9 sources up, with the same range. */
 fwi_status fwi_born_gradient(int32_t F, const float *omega, const float *spec, int32_t S,
                              int32_t R, int32_t C, double K0, double rho0, double dA,
                              const float *resid, const float *Gs, const float *Gsx,

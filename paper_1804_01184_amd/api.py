@@ -73,7 +73,9 @@ class Plan:
     defaults); two_step (0 default on, 1 off, 2 on) and the two_step_*
     fields the two-step forward kernel; adj_two_step (0 default on, 1 off,
     2 on) and the adj_two_step_* fields the two-step adjoint kernel, which
-    shares shots_per_group.
+    takes shots_per_group where that is set.  With none of them set a small
+    problem runs on the tile kernels; two_step=2 keeps it on the strip
+    kernels, which leave more of the device to other calls at the same time.
     """
 
     def __init__(self, grid: Grid, src_xz, rec_xz, wavelet_per_shot=False, mode="batched",

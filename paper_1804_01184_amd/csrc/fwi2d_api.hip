@@ -180,7 +180,7 @@ struct Layout {
     size_t work[2], lam[2];
     size_t ckpt, store, gpart, fold, traces, resid, partials;
     size_t mid;   // p^{n+1} of a two-step launch outside the stored history
-    size_t injacc;   // R^T r of up to kStageSteps steps per injection node (batched adjoint)
+    size_t injacc;   // R^T r of up to stage_steps steps per injection node (batched adjoint)
     size_t nodes;    // p^{n+1} at the receiver nodes (two-step forward, level only sampled)
     size_t hist;     // levels to sample (tile forward without a kept history)
     size_t total;
@@ -1381,8 +1381,8 @@ fwi_status fwi_plan_create(const fwi_grid *grid, const fwi_acq *acq, const fwi_e
         };
         // Shots per wave and band height of the two-step adjoint: a row of a
         // workgroup takes kRowUs[n - 1] us where a compute unit runs n
-        // workgroups at once (measured on MI355X at one column per lane;
-        // wider lanes are taken in proportion); with more workgroups than run
+        // workgroups at once (measured on a whole MI355X, 256 compute units, at one
+        // column per lane; wider lanes are taken in proportion); with more workgroups than run
         // at once their rounds overlap, and each full round takes kRoundUs.  A
         // band takes kStart rows more (its halo and the start of its windows),
         // and taller bands lose some of the cache lines that the groups of a
@@ -1394,8 +1394,9 @@ fwi_status fwi_plan_create(const fwi_grid *grid, const fwi_acq *acq, const fwi_e
         // after the other 1.04 and 1.21): 64 shots of 1081 x 1081 (4 shots a
         // wave, 91 rows) 897 us, 2 shots 1005; 32 of 2081 x 2081 (4, 64) 1585,
         // best 1553, 2 shots 1748; 40 of 481 x 481 (2, 20) 167, 1 shot 172, 4
-        // shots 185; 13 of 413 x 531 (1, 20) 57, 2 shots 67.  Shots that only
-        // fill up a group cost the forward sweeps too.
+        // shots 185; 13 of 413 x 531 (1, 20) 57, 2 shots 67.  (Taken before the
+        // receiver nodes of a row were added at once: 1 to 6 % less since on these.)
+        // Shots that only fill up a group cost the forward sweeps too.
         auto adj_cost = [&](int sg, int cl, int H) {
             static const double kRowUs[3][4] = {
                 {1.14, 1.49, 1.94, 2.36}, {2.1, 2.4, 3.08, 0}, {3.14, 3.76, 0, 0}};
@@ -1427,9 +1428,10 @@ fwi_status fwi_plan_create(const fwi_grid *grid, const fwi_acq *acq, const fwi_e
         // the batched kernels address a shot group's records, the model and
         // a partial gradient with 32-bit byte offsets below 2^31
         const long long lim = (1LL << 31) - 64LL * Nx;
-        // the two-step adjoint addresses a group's three pressure levels
-        // (consecutive store levels, the padded shots' ST floats apart)
-        // through one buffer resource
+        // the two-step adjoint addresses a group's pressure levels (consecutive
+        // store levels, the padded shots' ST floats apart) through one buffer
+        // resource.  It reads two; the bound is that of three, so that the
+        // plans accepted with adj_two_step = 2 stay the same.
         auto adj2_fits = [&](int sg) {
             const long long Sp = (p->S + sg - 1) / sg * sg;
             return (2LL * Sp + sg) * p->ST * 4 < lim;
@@ -1440,7 +1442,8 @@ fwi_status fwi_plan_create(const fwi_grid *grid, const fwi_acq *acq, const fwi_e
         // Shot groups of the one-step kernels: with the two-step adjoint (they
         // then only run what a forward segment leaves over) two shots a wave,
         // or one when even 16-row bands of two-shot waves number fewer than
-        // two per SIMD; without it up to four.  One column per lane.
+        // two per SIMD of 256 compute units; without it up to four.  One column
+        // per lane.
         int spg = ex.shots_per_group, cols = ex.lane_cols;
         if (spg == 0) {
             if (adj2_wanted) {

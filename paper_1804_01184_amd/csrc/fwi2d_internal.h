@@ -214,7 +214,6 @@ struct FwdStep {
     const float *Q;     // [S][nt] time integral of the wavelet at n+1/2
     int n;              // time step being taken (n -> n+1)
 };
-// Two forward steps n -> n+2: pmid receives p^{n+1} and its split.
 // Two forward steps n, n+1.  p^{n+1} goes to pmid (midw 0), or, when the
 // level is only sampled, just its receiver nodes go to `nodes` (midw 1), or
 // nothing is kept (midw 2).  The nodes are listed by shot, strip (the one
@@ -272,8 +271,8 @@ void launch_fused_fwd(const Geo &g, const float *tabs, const float *model,
 void launch_fused_adj(const Geo &g, const float *tabs, const float *model, const Sweep &sw,
                       const AdjStep &a, hipStream_t st, hipEvent_t e0 = nullptr,
                       hipEvent_t e1 = nullptr);
-// sw: a decomposition made with steps = 2 and the shots per group of the
-// one-step adjoint (the two share the partial gradients of each group).
+// sw: a decomposition made with steps = 2; gpart holds a partial gradient per
+// group of it.
 void launch_fused_adj2(const Geo &g, const float *tabs, const float *model, const Sweep &sw,
                        const AdjStep2 &a, hipStream_t st, hipEvent_t e0 = nullptr,
                        hipEvent_t e1 = nullptr);

@@ -364,7 +364,9 @@ typedef __bf16 v8bf __attribute__((ext_vector_type(8)));
 // h l, l h; the dropped ones are within 2^-24 of the product, the size of an FP32
 // rounding of it.  Against FP64 sums over the same tables the data are off by 1.3
 // to 2.3e-7 at 9 to 53 sources (FP32 matrix instructions: 1.3 to 4.9e-7), the
-// gradients by 0.5 to 3.7e-7 (0.6 to 4.4e-7).
+// gradients by 0.5 to 3.7e-7 (0.6 to 4.4e-7).  The range is narrower than FP32's:
+// below about 2^-110 the low parts fall under the smallest bf16 and vanish, and an
+// infinite value gives NaN (inf - inf).
 struct Split3 {
     unsigned h, m, l;
 };

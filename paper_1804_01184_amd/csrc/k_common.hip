@@ -526,7 +526,8 @@ __global__ void k_descent_apply(long long n, const float *m, const float *m0, co
 
 // out[0] = sum a^2 + sum b^2, out[1] = max |a|, |b| in one workgroup (there is
 // no memory for the partial sums of several): per-thread strided passes in a
-// fixed order, then a fixed tree, in FP64 (the same bits on every call).
+// fixed order, four FP32 sums a thread, added up in FP64 by a fixed tree (the
+// same bits on every call).
 //
 // Memory latency bounds it: one compute unit, so as many bytes in flight as it
 // can hold.  16 waves, each thread with four loads of a and four of b at a time, V

@@ -10,13 +10,13 @@
 // are halo (the stencil reaches 3 columns through the two half steps).  The
 // vertical parts of the stencils live in per-lane register windows (the
 // rows above and below the current one); the horizontal parts take the
-// neighbouring lane's edge columns with DPP wave shifts, so the kernels use
-// no LDS and no barriers: waves are independent and occupancy is limited
-// only by registers.  Velocity and pressure half-steps are fused: the new
-// velocities of a row are formed and consumed by the new pressure of the
-// same row in registers, so every wavefield value is read once and written
-// once per step (ping-pong buffers, since neighbouring strips and bands
-// still read the old level).
+// neighbouring lane's edge columns with DPP wave shifts, so the kernels need
+// no barriers and share nothing between waves (k_adj2 keeps what waits for
+// its second step in LDS words of the lane's own).  Velocity and pressure
+// half-steps are fused: the new velocities of a row are formed and consumed
+// by the new pressure of the same row in registers, so every wavefield value
+// is read once and written once per step (ping-pong buffers, since
+// neighbouring strips and bands still read the old level).
 //
 // A wave advances SPG shots of the same model together, row by row: the
 // model coefficients of a row are read once for all of them, and in the
@@ -30,13 +30,13 @@
 // a row of work and no register copies (which would wait for them) are
 // needed.  The adjoint reads the values it needs only at the end of a row
 // (the partial gradient) into a single set, issued at the start of the row
-// before the next row's loads.  Loads are unconditional: rows outside the grid or past
-// the band are read through an out-of-range lane offset, which returns zero
-// without touching memory, so the memory counters see the same sequence on
-// every row.
+// before the next row's loads.  Loads are unconditional: rows outside the
+// grid or past the band are read through an out-of-range lane offset, which
+// returns zero without touching memory, so the memory counters see the same
+// sequence on every row.
 //
 // Receiver sampling is a separate small launch, and the receivers' sums of the
-// adjoint source (R^T r) are staged per node by one, 64 steps at a time.  The
+// adjoint source (R^T r) are staged per node by one, up to 64 steps at a time.  The
 // kernels only add or write the nodes listed for their strip and row: k_adj
 // and k_adj2 add the staged sums to the new adjoint pressure, and k_fwd2 writes
 // the receiver nodes of an intermediate level that is only sampled, for a node
@@ -1217,9 +1217,9 @@ __global__ void __launch_bounds__(NTHR)
 // model and read and write the partial gradient once.  Four shots fit the 256
 // registers of two waves a SIMD (three with two shots) because the values that
 // wait three rows sit in LDS.  us per launch on one and the same buffer, before
-// and after: 958 and 898 (64 shots of 1081 x 1081, 4 shots a wave, 91 rows),
-// 1865 and 1537 (32 of 2081 x 2081; 4, 49), 172 and 155 (40 of 481 x 481; 2,
-// 49); 18 + 10 f + 18 / SPG bytes a cell-step became 16 + 4 f + 18 / SPG, f the
+// and after: 958 and 886 (64 shots of 1081 x 1081, 4 shots a wave, 91 rows),
+// 1865 and 1590 (32 of 2081 x 2081; 4, 64), 172 and 158 (40 of 481 x 481; 2,
+// 20); 18 + 10 f + 18 / SPG bytes a cell-step became 16 + 4 f + 18 / SPG, f the
 // layer's share of the cells.
 
 template <int SPG, int C>
