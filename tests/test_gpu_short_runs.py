@@ -1,8 +1,8 @@
 """Checkpoints on every step or two: a tile launch does not get to spread its
 load, store and overlap over several steps there, and the default plan is not
-slower than the strip kernels for it.  (1.15 times allows for the placement of
-the two workspaces; with the steps per launch chosen regardless of the
-checkpoints the three took 2.0, 1.26 and 1.5 times as long.)"""
+slower than the strip kernels for it, in one workspace.  (1.1 times
+allows for noise; with the steps per launch chosen regardless of the checkpoints
+the three took 2.0, 1.26 and 1.5 times as long.)"""
 import time
 
 import numpy as np
@@ -26,17 +26,20 @@ def test_close_checkpoints_not_slower_than_strips(nz, nx, S, nt, ckpt):
     grid = api.Grid(nz, nx, h, h, 20, nt, 0.5 * h / vmax, vmax)
     vp = torch.full((nz, nx), 2000.0, device="cuda")
     f = torch.as_tensor(rng.standard_normal(nt).astype(np.float32), device="cuda")
-    obs = torch.zeros((S, 40, nt), device="cuda")
+    adj = torch.ones((S, 40, nt), device="cuda")
     plans = [api.Plan(grid, src, rec, ckpt_every=ckpt, **kw) for kw in ({}, {"two_step": 2})]
+    ws = torch.empty(max(p.workspace_bytes(api.L.FWI_OP_GRADIENT) for p in plans) + 256,
+                     dtype=torch.uint8, device="cuda")
     best = [np.inf, np.inf]
     for _ in range(6):
         for i, p in enumerate(plans):
             torch.cuda.synchronize()
             t = time.perf_counter()
-            p.gradient("vp-rho", vp, vp, f, obs)
+            p.forward_keep("vp-rho", vp, vp, f, ws)
+            p.adjoint_kept("vp-rho", vp, vp, f, adj, ws)
             torch.cuda.synchronize()
             best[i] = min(best[i], time.perf_counter() - t)
-    assert best[0] <= 1.15 * best[1], best
+    assert best[0] <= 1.1 * best[1], best
 
 
 def test_one_step_takes_one_step_launch():
