@@ -7,9 +7,10 @@ separately on a short run of the real grid and shot count, with the whole
 pressure history kept: each candidate is timed by its own launches, using
 the library's per-launch HIP event timing.  Setting any of them puts a plan
 on the strip kernels; a plan that sets none may run on the tile kernels, and
-chooses by the library's own rules.  So the best decomposition is timed
-against that plan at the end, over a whole gradient, and plan_keywords and
-tuned_plan leave the decomposition out where the default plan is faster.
+chooses by the library's own rules.  So for sizes that may run on tiles the
+best decomposition is timed against that plan at the end, over a whole
+gradient, and plan_keywords and tuned_plan leave the decomposition out where
+the default plan is faster.
 
 The two-step adjoint takes the shot groups of the one-step kernels (which the
 tuner sets); it is chosen when its time per step beats the one-step kernel's,
@@ -182,6 +183,12 @@ def _gradient_ms(grid, src_xz, rec_xz, ws, device, reps, **decomp):
     return min(a.elapsed_time(b) for a, b in zip(ev, ev[1:]))
 
 
+# Padded nodes over all shots up to which a plan may run on the tile kernels.  Beyond,
+# the default is a strip decomposition like those measured (within 1 % of the best of
+# them at the benchmark shapes), and a 48-step history would take tens of gigabytes.
+TILE_NODES = 4_000_000
+
+
 def default_wins(grid, src_xz, rec_xz, best, nt_probe=48, reps=3, device=None):
     """Whether the plan without a decomposition runs a gradient faster than the
     one with `best`, both in the same workspace (the strip kernels' time moves
@@ -275,7 +282,7 @@ def _tuned_entry(grid, src_xz, rec_xz, force, verbose, device):
             best["two_step"] = 1
     else:
         best["two_step"] = 1
-    wins = default_wins(grid, src_xz, rec_xz, best, device=device)
+    wins = Nz * Nx * S <= TILE_NODES and default_wins(grid, src_xz, rec_xz, best, device=device)
     if verbose:
         print(f"  default plan {'faster' if wins else 'not faster'}", flush=True)
     cache = load_cache()

@@ -59,3 +59,23 @@ def test_a_decomposition_that_wins_is_kept(tmp_path, monkeypatch):
         assert autotune.tune(g, src, rec) == best
         assert autotune.tuned_plan(g, src, rec).info["band_rows"] == \
             api.Plan(g, src, rec, **want).info["band_rows"]
+
+
+def test_large_shapes_are_not_run_against_the_default(tmp_path, monkeypatch):
+    """Beyond the tile kernels' sizes the comparison, whose 48-step history would
+    take tens of gigabytes there, is left out."""
+    torch = pytest.importorskip("torch")
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_1804_01184_amd import api, autotune
+    monkeypatch.setenv("FWI2D_TUNE_CACHE", str(tmp_path / "tune.json"))
+    for name in ("candidates", "candidates2", "candidates_adj2"):
+        monkeypatch.setattr(autotune, name, lambda Nz, Nx, S: [(32, 2, 1)])
+
+    def never(*a, **kw):
+        raise AssertionError("compared with the default plan")
+
+    monkeypatch.setattr(autotune, "default_wins", never)
+    g = api.Grid(601, 601, 5.0, 5.0, 40, 40, 0.001, 2400.0)
+    src = [[300.0 + 100.0 * s, 900.0] for s in range(10)]
+    assert autotune.plan_keywords(g, src, [[600.0, 640.0]])["adj_two_step_band_rows"] == 32
